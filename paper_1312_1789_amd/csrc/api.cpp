@@ -218,7 +218,6 @@ Layout make_layout(const nbody_config &c)
     L.act = take(n * sizeof(int32_t));
     L.sched = take(nb * (2 * sizeof(int64_t) + sizeof(int32_t)));
     L.scal = take(sizeof(DevScalars));
-    L.energy = take(2 * ((n + 255) / 256) * sizeof(double));
     L.init = 0;
     L.irec = take(n * 112);
     L.total = off;
@@ -762,9 +761,9 @@ nbody_status nbody_energy(nbody_ctx *ctx, const nbody_state *st, double *ekin, d
     nbody_status s = check_state(ctx, st);
     if (s != NBODY_OK) return s;
     if (!ekin || !epot) return fail(NBODY_E_INVALID, "ekin and epot are required");
-    int np = 0;
-    double *part = ws_at<double>(ctx, ctx->lay.energy);
-    NB_HIP(nb::launch_energy(ctx->cfg.n, ctx->cfg.n, hard_count(ctx->cfg), ctx->cfg.eps2, st->m, st->x, st->v, part, &np,
+    const int np = nb::energy_partials(ctx->cfg.n);
+    double *part = ws_at<double>(ctx, ctx->lay.part);   // the force scratch
+    NB_HIP(nb::launch_energy(ctx->cfg.n, ctx->cfg.n, hard_count(ctx->cfg), ctx->cfg.eps2, st->m, st->x, st->v, part,
                              ctx->stream));
     std::vector<double> h(2 * size_t(np));
     NB_HIP(hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));

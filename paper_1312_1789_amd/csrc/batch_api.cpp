@@ -18,7 +18,7 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct BatchLayout {
     size_t off, ord, cid, tnext, bmin, bcnt, blk, plan, nact, aoff, ioff, poff, jchunk, split, tcur, rank, ctr, act,
-        part, force, rec, energy, total;
+        part, force, rec, total;
 };
 
 int64_t max_cluster(const std::vector<int64_t> &off)
@@ -33,13 +33,6 @@ int64_t sched_blocks(const std::vector<int64_t> &off)
 {
     int64_t s = 0;
     for (size_t c = 0; c + 1 < off.size(); ++c) s += (off[c + 1] - off[c] + nb::kBatchSchedBlock - 1) / nb::kBatchSchedBlock;
-    return s;
-}
-
-int64_t sum_energy_blocks(const std::vector<int64_t> &off)
-{
-    int64_t s = 0;
-    for (size_t c = 0; c + 1 < off.size(); ++c) s += (off[c + 1] - off[c] + 255) / 256;
     return s;
 }
 
@@ -76,7 +69,6 @@ BatchLayout make_batch_layout(const nbody_config &c, const std::vector<int64_t> 
     L.part = take(12 * (size_t(nb::kBatchMaxRows) + n) * sizeof(double));
     L.force = take(12 * n * sizeof(double));
     L.rec = take(n * size_t(std::max(nb::record_bytes(c.order, c.precision), nb::record_bytes(8, NBODY_FP64))));
-    L.energy = take(2 * size_t(sum_energy_blocks(off)) * sizeof(double));
     L.total = at;
     return L;
 }
@@ -422,7 +414,7 @@ nbody_status nbody_batch_energy(nbody_batch *b, const nbody_state *st, double *e
     nbody_status s = check_bstate(b, st);
     if (s != NBODY_OK) return s;
     if (!ekin || !epot) return fail(NBODY_E_INVALID, "ekin and epot are required");
-    double *part = at<double>(b, b->lay.energy);
+    double *part = b->L.part;   // the force scratch: 12 (2^22 + n) doubles; the partials take at most n
     std::vector<int> np(size_t(b->nc));
     std::vector<size_t> first(size_t(b->nc));
     size_t used = 0;
@@ -430,8 +422,9 @@ nbody_status nbody_batch_energy(nbody_batch *b, const nbody_state *st, double *e
         const int64_t o = b->off[size_t(c)], nn = b->off[size_t(c) + 1] - o;
         const int64_t nh = b->cfg.eps2 == 0.0 ? nn : b->cfg.n_hard;
         first[size_t(c)] = used;
+        np[size_t(c)] = nb::energy_partials(nn);
         NB_HIP(nb::launch_energy(nn, b->cfg.n, nh, b->cfg.eps2, st->m + o, st->x + o, st->v + o, part + used,
-                                 &np[size_t(c)], b->stream));
+                                 b->stream));
         used += 2 * size_t(np[size_t(c)]);
     }
     std::vector<double> h(used);

@@ -69,7 +69,6 @@ struct Layout {
     size_t act;        // active indices, n int32
     size_t sched;      // scheduler per-block scratch (min ticks, counts, offsets)
     size_t scal;       // device scalars: t_next, n_act, counters
-    size_t energy;     // energy partials
     size_t init;       // init scratch: 4 x [3][n] doubles (a, j, s, c of the two passes)
     size_t irec;       // init records (FP64 order-8 layout), n * 112
     size_t total;
@@ -214,9 +213,11 @@ hipError_t launch_schedule(int64_t n, const int64_t *t_tick, const int32_t *leve
 hipError_t launch_init_levels(const nbody_config &c, const nbody_state &st, const double *a, const double *j,
                               hipStream_t s);
 
-// Energy partials of n particles whose [3][.] arrays have row stride `stride`.
+// Energy of n particles whose [3][.] arrays have row stride `stride`:
+// energy_partials(n) pairs (kinetic, potential), to be summed in order.
+int energy_partials(int64_t n);
 hipError_t launch_energy(int64_t n, int64_t stride, int64_t n_hard, double eps2, const double *m, const double *x,
-                         const double *v, double *partials, int *n_partials, hipStream_t s);
+                         const double *v, double *partials, hipStream_t s);
 
 }  // namespace nb
 

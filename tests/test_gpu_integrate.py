@@ -205,6 +205,25 @@ def test_energy_parity():
     assert abs(W - Wo) <= 1e-12 * abs(Wo)
 
 
+@pytest.mark.parametrize("n", [2, 63, 65, 511, 512, 513, 1025, 5003])
+@pytest.mark.parametrize("n_hard, eps2", [(0, 1e-8), (2, 1e-4), (600, 1e-4), (0, 0.0)])
+def test_energy_pair_tiles(n, n_hard, eps2):
+    """Around the edges of the energy's row tiles (512) and j chunks (64),
+    with none, some and all pairs unsoftened and unequal masses.  The terms of
+    each sum have one sign, so any order of at most a few thousand of them
+    stays within 1e-12 relative (a few hundred roundings of 1e-16 at most per
+    chain, random in sign)."""
+    n_hard = min(n_hard, n)
+    model = nbody_ics.plummer(n, 300 + n)
+    m = model.m * np.random.default_rng(n).uniform(0.5, 2.0, n)
+    sim = _sim(nbody_ics.Model(m, model.x, model.v), 4, n_hard=n_hard, eps2=eps2)
+    T, W = sim.energy()
+    To, Wo = oracle.energy(_ocfg(sim), m, model.x, model.v)
+    say("energy n=%d n_hard=%d eps2=%g T %.2e W %.2e" % (n, n_hard, eps2, T / To - 1, W / Wo - 1))
+    assert abs(T - To) <= 1e-12 * abs(To)
+    assert abs(W - Wo) <= 1e-12 * abs(Wo)
+
+
 def test_c1_integration_vs_oracle():
     """The small parity workload: Plummer n=1024, 4th order, eta=0.01,
     eps=1e-4, FP64, t = 0 -> 0.125: same block-step sequence at the start,
