@@ -64,7 +64,7 @@ int64_t hard_count(const nbody_config &c) { return c.eps2 == 0.0 ? c.n : c.n_har
 
 // Force arguments and the launch shape for n_act active particles: the shape
 // set by nbody_set_launch, else the tuned table's, else the default.
-nb::ForceArgs force_args(nbody_ctx *ctx, const void *rec, int64_t n_act, const int32_t *act, double *acc,
+nb::ForceArgs force_args(nbody_ctx *ctx, int precision, const void *rec, int64_t n_act, const int32_t *act, double *acc,
                          double *jrk, double *snp, double *crk, double *pot)
 {
     nb::ForceArgs a{};
@@ -93,15 +93,11 @@ nb::ForceArgs force_args(nbody_ctx *ctx, const void *rec, int64_t n_act, const i
         a.ni = ctx->tune[r].ni;
         a.block = ctx->tune[r].block;
         a.n_split = ctx->tune[r].n_split;
+        a.fine = true;
         a.jpath = ctx->tune[r].jpath;
     } else {
-        // untuned default: the wave j-split kernel for active sets of up to 32
-        // (the autotuner's choice there on MI355X in every precision), else
-        // workgroups no wider than the active set needs
-        a.ni = 1;
-        a.block = n_act <= 64 ? 64 : (n_act <= 128 ? 128 : 256);
+        nb::default_shape(precision, a.n, n_act, &a.ni, &a.block, &a.jpath);
         a.n_split = 0;
-        a.jpath = n_act <= 32 ? 3 : 0;
     }
     return a;
 }
@@ -109,7 +105,7 @@ nb::ForceArgs force_args(nbody_ctx *ctx, const void *rec, int64_t n_act, const i
 nbody_status run_force(nbody_ctx *ctx, int order, int precision, const void *rec, int64_t n_act,
                        const int32_t *act, double *acc, double *jrk, double *snp, double *crk, double *pot)
 {
-    const nb::ForceArgs a = force_args(ctx, rec, n_act, act, acc, jrk, snp, crk, pot);
+    const nb::ForceArgs a = force_args(ctx, precision, rec, n_act, act, acc, jrk, snp, crk, pot);
     NB_HIP(nb::launch_force(order, precision, a, ctx->stream, &ctx->last_shape));
     ctx->stats.interactions += double(n_act) * double(ctx->cfg.n);
     return NBODY_OK;
@@ -124,7 +120,7 @@ nbody_status run_predict_force(nbody_ctx *ctx, const nbody_state *st, int64_t t,
                                double *acc, double *jrk, double *snp, double *crk, double *pot, bool *fused)
 {
     const nbody_config &c = ctx->cfg;
-    const nb::ForceArgs a = force_args(ctx, ctx->ws + ctx->lay.rec, n_act, act, acc, jrk, snp, crk, pot);
+    const nb::ForceArgs a = force_args(ctx, c.precision, ctx->ws + ctx->lay.rec, n_act, act, acc, jrk, snp, crk, pot);
     const bool f = ctx->fuse && a.jpath == 3;
     if (fused) *fused = f;
     if (f) {
@@ -371,7 +367,7 @@ nbody_status nbody_autotune(nbody_ctx *ctx, int64_t max_n_act, int32_t reps)
                     // the wave j-split kernel ignores ni and block, and serves small active sets
                     if (jpath == 3 && (ni != 1 || block != 64 || na > 64)) continue;
                     const int64_t prow = nb::part_rows_for(n);
-                    const int base = nb::auto_split_path(n, na, ni, block, jpath, prow);
+                    const int base = nb::auto_split(c.precision, n, na, ni, jpath, prow);
                     int prev = -1;
                     for (int mult : {1, 2, 4}) {   // splits base / 2, base, base * 2
                         int sp = mult == 1 ? base / 2 : (mult == 2 ? base : base * 2);
@@ -396,6 +392,7 @@ nbody_status nbody_autotune(nbody_ctx *ctx, int64_t max_n_act, int32_t reps)
                         a.ni = ni;
                         a.block = block;
                         a.n_split = sp;
+                        a.fine = true;
                         a.jpath = jpath;
                         hipError_t e = nb::launch_force(c.order, c.precision, a, ctx->stream, nullptr);
                         if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
@@ -465,15 +462,16 @@ nbody_status nbody_init(nbody_ctx *ctx, nbody_state *st)
     void *irec = ctx->ws + ctx->lay.irec;
     int32_t *all = ws_at<int32_t>(ctx, ctx->lay.act);
     NB_HIP(nb::launch_iota(c.n, all, ctx->stream));
-    // pass 1: acceleration and jerk from positions and velocities
+    // pass 1: acceleration and jerk from positions and velocities, the terms of order 4
     NB_HIP(nb::launch_pack_f64(c.n, st->m, st->x, st->v, nullptr, nullptr, irec, ctx->stream));
-    s = run_force(ctx, 8, NBODY_FP64, irec, c.n, all, st->d[0], st->d[1], nullptr, nullptr, nullptr);
+    s = run_force(ctx, 4, NBODY_FP64, irec, c.n, all, st->d[0], st->d[1], nullptr, nullptr, nullptr);
     if (s != NBODY_OK) return s;
     if (c.order >= 6) {
         // pass 2: snap and crackle, using the pass-1 acceleration and jerk
         NB_HIP(nb::launch_pack_f64(c.n, st->m, st->x, st->v, st->d[0], st->d[1], irec, ctx->stream));
-        s = run_force(ctx, 8, NBODY_FP64, irec, c.n, all, nullptr, nullptr, st->d[2], st->d[3], nullptr);
-        if (s != NBODY_OK) return s;
+        const nb::ForceArgs a = force_args(ctx, NBODY_FP64, irec, c.n, all, nullptr, nullptr, st->d[2], st->d[3], nullptr);
+        NB_HIP(nb::launch_force_high(a, ctx->stream, &ctx->last_shape));
+        ctx->stats.interactions += double(c.n) * double(c.n);
     }
     if (nb::pn_on(c))   // hard pairs at t = 0, from the state itself, after pass 2 (Newtonian a, jerk)
         NB_HIP(nb::launch_pn(c, *st, nullptr, 0, all, c.n, st->d[0], st->d[1], c.order >= 6 ? st->d[2] : nullptr,
@@ -668,7 +666,7 @@ nbody_status step_impl(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, bool ch
     if (tm) NB_HIP(hipEventRecord(ctx->ev[2], ctx->stream));
     double *F = ws_at<double>(ctx, ctx->lay.force);
     double *acc = F, *jrk = F + 3 * n_act, *snp = F + 6 * n_act, *crk = F + 9 * n_act;
-    const nb::ForceArgs shape = force_args(ctx, nullptr, n_act, act, acc, jrk, snp, crk, nullptr);
+    const nb::ForceArgs shape = force_args(ctx, c.precision, nullptr, n_act, act, acc, jrk, snp, crk, nullptr);
     if (ctx->fuse && shape.jpath == 3) {
         // predictor inside the force kernel: the predictor phase is empty
         if (tm) NB_HIP(hipEventRecord(ctx->ev[3], ctx->stream));

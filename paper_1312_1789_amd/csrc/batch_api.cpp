@@ -295,12 +295,12 @@ nbody_status nbody_batch_init(nbody_batch *b, nbody_state *st)
     const nbody_config &c = b->cfg;
     const nb::BatchLaunch &L = b->L;
     void *rec = b->ws + b->lay.rec;
-    // every particle active at t = 0; FP64 order-8 pairwise terms
+    // every particle active at t = 0; the plan's partials hold the terms of order 8
     NB_HIP(nb::batch_schedule(L, *st, 1, 8, b->stream));
-    // pass 1: acceleration and jerk from positions and velocities
+    // pass 1: acceleration and jerk from positions and velocities, the terms of order 4
     NB_HIP(nb::launch_pack_f64(c.n, st->m, st->x, st->v, nullptr, nullptr, rec, b->stream));
-    NB_HIP(nb::batch_force(L, 8, NBODY_FP64, rec, b->stream));
-    NB_HIP(nb::batch_reduce(L, 8, st->d[0], st->d[1], nullptr, nullptr, b->stream));
+    NB_HIP(nb::batch_force(L, 4, NBODY_FP64, rec, b->stream));
+    NB_HIP(nb::batch_reduce(L, 4, st->d[0], st->d[1], nullptr, nullptr, b->stream));
     if (c.order >= 6) {
         // pass 2: snap and crackle, using the pass-1 acceleration and jerk
         NB_HIP(nb::batch_requeue(L, b->stream));

@@ -41,7 +41,7 @@ __device__ __forceinline__ void store_rows(int64_t n_act, int64_t row0, int spli
                                            double *__restrict__ o_crk, double *__restrict__ o_pot,
                                            double *__restrict__ part)
 {
-    constexpr int NV = 3 * (P / 2);
+    constexpr int NV = 3 * (P / 2), C0 = Pol::kFirst;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
         const int64_t q = row0 + int64_t(k) * blockDim.x;
@@ -50,7 +50,7 @@ __device__ __forceinline__ void store_rows(int64_t n_act, int64_t row0, int spli
         if (n_split == 1) {
             double *outs[4] = {o_acc, o_jrk, o_snp, o_crk};
 #pragma unroll
-            for (int c = 0; c < NV; ++c) {
+            for (int c = C0; c < NV; ++c) {
                 double *o = outs[c / 3];
                 if (o) o[(c % 3) * n_act + q] = acc[k][c];
             }
@@ -59,13 +59,13 @@ __device__ __forceinline__ void store_rows(int64_t n_act, int64_t row0, int spli
             double *base = part + q * n_split + split;
             const int64_t cs = n_act * n_split;
 #pragma unroll
-            for (int c = 0; c < NV; ++c) base[c * cs] = acc[k][c];
+            for (int c = C0; c < NV; ++c) base[(c - C0) * cs] = acc[k][c];
             if (Pol::kWithPot) base[NV * cs] = -pot;
         } else {
             constexpr int NC = NV + 1;
             double *base = part + int64_t(split) * NC * n_act;
 #pragma unroll
-            for (int c = 0; c < NV; ++c) base[int64_t(c) * n_act + q] = acc[k][c];
+            for (int c = C0; c < NV; ++c) base[int64_t(c - C0) * n_act + q] = acc[k][c];
             if (Pol::kWithPot) base[int64_t(NV) * n_act + q] = -pot;
         }
     }
@@ -87,6 +87,7 @@ k_force(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__r
     using ET = typename Pol::ET;
     const ET e2 = ET(eps2);
     const int64_t row0 = int64_t(blockIdx.x) * blockDim.x * NI + threadIdx.x;
+    if (row0 - int64_t(threadIdx.x & 63) >= n_act) return;   // a wave of padding rows only (no barrier follows)
     const int split = blockIdx.y;
     const int64_t j0 = int64_t(split) * j_chunk;
     const int64_t j1 = (j0 + j_chunk < n) ? j0 + j_chunk : n;
@@ -246,7 +247,9 @@ k_force_ws(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *
 // kSplitFastestAbove splits: a workgroup's lanes write consecutive rows);
 // SF = true, part[component][row][split] (kernels A and B with more splits,
 // and the wave j-split kernels: a group's lanes read consecutive splits).
-template <int P, int L, bool SF>
+// C0: the first component of the launch (Pol::kFirst); the partials hold
+// those from it on.
+template <int P, int L, bool SF, int C0>
 __global__ void __launch_bounds__(256)
 k_reduce(const double *__restrict__ part, int64_t n_act, int n_split, double *__restrict__ o_acc,
          double *__restrict__ o_jrk, double *__restrict__ o_snp, double *__restrict__ o_crk,
@@ -256,7 +259,7 @@ k_reduce(const double *__restrict__ part, int64_t n_act, int n_split, double *__
     constexpr int NC = NV + 1;
     const int64_t g = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / L;   // output index
     const int l = int(threadIdx.x) % L;
-    const bool valid = g < n_act * NC;
+    const bool valid = g < n_act * (o_pot ? NC : NV - C0);   // the potential's sums exist only when asked for
     const int64_t gg = valid ? g : 0;
     const int c = int(gg / n_act);
     const int64_t q = gg - int64_t(c) * n_act;
@@ -279,23 +282,24 @@ k_reduce(const double *__restrict__ part, int64_t n_act, int n_split, double *__
 #pragma unroll
     for (int m = L / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
     if (!valid || l != 0) return;
-    if (c == NV) {
+    if (!C0 && c == NV) {
         if (o_pot) o_pot[q] = s;
         return;
     }
     double *outs[4] = {o_acc, o_jrk, o_snp, o_crk};
-    double *o = outs[c / 3];
+    double *o = outs[(c + C0) / 3];
     if (o) o[(c % 3) * n_act + q] = s;
 }
 
-template <int P, bool SF>
+template <int P, bool SF, int C0 = 0>
 hipError_t launch_reduce(const ForceArgs &a, int n_split, hipStream_t s)
 {
-    const int64_t outs = a.n_act * (3 * (P / 2) + 1);
+    static_assert(C0 % 3 == 0, "whole vectors");
+    const int64_t outs = a.n_act * (3 * (P / 2) - C0 + (a.out[4] ? 1 : 0));
     // lanes per output: enough that each lane adds at most about 8 splits
     const int L = n_split <= 8 ? 1 : n_split <= 32 ? 4 : n_split <= 128 ? 16 : 64;
     const unsigned blocks = unsigned((outs * L + 255) / 256);
-#define NB_RED(LL) hipLaunchKernelGGL((k_reduce<P, LL, SF>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
+#define NB_RED(LL) hipLaunchKernelGGL((k_reduce<P, LL, SF, C0>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
                                       a.out[0], a.out[1], a.out[2], a.out[3], a.out[4])
     if (L == 1) NB_RED(1);
     else if (L == 4) NB_RED(4);
@@ -366,6 +370,37 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
     return a.out[4] ? run_pot<P, true>(precision, a, s, sh) : run_pot<P, false>(precision, a, s, sh);
 }
 
+// The default j-split of kernels A and B, sized in waves of 64 NI rows (wt row
+// tiles) that walk c particles each:
+//  - many (wt n / 128 >= 16384, several rounds of waves on the chip): about
+//    32768 waves of at least 128 particles (256 if that still gives 16384), so
+//    that the last round is a small part of the call, and at most 8192 (a wave
+//    is then some microseconds of work to a 100-byte partial row).  About 8192 waves, two or
+//    three rounds, had cost 10-30% of it: n_act = n = 90000 MIXED order 6 11219
+//    us with 6 splits, 9280 with 23; n = 262144, n_act = 3001 994 with 171, 926
+//    with 683;
+//  - otherwise a MIXED row takes its FP32 chunks (128 particles) one to a wave;
+//  - FP64 and DS sums have no chunks to keep, and a wave that walks 128
+//    particles alone on its SIMD is all latency (28 us at order 4, FP64, for
+//    any n): as few as 32 each, about 3072 waves, at most about 1250 splits (the
+//    sum of the partials grows with them).  n = 1024, n_act = 100 FP64 order 4:
+//    20.2 us with 8 splits of 128, 9.1 with 32 of 32 (order 8: 40.9, 13.1); n =
+//    16384, n_act = 400: 26.0 with 128, 22.6 with 64.
+int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
+{
+    const int64_t wt = (n_act + 64 * ni - 1) / (64 * ni);
+    const auto up = [](int64_t v, int64_t g) { return (v + g - 1) / g * g; };
+    if (wt * n >= int64_t(16384) * 128) {
+        int64_t c = up(wt * n / 32768, 128);
+        if (c < 256 && wt * n >= int64_t(16384) * 256) c = 256;
+        return c < 8192 ? c : 8192;
+    }
+    if (precision == NBODY_MIXED) return kMixedChunk;
+    int64_t c = wt * n / 3072 > n / 1250 ? wt * n / 3072 : n / 1250;
+    c = up(c, 32);
+    return c < 32 ? 32 : (c > 128 ? 128 : c);
+}
+
 }  // namespace
 
 int record_bytes(int order, int precision)
@@ -374,55 +409,73 @@ int record_bytes(int order, int precision)
     return order == 8 ? 80 : 64;
 }
 
-// Number of j-splits: enough waves to cover every SIMD several times when the
-// active set is small, bounded by the partial-sum scratch and by keeping at
-// least 256 j per split.
-int auto_split(int64_t n, int64_t n_act, int ni, int block, int64_t part_rows)
+// Shortest j-split: a MIXED split holds whole FP32 chunks; the others' default
+// and tuned splits may be shorter (kernel C walks tiles of 64).
+int64_t split_grain(int precision, int jpath, bool fine)
 {
-    const int64_t per_block = int64_t(block) * ni;
-    const int64_t tiles = (n_act + per_block - 1) / per_block;
-    const int64_t waves = tiles * (block / 64);
-    const int64_t target_waves = 256 * 4 * 8;   // CUs x SIMDs x waves per SIMD
-    int64_t sp = (target_waves + waves - 1) / waves;
-    const int64_t max_by_n = n / kMixedChunk > 0 ? n / kMixedChunk : 1;   // splits of at least one FP32 chunk
-    const int64_t max_by_part = part_rows / (n_act > 0 ? n_act : 1);
-    if (sp > max_by_n) sp = max_by_n;
-    if (sp > max_by_part) sp = max_by_part;
+    if (precision == NBODY_MIXED || !fine) return kMixedChunk;
+    return jpath == 3 ? 64 : 32;
+}
+
+int auto_split(int precision, int64_t n, int64_t n_act, int ni, int jpath, int64_t part_rows)
+{
+    int64_t sp;
+    if (jpath == 3) {
+        // kernel C: one 64-lane workgroup per 1, 4 or 16 rows and split.  Split
+        // counts giving about 512, 1024 and 2048 workgroups were the fastest on
+        // MI355X (n = 2^17 and 2^20, orders 6 and 8, with and without the
+        // predictor inside): shorter splits cost more in per-workgroup set-up and
+        // in the split reduction than they add in parallelism.
+        const int64_t rw = n_act <= 1 ? 1 : (n_act <= 4 ? 4 : 16);
+        const int64_t tiles = (n_act + rw - 1) / rw;
+        const int64_t target = rw == 1 ? 512 : (rw == 4 ? 1024 : 2048);
+        const int64_t g = split_grain(precision, 3, true);
+        sp = (target + tiles - 1) / tiles;
+        if (sp > n / g) sp = n / g;
+    } else {
+        const int64_t c = default_chunk(precision, n, n_act, ni);
+        sp = (n + c - 1) / c;
+    }
+    if (sp * n_act > part_rows) sp = part_rows / n_act;
     if (sp > 65535) sp = 65535;
     return sp < 1 ? 1 : int(sp);
 }
 
-int auto_split_path(int64_t n, int64_t n_act, int ni, int block, int jpath, int64_t part_rows)
+void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool fine, int ni, int jpath,
+                 int64_t part_rows, int *n_split, int64_t *j_chunk)
 {
-    if (jpath != 3) return auto_split(n, n_act, ni, block, part_rows);
-    // kernel C: one 64-lane workgroup per 1, 4 or 16 rows and split.  Split
-    // counts giving about 512, 1024 and 2048 workgroups were the fastest on
-    // MI355X (n = 2^17 and 2^20, orders 6 and 8, with and without the
-    // predictor inside): shorter splits cost more in per-workgroup set-up and
-    // in the split reduction than they add in parallelism.
-    const int64_t rw = n_act <= 1 ? 1 : (n_act <= 4 ? 4 : 16);
-    const int64_t tiles = (n_act + rw - 1) / rw;
-    const int64_t target = rw == 1 ? 512 : (rw == 4 ? 1024 : 2048);
-    int64_t sp = (target + tiles - 1) / tiles;
-    const int64_t max_by_n = n / kMixedChunk > 0 ? n / kMixedChunk : 1;
-    const int64_t max_by_part = part_rows / (n_act > 0 ? n_act : 1);
-    if (sp > max_by_n) sp = max_by_n;
-    if (sp > max_by_part) sp = max_by_part;
-    if (sp > 65535) sp = 65535;
-    return sp < 1 ? 1 : int(sp);
-}
-
-void split_shape(int64_t n, int64_t n_act, int n_split_req, int ni, int block, int jpath, int64_t part_rows,
-                 int *n_split, int64_t *j_chunk)
-{
-    int sp = n_split_req > 0 ? n_split_req : auto_split_path(n, n_act, ni, block, jpath, part_rows);
+    int sp = n_split_req > 0 ? n_split_req : auto_split(precision, n, n_act, ni, jpath, part_rows);
     if (n_act > 0 && int64_t(sp) * n_act > part_rows) sp = int(part_rows / n_act);
     if (sp < 1) sp = 1;
-    // split length: a multiple of the MIXED chunk so chunks never straddle splits
+    const int64_t g = split_grain(precision, jpath, fine || n_split_req <= 0);
     int64_t jc = (n + sp - 1) / sp;
-    jc = (jc + kMixedChunk - 1) / kMixedChunk * kMixedChunk;
+    jc = (jc + g - 1) / g * g;
     *j_chunk = jc;
     *n_split = int((n + jc - 1) / jc);
+}
+
+// The launch shape of an untuned call.  Kernel C up to 32 rows; FP64 and DS
+// up to 64 (one row per lane leaves a chip of 1024 SIMDs nearly idle there: n =
+// 30000, 64 rows, FP64 order 8 45.7 us with kernel A, 19.9 with C; MIXED keeps
+// the order of its FP32 sums).  One row per lane beyond: with many waves
+// (default_chunk) the scalar path, whose j records cost no LDS bandwidth (90000
+// rows MIXED order 4: LDS 6261, scalar 5459 us), in workgroups of 128; with few,
+// the LDS path, whose loads run ahead (n = 80000, 200 rows FP64 order 8: scalar
+// 107, LDS 91 us), one wave to a workgroup.
+void default_shape(int precision, int64_t n, int64_t n_act, int *ni, int *block, int *jpath)
+{
+    *ni = 1;
+    const int64_t wt = (n_act + 63) / 64;
+    if (n_act <= (precision == NBODY_MIXED ? 32 : 64)) {
+        *block = 64;
+        *jpath = 3;
+    } else if (wt * n >= int64_t(16384) * 128) {
+        *block = 128;
+        *jpath = 1;
+    } else {
+        *block = 64;
+        *jpath = 2;
+    }
 }
 
 hipError_t launch_split_reduce_sf(int order, const ForceArgs &a, int n_split, hipStream_t s)
@@ -432,6 +485,22 @@ hipError_t launch_split_reduce_sf(int order, const ForceArgs &a, int n_split, hi
     return launch_reduce<8, true>(a, n_split, s);
 }
 
+hipError_t launch_force_high(const ForceArgs &a, hipStream_t s, UsedShape *used)
+{
+    Shape sh{};
+    sh.block = (a.block == 64 || a.block == 128) ? a.block : 256;
+    split_shape(NBODY_FP64, a.n, a.n_act, a.n_split, a.fine, 1, 1, a.part_rows, &sh.n_split, &sh.j_chunk);
+    if (used) *used = UsedShape{1, sh.block, sh.n_split, 1};
+    const dim3 grid{unsigned((a.n_act + sh.block - 1) / sh.block), unsigned(sh.n_split), 1u};
+    hipLaunchKernelGGL((k_force<PolF64High, 8, 1>), grid, dim3(sh.block), 0, s, static_cast<const RecF64<8> *>(a.rec),
+                       a.n, a.act, a.n_act, a.eps2, a.n_hard, sh.j_chunk, sh.n_split, nullptr, nullptr, a.out[2],
+                       a.out[3], nullptr, a.part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || sh.n_split == 1) return e;
+    return sh.n_split > kSplitFastestAbove ? launch_reduce<8, true, PolF64High::kFirst>(a, sh.n_split, s)
+                                           : launch_reduce<8, false, PolF64High::kFirst>(a, sh.n_split, s);
+}
+
 hipError_t launch_force(int order, int precision, const ForceArgs &a, hipStream_t s, UsedShape *used)
 {
     Shape sh{};
@@ -439,7 +508,7 @@ hipError_t launch_force(int order, int precision, const ForceArgs &a, hipStream_
     sh.block = (a.block == 64 || a.block == 128) ? a.block : 256;
     // j path: FP64 reads j records from SGPRs, the FP32 modes from LDS
     sh.jpath = a.jpath >= 1 && a.jpath <= 3 ? a.jpath : (precision == NBODY_FP64 ? 1 : 2);
-    split_shape(a.n, a.n_act, a.n_split, sh.ni, sh.block, sh.jpath, a.part_rows, &sh.n_split, &sh.j_chunk);
+    split_shape(precision, a.n, a.n_act, a.n_split, a.fine, sh.ni, sh.jpath, a.part_rows, &sh.n_split, &sh.j_chunk);
     if (used) *used = UsedShape{sh.jpath == 3 ? 1 : sh.ni, sh.jpath == 3 ? 64 : sh.block, sh.n_split, sh.jpath};
     switch (order) {
     case 4: return run_prec<4>(precision, a, s, sh);

@@ -198,7 +198,7 @@ hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const
 {
     int n_split = 1;
     int64_t j_chunk = 0;
-    split_shape(a.n, a.n_act, a.n_split, 1, 64, 3, a.part_rows, &n_split, &j_chunk);
+    split_shape(precision, a.n, a.n_act, a.n_split, a.fine, 1, 3, a.part_rows, &n_split, &j_chunk);
     if (used) *used = UsedShape{1, 64, n_split, 3};
     switch (order) {
     case 4: return run_prec<4>(precision, a, in, s, n_split, j_chunk);

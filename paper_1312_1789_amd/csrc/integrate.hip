@@ -59,18 +59,22 @@ k_unpack(int64_t n, const void *__restrict__ rec, double *__restrict__ xp, doubl
     }
 }
 
-// FP64 order-8 records from plain arrays (initialisation passes).
+// FP64 records of order P from plain arrays (initialisation passes): order 4
+// holds position, mass and velocity, order 8 acceleration and jerk as well.
+template <int P>
 __global__ void __launch_bounds__(256)
 k_pack_f64(int64_t n, const double *__restrict__ m, const double *__restrict__ x, const double *__restrict__ v,
-           const double *__restrict__ a, const double *__restrict__ j, RecF64<8> *__restrict__ rec)
+           const double *__restrict__ a, const double *__restrict__ j, RecF64<P> *__restrict__ rec)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    RecF64<8> r{};
+    RecF64<P> r{};
     r.x = x[i]; r.y = x[n + i]; r.z = x[2 * n + i]; r.m = m[i];
     r.vx = v[i]; r.vy = v[n + i]; r.vz = v[2 * n + i];
-    if (a) { r.ax = a[i]; r.ay = a[n + i]; r.az = a[2 * n + i]; }
-    if (j) { r.jx = j[i]; r.jy = j[n + i]; r.jz = j[2 * n + i]; }
+    if constexpr (P == 8) {
+        r.ax = a[i]; r.ay = a[n + i]; r.az = a[2 * n + i];
+        r.jx = j[i]; r.jy = j[n + i]; r.jz = j[2 * n + i];
+    }
     rec[i] = r;
 }
 
@@ -501,8 +505,12 @@ hipError_t launch_unpack(int order, int precision, int64_t n, const void *rec, d
 hipError_t launch_pack_f64(int64_t n, const double *m, const double *x, const double *v, const double *a,
                            const double *j, void *rec, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pack_f64, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, m, x, v, a, j,
-                       static_cast<RecF64<8> *>(rec));
+    if (a && j)
+        hipLaunchKernelGGL(k_pack_f64<8>, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, m, x, v, a, j,
+                           static_cast<RecF64<8> *>(rec));
+    else
+        hipLaunchKernelGGL(k_pack_f64<4>, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, m, x, v, a, j,
+                           static_cast<RecF64<4> *>(rec));
     return hipGetLastError();
 }
 

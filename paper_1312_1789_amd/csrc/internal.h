@@ -96,7 +96,8 @@ struct ForceArgs {
     double *part;           // partial-sum scratch
     int64_t part_rows;      // its capacity in rows of kMaxComp doubles (n_act * n_split <= part_rows)
     int ni, block, n_split; // launch shape (n_split 0 = auto)
-    int jpath;              // 0 auto, 1 scalar loads, 2 LDS tiles
+    bool fine;              // n_split is a tuned count: splits may be as short as the default ones
+    int jpath;              // 0 auto, 1 scalar loads, 2 LDS tiles, 3 wave j-split
 };
 
 // The launch shape a force call ran with (n_split after the scratch bound).
@@ -106,12 +107,20 @@ struct UsedShape {
 
 hipError_t launch_force(int order, int precision, const ForceArgs &a, hipStream_t s, UsedShape *used);
 
-// j-splits and split length (a multiple of the MIXED chunk) of a force launch:
-// n_split_req > 0 is taken as given, bounded by the partial-sum scratch
-// (n_act * n_split <= part_rows) and by the split length (at least one MIXED
-// chunk); 0 chooses from n_act and the shape.
-void split_shape(int64_t n, int64_t n_act, int n_split_req, int ni, int block, int jpath, int64_t part_rows,
-                 int *n_split, int64_t *j_chunk);
+// Snap and crackle alone, FP64 order 8 (a.rec: RecF64<8>, outputs a.out[2] and
+// a.out[3]): the second initialisation pass.  One row per lane, scalar j path.
+// With the first pass at order 4 (it had run the order-8 kernel too) nbody_init
+// at order 6 and n = 40961 takes 6999 us instead of 10880.
+hipError_t launch_force_high(const ForceArgs &a, hipStream_t s, UsedShape *used);
+
+// j-splits and split length of a force launch: n_split_req > 0 is taken as
+// given, bounded by the partial-sum scratch (n_act * n_split <= part_rows) and by
+// the split length (at least one MIXED chunk, less when `fine`); 0 chooses from
+// n_act and the shape.
+void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool fine, int ni, int jpath,
+                 int64_t part_rows, int *n_split, int64_t *j_chunk);
+// The shape of an untuned call.
+void default_shape(int precision, int64_t n, int64_t n_act, int *ni, int *block, int *jpath);
 
 // Fixed-order sum of n_split partial results in a.part into a.out.
 // the split reduction for partial sums in part[component][row][split] (wave j-split kernels)
@@ -152,12 +161,8 @@ int64_t nb_scratch_per_row(int max_nb);
 int nb_split(int64_t n, int64_t n_act, int max_nb, int64_t scratch_bytes, int n_split_req);
 hipError_t launch_force_nb(int precision, const NbArgs &a, int n_split, hipStream_t s, int *used_split);
 
-// j-splits that give about 8 waves per SIMD for n_act rows in workgroups of
-// `block` lanes with ni rows per lane (the default when n_split is 0).
-int auto_split(int64_t n, int64_t n_act, int ni, int block, int64_t part_rows);
-// The default split of a j path (jpath 3, the wave j-split kernel, sizes its
-// own workgroups: 1, 4 or 16 active rows in 64 lanes).
-int auto_split_path(int64_t n, int64_t n_act, int ni, int block, int jpath, int64_t part_rows);
+// The default split count of a j path.
+int auto_split(int precision, int64_t n, int64_t n_act, int ni, int jpath, int64_t part_rows);
 
 // One row of the force-launch table filled by nbody_autotune.
 struct TuneRow {
@@ -167,7 +172,8 @@ struct TuneRow {
 };
 constexpr int kTuneRows = 32;
 
-// Pack FP64 order-8 records {x, m, v, a, j} from state arrays (a, j may be null = 0).
+// Pack FP64 records from state arrays: order 4 {x, m, v} (a and j null), or
+// order 8 {x, m, v, a, j}.
 hipError_t launch_pack_f64(int64_t n, const double *m, const double *x, const double *v, const double *a,
                            const double *j, void *rec, hipStream_t s);
 

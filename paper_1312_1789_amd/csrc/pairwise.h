@@ -80,6 +80,7 @@ template <int P, bool POT> struct PolF64 {
     using ET = double;                   // softening type
     static constexpr int kChunk = 0;
     static constexpr bool kWithPot = POT;
+    static constexpr int kFirst = 0;     // first component wanted
     struct I { double x, y, z, vx, vy, vz, ax, ay, az, jx, jy, jz; };
 
     __device__ static I load(const Rec &r)
@@ -105,6 +106,13 @@ template <int P, bool POT> struct PolF64 {
         if (MASK) mr = valid ? mr : 0.0;
         core_fma<P, POT, double>(dx, dy, dz, wx, wy, wz, ex, ey, ez, fx, fy, fz, mr, rinv * rinv, A);
     }
+};
+
+// FP64 order-8 terms of which only the snap and the crackle are wanted (the
+// second initialisation pass): the sums of the others are never read, so
+// the compiler leaves them out.
+struct PolF64High : PolF64<8, false> {
+    static constexpr int kFirst = 6;
 };
 
 // Double-single inputs shared by the MIXED and DS policies: positions and
@@ -156,6 +164,7 @@ template <int P, bool POT> struct PolMx {
     using I = typename DSIn<P>::I;
     static constexpr int kChunk = kMixedChunk;
     static constexpr bool kWithPot = POT;
+    static constexpr int kFirst = 0;
     __device__ static I load(const Rec &r) { return DSIn<P>::load(r); }
     template <bool MASK>
     __device__ static void pair(const I &i, const Rec &j, float eps2, bool valid, float *A)
@@ -186,6 +195,7 @@ template <int P, bool POT> struct PolDS {
     using I = typename DSIn<P>::I;
     static constexpr int kChunk = 0;
     static constexpr bool kWithPot = POT;
+    static constexpr int kFirst = 0;
     __device__ static I load(const Rec &r) { return DSIn<P>::load(r); }
     template <bool MASK>
     __device__ static void pair(const I &i, const Rec &j, float eps2, bool valid, DS *A)

@@ -294,6 +294,38 @@ def test_last_launch_reports_split_bounds(small_case):
     sim.close()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "ds"])
+@pytest.mark.parametrize("order", [4, 8])
+def test_default_shapes(small_case, order, precision):
+    """Untuned calls at the edges of the default launch rule: the wave j-split
+    kernel's last sizes (32, 64), the first ones past it with the shortest
+    splits, and part-filled row tiles; then, on a larger system, the first
+    call with many waves (scalar path, a ragged last tile of rows)."""
+    model, eps2, n_hard, d = small_case
+    n = model.n
+    sim = _sim(model, order, precision, eps2, n_hard, d)
+    for na in (32, 33, 64, 65, 129, 1000):
+        act = nbody_ics.active_subset(n, na, 1600 + na)
+        out = sim.force_block(torch.as_tensor(act, device=sim.device))
+        say("default shape p%d %s n_act=%d ran as %s" % (order, precision, na, sim.last_launch()))
+        assert (sim.last_launch()[3] == 3) == (na <= (32 if precision == "mixed" else 64))
+        ref = oracle_force(order, eps2, n_hard, model.m, model.x, model.v, d[0], d[1], act=act)
+        _check(out, ref, order, precision, na)
+    sim.close()
+    big = cluster_with_bh(11998, 22)
+    dd = random_derivs(big.n, 1601, 8)
+    sim = _sim(big, order, precision, eps2, n_hard, dd)
+    act = np.arange(big.n, dtype=np.int32)[:-31]
+    out = sim.force_block(torch.as_tensor(act, device=sim.device))
+    say("default shape p%d %s n_act=%d ran as %s" % (order, precision, act.size, sim.last_launch()))
+    assert sim.last_launch()[3] == 1
+    rows = np.concatenate([[0, 1], np.arange(act.size - 70, act.size)]).astype(np.int32)
+    got = {k: t[..., torch.as_tensor(rows, device=sim.device, dtype=torch.int64)] for k, t in out.items()}
+    ref = oracle_force(order, eps2, n_hard, big.m, big.x, big.v, dd[0], dd[1], act=rows)
+    _check(got, ref, order, precision, rows.size)
+    sim.close()
+
+
 def test_force_max_size_sampled():
     """The largest system the C-ABI accepts, n = 2^26 (Plummer, 4th order):
     4096 random active rows through the tiled kernels and 7 through the wave
