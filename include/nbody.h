@@ -127,9 +127,9 @@ nbody_status nbody_workspace_size(const nbody_config *cfg, size_t *bytes /* host
  * nbody_workspace_size() bytes, 256-byte aligned, owned by the caller and kept
  * alive until nbody_destroy.  stream: a hipStream_t (NULL = default stream).
  * *out (host) receives the context.  The context allocates no device memory;
- * it takes 64 bytes of pinned host memory (hipHostMalloc, coherent), into
- * which the block-step scheduler writes its result so that nbody_step and
- * nbody_run wait for it by polling (if that allocation fails they copy the
+ * it takes 512 bytes of pinned host memory (hipHostMalloc, coherent), into
+ * which the block-step scheduler writes its results so that nbody_step and
+ * nbody_run wait for them by polling (if that allocation fails they copy the
  * result and synchronise the stream instead).  nbody_destroy synchronises
  * the stream and frees it. */
 nbody_status nbody_create(const nbody_config *cfg, void *workspace, size_t bytes, void *stream,
@@ -254,10 +254,12 @@ nbody_status nbody_step(nbody_ctx *ctx, nbody_state *state, int64_t *t_tick_out,
 /* Block steps (as nbody_step) until the next block time would exceed
  * t_end_tick, or max_steps steps: *steps_out (host) = steps taken,
  * *t_tick_out (host) = time of the last step (0 if none); both may be NULL.
- * The corrector's counters are read with the next step's scheduler result,
- * so a run costs one host round trip per step.  Returns NBODY_E_NONFINITE
- * (after the step that produced it, or the one after) when a corrected value
- * became NaN or infinite. */
+ * Steps with few active particles are enqueued ahead of the host reading their
+ * schedule (they read it on the device), so a run of them does not wait for
+ * the host; each step's counters are published with the next schedule.
+ * Returns NBODY_E_NONFINITE (after the step that produced it, or the one
+ * after) when a corrected value became NaN or infinite.  The stream is
+ * synchronised on return. */
 nbody_status nbody_run(nbody_ctx *ctx, nbody_state *state, int64_t t_end_tick, int64_t max_steps,
                        int64_t *steps_out, int64_t *t_tick_out);
 

@@ -157,7 +157,7 @@ nbody_status read_scalars(nbody_ctx *ctx, nb::DevScalars *h)
 nbody_status read_published(nbody_ctx *ctx, int64_t seq, nb::DevScalars *h)
 {
     if (!ctx->pub_host) return read_scalars(ctx, h);
-    const nb::HostScalars *p = ctx->pub_host;
+    const nb::HostScalars *p = ctx->pub_host + (seq & (nb::kPubSlots - 1));
     unsigned spins = 0;
     while (__atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) != seq) {
         if ((++spins & 4095u) == 0) {
@@ -173,6 +173,7 @@ nbody_status read_published(nbody_ctx *ctx, int64_t seq, nb::DevScalars *h)
     h->n_act = p->n_act;
     h->underflow = p->underflow;
     h->nonfinite = p->nonfinite;
+    h->seq = seq;
     return NBODY_OK;
 }
 
@@ -213,7 +214,7 @@ Layout make_layout(const nbody_config &c)
     L.force = take(12 * n * sizeof(double));
     L.act = take(n * sizeof(int32_t));
     L.sched = take(nb * (2 * sizeof(int64_t) + sizeof(int32_t)));
-    L.scal = take(sizeof(DevScalars));
+    L.scal = take(sizeof(DevScalars) + kStepCounters * sizeof(unsigned));
     L.init = 0;
     L.irec = take(n * 112);
     L.total = off;
@@ -263,13 +264,14 @@ nbody_status nbody_create(const nbody_config *cfg, void *workspace, size_t bytes
     ctx->last_shape = nb::UsedShape{0, 0, 0, 0};
     memset(&ctx->stats, 0, sizeof(ctx->stats));
     hipError_t e = hipGetDevice(&ctx->device);
-    if (e == hipSuccess) e = hipMemsetAsync(scalars(ctx), 0, sizeof(nb::DevScalars), ctx->stream);
-    // 64 bytes of pinned, coherent host memory for the scheduler result
-    // (without it the steps copy the result and synchronise instead)
+    if (e == hipSuccess)
+        e = hipMemsetAsync(scalars(ctx), 0, sizeof(nb::DevScalars) + nb::kStepCounters * sizeof(unsigned), ctx->stream);
+    // pinned, coherent host memory for the scheduler's results (without it the
+    // steps copy the result and synchronise instead)
     if (e == hipSuccess &&
-        hipHostMalloc(reinterpret_cast<void **>(&ctx->pub_host), sizeof(nb::HostScalars), hipHostMallocCoherent) ==
-            hipSuccess) {
-        ctx->pub_host->seq = 0;
+        hipHostMalloc(reinterpret_cast<void **>(&ctx->pub_host), nb::kPubSlots * sizeof(nb::HostScalars),
+                      hipHostMallocCoherent) == hipSuccess) {
+        for (int k = 0; k < nb::kPubSlots; ++k) ctx->pub_host[k].seq = 0;
         if (hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->pub_dev), ctx->pub_host, 0) != hipSuccess) {
             (void)hipHostFree(ctx->pub_host);
             ctx->pub_host = nullptr;
@@ -653,7 +655,7 @@ nbody_status step_impl(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, bool ch
     if (tm) NB_HIP(hipEventRecord(ctx->ev[0], ctx->stream));
     const int64_t seq = ++ctx->pub_seq;
     NB_HIP(nb::launch_schedule(c.n, st->t_tick, st->level, ctx->ws + ctx->lay.sched, act, scalars(ctx),
-                               ctx->pub_dev, seq, ctx->stream));
+                               ctx->pub_dev ? ctx->pub_dev + (seq & (nb::kPubSlots - 1)) : nullptr, seq, ctx->stream));
     if (tm) NB_HIP(hipEventRecord(ctx->ev[1], ctx->stream));
     nb::DevScalars h;
     nbody_status s = read_published(ctx, seq, &h);
@@ -711,6 +713,127 @@ nbody_status step_impl(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, bool ch
     return NBODY_OK;
 }
 
+// The step kernel's scratch: in the initialisation records, which nothing else
+// uses between calls, and behind the device scalars.
+nb::StepScratch step_scratch(nbody_ctx *ctx)
+{
+    const int64_t n = ctx->cfg.n, nblk = (n + nb::kStepBlock - 1) / nb::kStepBlock;
+    nb::StepScratch w{};
+    w.blk = ws_at<nb::StepBlock>(ctx, ctx->lay.irec);
+    w.boff = reinterpret_cast<int32_t *>(w.blk + nblk);
+    w.cand = w.boff + nblk;   // [n]: 20 nblk + 4 n bytes in all, within 112 n
+    w.arrive = reinterpret_cast<unsigned *>(ctx->ws + ctx->lay.scal + sizeof(nb::DevScalars));
+    w.act = ws_at<int32_t>(ctx, ctx->lay.act);
+    return w;
+}
+
+// Small steps that may be enqueued before the schedule that decides on them has
+// been read: two after a small step (one running, one to follow it at once),
+// one after a large step, whose successor may well be large (the kernels of a
+// step that is not small leave at once, a few microseconds).
+constexpr int64_t kAheadSmall = 2, kAheadLarge = 1;
+
+// Block steps until the next one would exceed t_limit, or max_steps of them,
+// with the step kernel: a schedule to begin with, then per small step the force
+// kernel with the predictor inside and the step kernel, both reading the
+// schedule on the device, and per larger step the predictor, force and split
+// reduction kernels and the step kernel.  The host reads each schedule as it
+// is published.
+nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t max_steps, int64_t *steps_out,
+                       int64_t *t_out, int64_t *n_act_out)
+{
+    const nbody_config &c = ctx->cfg;
+    int32_t *act = ws_at<int32_t>(ctx, ctx->lay.act);
+    double *F = ws_at<double>(ctx, ctx->lay.force);
+    const bool pn = nb::pn_on(c), pn_inside = pn && c.n_hard <= nb::kStepBlock;
+    nb::StepArgs sa{};
+    sa.cfg = c;
+    sa.rule = nb::dt_rule_of(c);
+    sa.st = *st;
+    sa.w = step_scratch(ctx);
+    sa.sc = scalars(ctx);
+    sa.pub = ctx->pub_dev;
+    sa.part = ws_at<double>(ctx, ctx->lay.part);
+    sa.t_limit = t_limit;
+    sa.pn = pn_inside;
+    bool any_small = false;
+    for (int64_t na = 1; na <= nb::kSmallMax && na <= c.n && ctx->fuse && pn == pn_inside; ++na) {
+        const nb::ForceArgs a = force_args(ctx, c.precision, nullptr, na, act, nullptr, nullptr, nullptr, nullptr, nullptr);
+        if (a.jpath != 3) continue;
+        int sp = 0;
+        int64_t jc = 0;
+        nb::split_shape(c.precision, c.n, na, a.n_split, a.fine, 1, 3, a.part_rows, &sp, &jc);
+        sa.tab.n_split[na - 1] = sp;
+        sa.tab.j_chunk[na - 1] = int32_t(jc);
+        any_small = true;
+    }
+    nb::ForceArgs fa = force_args(ctx, c.precision, nullptr, 1, act, nullptr, nullptr, nullptr, nullptr, nullptr);
+    nb::PredIn in{};
+    in.m = st->m;
+    in.x = st->x;
+    in.v = st->v;
+    for (int k = 0; k < 6; ++k) in.d[k] = k <= c.order - 3 ? st->d[k] : nullptr;
+    in.t_tick = st->t_tick;
+
+    int64_t seq = ++ctx->pub_seq, steps = 0, ahead = 0, allowed = kAheadLarge;
+    nbody_status s = NBODY_OK;
+    sa.mode = nb::kStepSchedule;
+    sa.seq = seq;
+    NB_HIP(nb::launch_step(sa, ctx->stream));
+    for (;;) {
+        while (any_small && ahead < allowed && steps + ahead < max_steps) {
+            NB_HIP(nb::launch_force_small_dev(c.order, c.precision, fa, in, sa.sc, sa.tab, t_limit, ctx->stream));
+            sa.mode = nb::kStepSmall;
+            NB_HIP(nb::launch_step(sa, ctx->stream));
+            ++ahead;
+        }
+        nb::DevScalars h;
+        s = read_published(ctx, seq, &h);
+        if (s == NBODY_OK && h.seq != seq) s = fail(NBODY_E_HIP, "the schedule of a block step was not published");
+        if (s == NBODY_OK) s = take_counters(ctx, h, *t_out);
+        if (s != NBODY_OK || steps == max_steps) break;
+        const int64_t t_next = h.t_next, n_act = h.n_act;
+        if (n_act <= 0 || n_act > c.n) {
+            s = fail(NBODY_E_STATE, "scheduler found %lld active particles", (long long)n_act);
+            break;
+        }
+        if (t_next > t_limit) break;
+        if (n_act <= nb::kSmallMax && sa.tab.n_split[n_act - 1] > 0) {
+            // the first of the steps enqueued ahead is this one
+            --ahead;
+            allowed = kAheadSmall;
+            ctx->predicted = false;   // the records are stale from here on
+            ctx->last_shape = nb::UsedShape{1, 64, sa.tab.n_split[n_act - 1], 3};
+            ctx->stats.interactions += double(n_act) * double(c.n);
+        } else {
+            // those enqueued ahead have left without effect when this step runs
+            ahead = 0;
+            allowed = kAheadLarge;
+            if (n_act > nb::kStepGather) NB_HIP(nb::launch_step_gather(sa.w, c.n, sa.sc, ctx->stream));
+            double *f[4] = {F, F + 3 * n_act, c.order >= 6 ? F + 6 * n_act : nullptr, c.order >= 8 ? F + 9 * n_act : nullptr};
+            s = run_predict_force(ctx, st, t_next, n_act, act, f[0], f[1], f[2], f[3], nullptr, nullptr);
+            if (s != NBODY_OK) break;
+            if (pn && !pn_inside)
+                NB_HIP(nb::launch_pn(c, *st, st->t_tick, t_next, act, n_act, f[0], f[1], f[2], f[3], ctx->stream));
+            nb::StepArgs big = sa;
+            big.mode = nb::kStepForces;
+            for (int k = 0; k < 4; ++k) big.f[k] = f[k];
+            NB_HIP(nb::launch_step(big, ctx->stream));
+        }
+        seq = ++ctx->pub_seq;
+        ++steps;
+        ctx->stats.steps += 1;
+        ctx->stats.sum_n_act += n_act;
+        *t_out = t_next;
+        *n_act_out = n_act;
+    }
+    *steps_out = steps;
+    if (s == NBODY_OK) NB_HIP(hipStreamSynchronize(ctx->stream));
+    return s;
+}
+
+bool steps_by_kernel(const nbody_ctx *ctx) { return ctx->pub_host && !ctx->timing && ctx->cfg.n <= nb::kStepMaxN; }
+
 }  // namespace
 
 extern "C" {
@@ -720,9 +843,10 @@ nbody_status nbody_step(nbody_ctx *ctx, nbody_state *st, int64_t *t_tick_out, in
     if (!ctx) return fail(NBODY_E_INVALID, "ctx is NULL");
     nbody_status s = check_state(ctx, st);
     if (s != NBODY_OK) return s;
-    int64_t t = 0, na = 0, prev = 0;
+    int64_t t = 0, na = 0, prev = 0, one = 0;
     bool stepped = false;
-    s = step_impl(ctx, st, INT64_MAX, true, &t, &na, &stepped, &prev);
+    if (steps_by_kernel(ctx)) s = run_steps(ctx, st, INT64_MAX, 1, &one, &t, &na);
+    else s = step_impl(ctx, st, INT64_MAX, true, &t, &na, &stepped, &prev);
     if (s != NBODY_OK) return s;
     if (t_tick_out) *t_tick_out = t;
     if (n_act_out) *n_act_out = na;
@@ -738,7 +862,11 @@ nbody_status nbody_run(nbody_ctx *ctx, nbody_state *st, int64_t t_end_tick, int6
     if (t_end_tick < 0 || max_steps < 0) return fail(NBODY_E_INVALID, "t_end_tick and max_steps must be >= 0");
     int64_t steps = 0, t = 0, na = 0, prev = 0;
     bool stepped = true;
-    while (steps < max_steps) {
+    if (steps_by_kernel(ctx) && max_steps > 0) {
+        s = run_steps(ctx, st, t_end_tick, max_steps, &steps, &prev, &na);
+        stepped = false;   // its counters are read
+    }
+    else while (steps < max_steps) {
         s = step_impl(ctx, st, t_end_tick, false, &t, &na, &stepped, &prev);
         if (s != NBODY_OK || !stepped) break;
         ++steps;

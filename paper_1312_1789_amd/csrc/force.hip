@@ -291,13 +291,70 @@ k_reduce(const double *__restrict__ part, int64_t n_act, int n_split, double *__
     if (o) o[(c % 3) * n_act + q] = s;
 }
 
+// Sum of kernel C's partial results (split-fastest), in the order of the kernel
+// that predicts inside: groups of gs consecutive splits first, each in order,
+// then lane l of an output's L lanes adds groups l, l + L, ... and the lanes
+// are folded as in k_reduce.
+template <int P, int L>
+__global__ void __launch_bounds__(256)
+k_reduce_groups(const double *__restrict__ part, int64_t n_act, int n_split, int gs, int ng,
+                double *__restrict__ o_acc, double *__restrict__ o_jrk, double *__restrict__ o_snp,
+                double *__restrict__ o_crk, double *__restrict__ o_pot)
+{
+    constexpr int NV = 3 * (P / 2);
+    const int64_t g = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / L;   // output index
+    const int l = int(threadIdx.x) % L;
+    const bool valid = g < n_act * (o_pot ? NV + 1 : NV);
+    const int64_t gg = valid ? g : 0;
+    const int c = int(gg / n_act);
+    const int64_t q = gg - int64_t(c) * n_act;
+    const double *src = part + (int64_t(c) * n_act + q) * n_split;
+    double s = 0.0;
+    if (valid)
+        for (int k = l; k < ng; k += L) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = (u < gs && k * gs + u < n_split) ? src[k * gs + u] : 0.0;
+            double t = 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t += v[u];   // the zeros past a group's end change nothing
+            s += t;
+        }
+#pragma unroll
+    for (int m = L / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
+    if (!valid || l != 0) return;
+    if (c == NV) {
+        o_pot[q] = s;
+        return;
+    }
+    double *outs[4] = {o_acc, o_jrk, o_snp, o_crk};
+    double *o = outs[c / 3];
+    if (o) o[(c % 3) * n_act + q] = s;
+}
+
+template <int P>
+hipError_t launch_reduce_groups(const ForceArgs &a, int n_split, hipStream_t s)
+{
+    const int gs = small_group(a.n_act), ng = (n_split + gs - 1) / gs;
+    const int64_t outs = a.n_act * (3 * (P / 2) + (a.out[4] ? 1 : 0));
+    const int L = reduce_lanes(ng);
+    const unsigned blocks = unsigned((outs * L + 255) / 256);
+#define NB_RED(LL) hipLaunchKernelGGL((k_reduce_groups<P, LL>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
+                                      gs, ng, a.out[0], a.out[1], a.out[2], a.out[3], a.out[4])
+    if (L == 1) NB_RED(1);
+    else if (L == 4) NB_RED(4);
+    else if (L == 16) NB_RED(16);
+    else NB_RED(64);
+#undef NB_RED
+    return hipGetLastError();
+}
+
 template <int P, bool SF, int C0 = 0>
 hipError_t launch_reduce(const ForceArgs &a, int n_split, hipStream_t s)
 {
     static_assert(C0 % 3 == 0, "whole vectors");
     const int64_t outs = a.n_act * (3 * (P / 2) - C0 + (a.out[4] ? 1 : 0));
-    // lanes per output: enough that each lane adds at most about 8 splits
-    const int L = n_split <= 8 ? 1 : n_split <= 32 ? 4 : n_split <= 128 ? 16 : 64;
+    const int L = reduce_lanes(n_split);
     const unsigned blocks = unsigned((outs * L + 255) / 256);
 #define NB_RED(LL) hipLaunchKernelGGL((k_reduce<P, LL, SF, C0>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
                                       a.out[0], a.out[1], a.out[2], a.out[3], a.out[4])
@@ -342,7 +399,8 @@ hipError_t run(const ForceArgs &a, hipStream_t s, const Shape &sh)
 #undef NB_FORCE_ARGS
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || sh.n_split == 1) return e;
-    if (sh.jpath == 3 || sh.n_split > kSplitFastestAbove) return launch_reduce<P, true>(a, sh.n_split, s);
+    if (sh.jpath == 3) return launch_reduce_groups<P>(a, sh.n_split, s);
+    if (sh.n_split > kSplitFastestAbove) return launch_reduce<P, true>(a, sh.n_split, s);
     return launch_reduce<P, false>(a, sh.n_split, s);
 }
 

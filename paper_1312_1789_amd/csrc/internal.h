@@ -68,7 +68,7 @@ struct Layout {
     size_t force;      // step force outputs, kMaxComp-1 rows of n doubles ([12][n])
     size_t act;        // active indices, n int32
     size_t sched;      // scheduler per-block scratch (min ticks, counts, offsets)
-    size_t scal;       // device scalars: t_next, n_act, counters
+    size_t scal;       // device scalars: t_next, n_act, counters; the step kernel's arrival counters
     size_t init;       // init scratch: 4 x [3][n] doubles (a, j, s, c of the two passes)
     size_t irec;       // init records (FP64 order-8 layout), n * 112
     size_t total;
@@ -81,8 +81,28 @@ struct DevScalars {
     int64_t n_act;
     unsigned long long underflow;
     unsigned long long nonfinite;
-    int64_t pad[4];
+    int64_t seq;                    // of the last schedule published by the step kernel
+    int64_t halt;                   // a corrected value was not finite: no further small step
+    unsigned long long nonfinite0;  // nonfinite when the run began
+    int64_t pad;
 };
+
+// Active sets that the small-step kernels take, and the split of each size
+// (n_split 0: not taken).
+constexpr int kSmallMax = 64;
+struct SmallTable {
+    int32_t n_split[kSmallMax];
+    int32_t j_chunk[kSmallMax];
+};
+
+// Whether the step the scheduler found is one for the small-step kernels.
+__device__ __forceinline__ bool small_step(const DevScalars &d, const SmallTable &t, int64_t t_limit)
+{
+    return d.n_act >= 1 && d.n_act <= kSmallMax && d.t_next <= t_limit && !d.halt && t.n_split[d.n_act - 1] > 0;
+}
+
+// Lanes that share the sum of one output over n partials: each adds at most about 8.
+__host__ __device__ constexpr int reduce_lanes(int n) { return n <= 8 ? 1 : n <= 32 ? 4 : n <= 128 ? 16 : 64; }
 
 // Force launch request.
 struct ForceArgs {
@@ -122,8 +142,8 @@ void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool 
 // The shape of an untuned call.
 void default_shape(int precision, int64_t n, int64_t n_act, int *ni, int *block, int *jpath);
 
-// Fixed-order sum of n_split partial results in a.part into a.out.
-// the split reduction for partial sums in part[component][row][split] (wave j-split kernels)
+// Fixed-order sum of n_split partial results in part[component][row][split]
+// into a.out.
 hipError_t launch_split_reduce_sf(int order, const ForceArgs &a, int n_split, hipStream_t s);
 
 // The stored state the predictor reads, and the time it predicts to.
@@ -134,11 +154,64 @@ struct PredIn {
     int64_t t;
 };
 
+struct OutPtrs {
+    double *p[5];
+};
+
 // The wave j-split force (ForceArgs.jpath 3) with the predictor in its j
 // loads: a.rec is not read; the j-particles and the active i-particles are
 // predicted from `in` to in.t, exactly as the predictor kernel writes them.
 hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const PredIn &in, hipStream_t s,
                              UsedShape *used);
+// The same for the step that the scheduler has written to dev (active set
+// a.act, split from tab); leaves the partial sums of each group of
+// small_group(n_act) splits in a.part, and does nothing when the step is not
+// small or past t_limit.
+hipError_t launch_force_small_dev(int order, int precision, const ForceArgs &a, const PredIn &in,
+                                  const DevScalars *dev, const SmallTable &tab, int64_t t_limit, hipStream_t s);
+// Consecutive splits whose sums that kernel adds in one workgroup.
+int small_group(int64_t n_act);
+
+// The end of a block step and the schedule of the next one (step.hip).
+constexpr int kStepBlock = 256;                    // particles (and threads) per workgroup
+constexpr int64_t kStepMaxN = int64_t(1) << 20;    // systems it takes
+constexpr int kStepGather = 4096;                  // active sets it lists itself
+constexpr int kStepSub = 64;                       // workgroups per arrival counter
+constexpr int kStepCounters = int(kStepMaxN / kStepBlock) / kStepSub + 1;
+struct StepBlock {
+    int64_t t_next;     // next time of a block of kStepBlock particles
+    int64_t count;      // its particles at it
+};
+struct StepScratch {
+    StepBlock *blk;     // [nb]
+    int32_t *boff;      // [nb] active particles before the block
+    int32_t *cand;      // [nb][kStepBlock] the block's particles at its next time
+    unsigned *arrive;   // [kStepCounters], zero between launches
+    int32_t *act;       // [n] the active list
+};
+enum StepMode {
+    kStepSchedule,      // only the schedule (starts a run: seq is the first sequence number)
+    kStepSmall,         // a small step from the partial sums of launch_force_small_dev
+    kStepForces         // any step from its forces f[k] ([3][n_act])
+};
+struct StepArgs {
+    nbody_config cfg;
+    int rule;                    // dt_rule_of(cfg)
+    nbody_state st;
+    StepScratch w;
+    DevScalars *sc;
+    struct HostScalars *pub;     // slots of the published schedules
+    StepMode mode;
+    int64_t seq;
+    SmallTable tab;              // kStepSmall
+    const double *part;          // kStepSmall
+    double *f[4];                // kStepForces
+    int64_t t_limit;             // kStepSmall
+    bool pn;                     // add the post-Newtonian terms (n_hard <= kStepBlock)
+};
+hipError_t launch_step(const StepArgs &a, hipStream_t s);
+// The active list of n_act > kStepGather particles.
+hipError_t launch_step_gather(const StepScratch &w, int64_t n, const DevScalars *sc, hipStream_t s);
 
 // Force split by neighbour spheres (order-4 terms) with the neighbour lists.
 struct NbArgs {
@@ -202,6 +275,9 @@ hipError_t launch_unpack(int order, int precision, int64_t n, const void *rec, d
 // The scheduler's result for the host: written by the scheduler into
 // pinned, coherent host memory, the sequence number last, so that the host
 // can wait for it by polling instead of a copy and a stream synchronisation.
+// One slot per sequence number modulo kPubSlots (a run has a few steps in
+// flight).
+constexpr int kPubSlots = 8;
 struct HostScalars {
     int64_t t_next;
     int64_t n_act;
