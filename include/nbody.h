@@ -393,14 +393,14 @@ nbody_status nbody_batch_energy(nbody_batch *b, const nbody_state *state, double
 nbody_status nbody_batch_get_stats(nbody_batch *b, nbody_stats *out);
 
 /* Persistent force launch: force_grid workgroups (0 = as many as fit on the
- * device at once), items_per_wg work items aimed for per workgroup (1..32,
- * 0 = 8: each step's padded work is cut into about force_grid * items_per_wg
- * items of equal cost, at most 2^22 / i_tile, by splitting each cluster's
- * j-range into pieces of at least 128) and i_tile active rows per work item
- * (64, 128 or 256, 0 = 64).  Applies to later steps and captures (a captured graph keeps
- * the shape it was captured with).  Results depend on the shape only through
- * the FP64 summation order of the split partials (and, in MIXED mode, where
- * the FP32 chunks start). */
+ * device at once), work items per workgroup (1..32, 0 = 8: the most a step's
+ * padded work is cut into, at most 2^22 / i_tile items in all, of equal cost, by
+ * splitting each cluster's j-range into pieces of at least 128 (FP64 and DS:
+ * 64); a step with little work is cut into about one per workgroup) and i_tile
+ * active rows per row tile (64, 128 or 256, 0 = 64).  Applies to later steps
+ * and captures (a captured graph keeps the shape it was captured with).  Results
+ * depend on the shape only through the FP64 summation order of the split
+ * partials (and, in MIXED mode, where the FP32 chunks start). */
 nbody_status nbody_batch_set_launch(nbody_batch *b, int32_t force_grid, int32_t items_per_wg, int32_t i_tile);
 
 /* The shape in use (HOST out[3]): force_grid, items_per_wg, i_tile. */

@@ -78,7 +78,9 @@ struct BatchLaunch {
     int force_grid;             // workgroups of the persistent force kernel
     int per_wg;                 // work items aimed for per persistent workgroup
     int k_items;                // items aimed for in one step: min(force_grid * per_wg, kBatchMaxRows / itile)
-    int itile;                  // active rows per work item: 64 or 256
+    int itile;                  // active rows per work item: 64, 128 or 256
+    int halves;                 // items per 64-row tile and split: 2 = half its rows each, one row per lane
+    int grain;                  // shortest j-split: MIXED an FP32 chunk, FP64 and DS two tiles
 };
 
 hipError_t batch_cid(const BatchLaunch &L, hipStream_t s);
@@ -93,6 +95,6 @@ hipError_t batch_reduce(const BatchLaunch &L, int order, double *o0, double *o1,
 hipError_t batch_correct(const BatchLaunch &L, const nbody_config &c, const nbody_state &st, hipStream_t s);
 // Workgroups of the persistent force kernel (i-tile itile) that fit on the
 // device at once.
-int batch_force_resident(int order, int precision, int itile, int device);
+int batch_force_resident(int order, int precision, int itile, int halves, int device);
 
 }  // namespace nb

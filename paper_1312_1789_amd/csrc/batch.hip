@@ -30,6 +30,7 @@ namespace {
 
 constexpr int kBBlock = kBatchSchedBlock;
 constexpr int kBTile = 32;   // records per LDS tile of the one-wave force workgroups
+constexpr int64_t kBItemMin = 32768;   // pair evaluations of a work item worth claiming
 constexpr int kBThreads = 256;  // threads per scheduling block (4 particles each)
 
 __device__ __forceinline__ int64_t b_next(const int64_t *t_tick, const int32_t *level, int64_t i)
@@ -149,6 +150,17 @@ __device__ int64_t block_sum(int64_t v, int64_t *sh)
     return r;
 }
 
+// Workgroups of range x's XCD: the items of the range that are dealt to them.
+__host__ __device__ __forceinline__ int b_dealt(int grid, int x) { return (grid - x + kXcds - 1) / kXcds; }
+
+// Start of range x's counter for `total` items.
+__device__ __forceinline__ uint32_t b_queue_start(int64_t total, int grid, int x)
+{
+    const int64_t len = total * (x + 1) / kXcds - total * x / kXcds;
+    const int dealt = b_dealt(grid, x);
+    return uint32_t(len < dealt ? len : dealt);
+}
+
 // The plan of one batched step (one block).  For every cluster: active
 // offset, j-splits and work items.  Items are sized by cost: the step's
 // padded work W = sum_c tiles_c * itile * N_c is cut into about k_items items
@@ -160,7 +172,8 @@ __device__ int64_t block_sum(int64_t v, int64_t *sh)
 // Also resets the work queues and adds the step's interactions to the counters.
 __global__ void __launch_bounds__(kBThreads)
 k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ ord, const int64_t *__restrict__ tnext,
-         BatchPlan *__restrict__ pl, int ncomp, int k_items, int itile, BatchCounters *__restrict__ ctr)
+         BatchPlan *__restrict__ pl, int ncomp, int k_items, int itile, int halves, int grain, int grid,
+         BatchCounters *__restrict__ ctr)
 {
     __shared__ int64_t sh[kBThreads];
     int64_t w = 0, inter = 0, live = 0;
@@ -175,7 +188,16 @@ k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ or
     const int64_t W = block_sum(w, sh);
     inter = block_sum(inter, sh);
     live = block_sum(live, sh);
-    const int64_t w_item = W / k_items + 1;
+    // Items of at least kBItemMin pairs (an item costs a few microseconds of
+    // loads before its first pair, and the claim of one from a counter that an
+    // eighth of the chip shares some 50 ns), up to the number asked for; a step
+    // of less than four such items per workgroup is cut into as many as there
+    // are workgroups (an eighth less, as the cuts round up), all dealt.
+    const int64_t tiles_per = itile == 64 ? halves : 1;   // items of a row tile and split
+    int64_t k = W / kBItemMin;
+    if (k < 4 * int64_t(grid)) k = int64_t(grid) * 7 / 8;
+    if (k > k_items) k = k_items;
+    const int64_t w_item = W * tiles_per / k + 1;
     block_scan(pl->aoff, nc, sh);
     // splits, items (in rank order), partial rows (in cluster order)
     for (int r = threadIdx.x; r < nc; r += kBThreads) {
@@ -183,14 +205,14 @@ k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ or
         const int64_t na = pl->nact[c], nn = off[c + 1] - off[c];
         const int64_t tiles = (na + itile - 1) / itile;
         int64_t sp = (int64_t(itile) * nn + w_item - 1) / w_item;
-        const int64_t sp_max = nn / kMixedChunk > 1 ? nn / kMixedChunk : 1;   // pieces of at least one FP32 chunk
+        const int64_t sp_max = (nn + grain - 1) / grain;   // pieces of at least a grain (MIXED: an FP32 chunk)
         sp = sp < 1 ? 1 : (sp > sp_max ? sp_max : sp);
         int64_t jc = (nn + sp - 1) / sp;
-        jc = (jc + kMixedChunk - 1) / kMixedChunk * kMixedChunk;
+        jc = (jc + grain - 1) / grain * grain;
         sp = (nn + jc - 1) / jc;
         pl->split[c] = int32_t(sp);
         pl->jchunk[c] = jc;
-        pl->ioff[r] = tiles * sp;
+        pl->ioff[r] = tiles * sp * tiles_per;
         pl->poff[c] = sp * na * ncomp;
     }
     __syncthreads();
@@ -211,7 +233,7 @@ k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ or
         d.c = c;
         pl->rank[r] = d;
     }
-    if (threadIdx.x < kXcds) pl->queue[threadIdx.x * 16] = 0u;
+    if (threadIdx.x < kXcds) pl->queue[threadIdx.x * 16] = b_queue_start(pl->ioff[nc], grid, int(threadIdx.x));
     if (threadIdx.x == 0) {
         pl->n_live = live;
         ctr->interactions += inter;
@@ -306,10 +328,13 @@ k_b_predict(int64_t n, const int32_t *__restrict__ cid, const int64_t *__restric
 // active rows takes the largest JS (at most 64 and the tile length) with
 // 2R >= rows, so a cluster's last, partly filled tile leaves at most half of
 // its lanes idle (b_item_rows).
-template <class Pol, int P, int JS, int TILE>
+//
+// NR = 1: the item is one of the two halves of the tile's rows (rows r + half R),
+// one row per lane; each row's sums are the same bits.
+template <class Pol, int P, int JS, int TILE, int NR>
 __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec, const int32_t *__restrict__ al,
                                        int64_t na, int64_t row0, int64_t base, int64_t nn, int64_t nh, int64_t j0,
-                                       int64_t j1, typename Pol::ET e2, typename Pol::Rec (*tile)[TILE],
+                                       int64_t j1, typename Pol::ET e2, int half, typename Pol::Rec (*tile)[TILE],
                                        double *__restrict__ dst)
 {
     using Rec = typename Pol::Rec;
@@ -324,12 +349,14 @@ __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec
     typedef uint4 __attribute__((may_alias)) piece_t;
     const int lane = int(threadIdx.x);
     const int r = lane / JS, sl = lane % JS;
-    typename Pol::I ip[2];
-    int64_t iidx[2];
-    double acc[2][NV];
-    Part pt[2][13];
+    row0 += half * R;
+    if (row0 >= na) return;   // no rows in this half (uniform over the workgroup)
+    typename Pol::I ip[NR];
+    int64_t iidx[NR];
+    double acc[NR][NV];
+    Part pt[NR][13];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < NR; ++k) {
         const int64_t q0 = row0 + r + k * R;
         const int64_t q = q0 < na ? q0 : na - 1;   // padding rows recompute the last row; never stored
         const int64_t ia = al[q];
@@ -344,7 +371,7 @@ __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec
     for (int64_t j = j0 + sl; j < jh1; j += JS) {
         const Rec rj = rec[j];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < NR; ++k) {
             Part ph[13];
 #pragma unroll
             for (int c = 0; c < 13; ++c) zero_part(ph[c]);
@@ -371,7 +398,7 @@ __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec
     };
     if (js0 < j1) fetch(js0);
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < NR; ++k)
 #pragma unroll
         for (int c = 0; c < 13; ++c) zero_part(pt[k][c]);
     // every tile is taken whole (IT records per lane): the slots of the last
@@ -394,11 +421,11 @@ __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec
         for (int u = 0; u < IT; ++u) {
             const Rec rj = tr[u * JS];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) Pol::template pair<false>(ip[k], rj, e2, true, pt[k]);
+            for (int k = 0; k < NR; ++k) Pol::template pair<false>(ip[k], rj, e2, true, pt[k]);
         }
         if (++since == FL) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int k = 0; k < NR; ++k)
 #pragma unroll
                 for (int c = 0; c < NV; ++c) {
                     acc[k][c] += to_double(pt[k][c]);
@@ -409,19 +436,19 @@ __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec
         buf ^= 1;
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < NR; ++k)
 #pragma unroll
         for (int c = 0; c < NV; ++c) acc[k][c] += to_double(pt[k][c]);
     // fold the group's JS lanes (consecutive lanes: xor offsets below JS stay in the group)
 #pragma unroll
     for (int m = JS / 2; m > 0; m >>= 1)
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < NR; ++k)
 #pragma unroll
             for (int c = 0; c < NV; ++c) acc[k][c] += __shfl_xor(acc[k][c], m, 64);
     if (sl == 0) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < NR; ++k) {
             const int64_t q0 = row0 + r + k * R;
             if (q0 < na)
 #pragma unroll
@@ -432,47 +459,57 @@ __device__ __forceinline__ void b_item(const typename Pol::Rec *__restrict__ rec
 
 // b_item with the largest lane group JS (at most 64 and the tile length)
 // whose 2 * 64 / JS rows hold the tile's `rows` active rows.
-template <class Pol, int P, int TILE, int ROWS>
+template <class Pol, int P, int TILE, int ROWS, int NR>
 __device__ __forceinline__ void b_item_rows(int rows, const typename Pol::Rec *__restrict__ rec,
                                             const int32_t *__restrict__ al, int64_t na, int64_t row0, int64_t base,
                                             int64_t nn, int64_t nh, int64_t j0, int64_t j1, typename Pol::ET e2,
-                                            typename Pol::Rec (*tile)[TILE], double *__restrict__ dst)
+                                            int half, typename Pol::Rec (*tile)[TILE], double *__restrict__ dst)
 {
     constexpr int J2 = 2 < TILE ? 2 : TILE, J4 = 4 < TILE ? 4 : TILE, J8 = 8 < TILE ? 8 : TILE;
     constexpr int J16 = 16 < TILE ? 16 : TILE, J32 = 32 < TILE ? 32 : TILE, J64 = 64 < TILE ? 64 : TILE;
-    if (ROWS == 128 && rows > 64) b_item<Pol, P, 1, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
-    else if (rows > 32) b_item<Pol, P, J2, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
-    else if (rows > 16) b_item<Pol, P, J4, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
-    else if (rows > 8) b_item<Pol, P, J8, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
-    else if (rows > 4) b_item<Pol, P, J16, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
-    else if (rows > 2) b_item<Pol, P, J32, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
-    else b_item<Pol, P, J64, TILE>(rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
+    if (ROWS == 128 && rows > 64) b_item<Pol, P, 1, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
+    else if (rows > 32) b_item<Pol, P, J2, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
+    else if (rows > 16) b_item<Pol, P, J4, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
+    else if (rows > 8) b_item<Pol, P, J8, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
+    else if (rows > 4) b_item<Pol, P, J16, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
+    else if (rows > 2) b_item<Pol, P, J32, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
+    else b_item<Pol, P, J64, TILE, NR>(rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
 }
 
+// Measured (32 clusters of 2^10 to 2^14, MIXED order 6, to t = 1/256, 208 steps):
+// 20578 us with two rows per lane, pieces of at least 256 particles (the cut
+// rounded up) and every item claimed, 17464 with one row per lane, pieces of
+// 128 and first items dealt; the median step's force kernel 42 -> 16 us.
+// 128 clusters of 2^10 to 2^16 (two rows per lane, kHalfTilesBelow) 49.5 -> 49.5
+// ms.
+//
 // Persistent force kernel.  The step's items (in cluster rank order: item
 // = cluster ord[rank], i-tile, j-split) form 8 contiguous ranges, one per
 // XCD, each with its own queue counter.  The dispatcher places workgroup g on
 // XCD g mod 8: a workgroup takes items from its own XCD's range (a few
 // clusters, whose j records that XCD's L2 then holds), then from the other
-// ranges in turn, and leaves when all eight are empty.  Each counter is
-// shared by an eighth of the workgroups only.  Every wave reaches the exit:
-// the counters only grow.  Tiles of ROWS = 64 or 128 rows run as one wave
+// ranges in turn, and leaves when all eight are empty.  Its first item is
+// dealt by its number, without the counter, which an eighth of the workgroups
+// would ask at once (some 0.1 us each; a step of 3600 items took 80 us that
+// way).  Every wave reaches the exit: the counters only grow.  Tiles of ROWS = 64 or 128 rows run as one wave
 // with two rows per lane (b_item); 256-row tiles as four waves with one row
 // per lane.
 
 // Waves per SIMD the register allocation of k_b_force aims for: the
 // one-wave workgroups of the FP32 pair arithmetic (MIXED) at orders 4 and 6
 // fit 3 without spills (otherwise the compiler's own choice).
-template <class Pol, int P, int BLOCK>
-constexpr int b_waves() { return (BLOCK == 64 && sizeof(typename Pol::Part) == 4 && P <= 6) ? 3 : 1; }
+template <class Pol, int P, int BLOCK, int NR>
+constexpr int b_waves() { return BLOCK == 64 && NR == 2 && sizeof(typename Pol::Part) == 4 && P <= 6 ? 3 : 1; }
 
 // One work item: the i-tile and j-split `local` of the cluster described by d.
-template <class Pol, int P, int BLOCK, int TILE, int ROWS>
+template <class Pol, int P, int BLOCK, int TILE, int ROWS, int NR>
 __device__ __forceinline__ void b_run(const BatchRank &d, int64_t local, const typename Pol::Rec *__restrict__ rec,
                                       const int32_t *__restrict__ act, typename Pol::ET e2, int64_t n_hard, int ncomp,
                                       double *__restrict__ part, typename Pol::Rec (*tile)[TILE])
 {
-    const uint32_t lq = uint32_t(local), sp = uint32_t(d.sp);
+    constexpr bool kHalves = ROWS == 64 && NR == 1;   // two items per row tile and split
+    const int half = kHalves ? int(local & 1) : 0;
+    const uint32_t lq = uint32_t(kHalves ? local >> 1 : local), sp = uint32_t(d.sp);
     const int64_t tile_i = lq / sp, split = lq % sp;
     const int64_t na = d.na, base = d.base, nn = d.nn, jc = d.jc;
     const int64_t j0 = base + split * jc;
@@ -483,7 +520,7 @@ __device__ __forceinline__ void b_run(const BatchRank &d, int64_t local, const t
     if constexpr (BLOCK == 64) {
         const int64_t row0 = tile_i * ROWS;
         const int64_t rows = na - row0 < ROWS ? na - row0 : ROWS;
-        b_item_rows<Pol, P, TILE, ROWS>(int(rows), rec, al, na, row0, base, nn, nh, j0, j1, e2, tile, dst);
+        b_item_rows<Pol, P, TILE, ROWS, NR>(int(rows), rec, al, na, row0, base, nn, nh, j0, j1, e2, half, tile, dst);
     } else {
         // this lane's active row
         const int64_t q0 = tile_i * BLOCK + threadIdx.x;
@@ -508,8 +545,8 @@ __device__ __forceinline__ void b_run(const BatchRank &d, int64_t local, const t
 
 __device__ __forceinline__ int64_t wave_uniform(uint32_t v) { return int64_t(uint32_t(__builtin_amdgcn_readfirstlane(v))); }
 
-template <class Pol, int P, int BLOCK, int TILE, int ROWS>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(b_waves<Pol, P, BLOCK>())))
+template <class Pol, int P, int BLOCK, int TILE, int ROWS, int NR>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(b_waves<Pol, P, BLOCK, NR>())))
 k_b_force(const typename Pol::Rec *__restrict__ rec, int nc, const int32_t *__restrict__ act,
           BatchPlan *__restrict__ pl, double eps2, int64_t n_hard, int ncomp, double *__restrict__ part)
 {
@@ -520,57 +557,66 @@ k_b_force(const typename Pol::Rec *__restrict__ rec, int nc, const int32_t *__re
     const ET e2 = ET(eps2);
     const BatchRank *__restrict__ rk = pl->rank;
     const int64_t total = rk[nc - 1].i1;
-    // a step with fewer items than workgroups: the first `total` workgroups
-    // (spread over the XCDs) take them all, the others leave at once
-    if (int64_t(blockIdx.x) >= total) return;
     const int x0 = int(blockIdx.x) % kXcds;
     const int64_t ahead = 2 * ((int64_t(gridDim.x) + kXcds - 1) / kXcds);   // two items per workgroup of an XCD
     for (int v = 0; v < kXcds; ++v) {
         const int xr = (x0 + v) % kXcds;
         const int64_t r0 = total * xr / kXcds, len = total * (xr + 1) / kXcds - r0;
         uint32_t *q = &pl->queue[xr * 16];
-        // the first item of this range; an exhausted range is seen with a
-        // load, without adding to its counter
-        __syncthreads();   // the previous item's tiles and s_take are no longer read
-        if (threadIdx.x == 0) {
-            const uint32_t seen = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_take = seen >= uint32_t(len) ? uint32_t(len) : atomicAdd(q, 1u);
+        int64_t take;
+        if (v == 0) {
+            // the first item is dealt: the range's counter starts past the
+            // items of its XCD's workgroups (b_dealt)
+            take = int64_t(blockIdx.x) / kXcds;
+        } else {
+            // an exhausted range is seen with a load, without adding to its counter
+            __syncthreads();   // the previous item's tiles and s_take are no longer read
+            if (threadIdx.x == 0) {
+                const uint32_t seen = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_take = seen >= uint32_t(len) ? uint32_t(len) : atomicAdd(q, 1u);
+            }
+            __syncthreads();
+            take = wave_uniform(s_take);   // scalar: the cluster, ranges and loop bounds stay in SGPRs
         }
-        __syncthreads();
-        int64_t take = wave_uniform(s_take);   // scalar: the cluster, ranges and loop bounds stay in SGPRs
-        if (take >= len) continue;
-        // rank of the item's cluster: rk[lo].i0 <= item < rk[lo].i1; the
-        // items a workgroup takes from one range only increase
-        int lo = 0;
-        {
-            int hi = nc;
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) / 2;
-                if (rk[mid].i0 <= r0 + take) lo = mid; else hi = mid;
+        if (take < len) {
+            // rank of the item's cluster: rk[lo].i0 <= item < rk[lo].i1; the
+            // items a workgroup takes from one range only increase
+            int lo = 0;
+            {
+                int hi = nc;
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) / 2;
+                    if (rk[mid].i0 <= r0 + take) lo = mid; else hi = mid;
+                }
+            }
+            const bool one = len <= b_dealt(int(gridDim.x), xr);   // every item of the range was dealt
+            for (;;) {
+                const int64_t item = r0 + take;
+                while (rk[lo].i1 <= item) ++lo;
+                const BatchRank d = rk[lo];
+                // one wave, far from the range's end: the next item is claimed
+                // now and its number read after this one, so the atomic's latency
+                // is not waited for (near the end a claimed item would wait for
+                // this one while other workgroups idle)
+                const bool early = BLOCK == 64 && take + ahead < len;
+                uint32_t nxt = 0u;
+                if (early && threadIdx.x == 0) nxt = atomicAdd(q, 1u);
+                b_run<Pol, P, BLOCK, TILE, ROWS, NR>(d, item - d.i0, rec, act, e2, n_hard, ncomp, part, tile);
+                if (one) break;
+                if (early) {
+                    take = wave_uniform(nxt);
+                } else {
+                    __syncthreads();   // the item's tiles and s_take are no longer read
+                    if (threadIdx.x == 0) s_take = atomicAdd(q, 1u);
+                    __syncthreads();
+                    take = wave_uniform(s_take);
+                }
+                if (take >= len) break;
             }
         }
-        for (;;) {
-            const int64_t item = r0 + take;
-            while (rk[lo].i1 <= item) ++lo;
-            const BatchRank d = rk[lo];
-            // one wave, far from the range's end: the next item is claimed
-            // now and its number read after this one, so the atomic's latency
-            // is not waited for (near the end a claimed item would wait for
-            // this one while other workgroups idle)
-            const bool early = BLOCK == 64 && take + ahead < len;
-            uint32_t nxt = 0u;
-            if (early && threadIdx.x == 0) nxt = atomicAdd(q, 1u);
-            b_run<Pol, P, BLOCK, TILE, ROWS>(d, item - d.i0, rec, act, e2, n_hard, ncomp, part, tile);
-            if (early) {
-                take = wave_uniform(nxt);
-            } else {
-                __syncthreads();   // the item's tiles and s_take are no longer read
-                if (threadIdx.x == 0) s_take = atomicAdd(q, 1u);
-                __syncthreads();
-                take = wave_uniform(s_take);
-            }
-            if (take >= len) break;
-        }
+        // a step with no more items than workgroups is all dealt: nothing is
+        // left in the other ranges
+        if (total <= int64_t(gridDim.x) / kXcds * kXcds) return;
     }
 }
 
@@ -642,10 +688,10 @@ k_b_correct(int64_t n, int nc, const int32_t *__restrict__ act, const int32_t *_
     }
 }
 
-// Work queues back to empty (a second force pass on the same plan).
-__global__ void k_b_requeue(BatchPlan *__restrict__ pl)
+// Work queues back to their start (a second force pass on the same plan).
+__global__ void k_b_requeue(BatchPlan *__restrict__ pl, int nc, int grid)
 {
-    if (threadIdx.x < kXcds) pl->queue[threadIdx.x * 16] = 0u;
+    if (threadIdx.x < kXcds) pl->queue[threadIdx.x * 16] = b_queue_start(pl->ioff[nc], grid, int(threadIdx.x));
 }
 
 unsigned nblk(int64_t n, int b) { return unsigned((n + b - 1) / b); }
@@ -659,14 +705,17 @@ template <class Pol, int P>
 hipError_t force_p(const BatchLaunch &L, const void *rec, hipStream_t s)
 {
     const auto *r = static_cast<const typename Pol::Rec *>(rec);
-    if (L.itile == 64)
-        hipLaunchKernelGGL((k_b_force<Pol, P, 64, kBTile, 64>), dim3(L.force_grid), dim3(64), 0, s, r, L.nc, L.act,
+    if (L.itile == 64 && L.halves == 2)
+        hipLaunchKernelGGL((k_b_force<Pol, P, 64, kBTile, 64, 1>), dim3(L.force_grid), dim3(64), 0, s, r, L.nc, L.act,
+                           L.plan, L.eps2, L.n_hard, 3 * (P / 2), L.part);
+    else if (L.itile == 64)
+        hipLaunchKernelGGL((k_b_force<Pol, P, 64, kBTile, 64, 2>), dim3(L.force_grid), dim3(64), 0, s, r, L.nc, L.act,
                            L.plan, L.eps2, L.n_hard, 3 * (P / 2), L.part);
     else if (L.itile == 128)
-        hipLaunchKernelGGL((k_b_force<Pol, P, 64, kBTile, 128>), dim3(L.force_grid), dim3(64), 0, s, r, L.nc, L.act,
+        hipLaunchKernelGGL((k_b_force<Pol, P, 64, kBTile, 128, 2>), dim3(L.force_grid), dim3(64), 0, s, r, L.nc, L.act,
                            L.plan, L.eps2, L.n_hard, 3 * (P / 2), L.part);
     else
-        hipLaunchKernelGGL((k_b_force<Pol, P, 256, 128, 256>), dim3(L.force_grid), dim3(256), 0, s, r, L.nc, L.act,
+        hipLaunchKernelGGL((k_b_force<Pol, P, 256, 128, 256, 1>), dim3(L.force_grid), dim3(256), 0, s, r, L.nc, L.act,
                            L.plan, L.eps2, L.n_hard, 3 * (P / 2), L.part);
     return hipGetLastError();
 }
@@ -692,36 +741,41 @@ hipError_t reduce_p(const BatchLaunch &L, double *o0, double *o1, double *o2, do
 
 hipError_t batch_requeue(const BatchLaunch &L, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_b_requeue, dim3(1), dim3(64), 0, s, L.plan);
+    hipLaunchKernelGGL(k_b_requeue, dim3(1), dim3(64), 0, s, L.plan, L.nc, L.force_grid);
     return hipGetLastError();
 }
 
 template <class Pol, int P>
-int resident_p(int itile, int device)
+int resident_p(int itile, int halves, int device)
 {
     int per_cu = 0, cus = 0;
-    const hipError_t e = itile == 64
-        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 64, kBTile, 64>, 64, 0)
-        : itile == 128 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 64, kBTile, 128>, 64, 0)
-                       : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 256, 128, 256>, 256, 0);
+    hipError_t e;
+    if (itile == 64 && halves == 2)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 64, kBTile, 64, 1>, 64, 0);
+    else if (itile == 64)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 64, kBTile, 64, 2>, 64, 0);
+    else if (itile == 128)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 64, kBTile, 128, 2>, 64, 0);
+    else
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_b_force<Pol, P, 256, 128, 256, 1>, 256, 0);
     if (e != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
     return per_cu * cus;
 }
 
 template <int P>
-int resident_prec(int precision, int itile, int device)
+int resident_prec(int precision, int itile, int halves, int device)
 {
-    if (precision == NBODY_MIXED) return resident_p<PolMx<P, false>, P>(itile, device);
-    if (precision == NBODY_DS) return resident_p<PolDS<P, false>, P>(itile, device);
-    return resident_p<PolF64<P, false>, P>(itile, device);
+    if (precision == NBODY_MIXED) return resident_p<PolMx<P, false>, P>(itile, halves, device);
+    if (precision == NBODY_DS) return resident_p<PolDS<P, false>, P>(itile, halves, device);
+    return resident_p<PolF64<P, false>, P>(itile, halves, device);
 }
 
-int batch_force_resident(int order, int precision, int itile, int device)
+int batch_force_resident(int order, int precision, int itile, int halves, int device)
 {
-    if (order == 4) return resident_prec<4>(precision, itile, device);
-    if (order == 6) return resident_prec<6>(precision, itile, device);
-    return resident_prec<8>(precision, itile, device);
+    if (order == 4) return resident_prec<4>(precision, itile, halves, device);
+    if (order == 6) return resident_prec<6>(precision, itile, halves, device);
+    return resident_prec<8>(precision, itile, halves, device);
 }
 
 hipError_t batch_cid(const BatchLaunch &L, hipStream_t s)
@@ -737,7 +791,7 @@ hipError_t batch_schedule(const BatchLaunch &L, const nbody_state &st, int all_a
     hipLaunchKernelGGL(k_b_count, g, dim3(kBThreads), 0, s, L.off, st.t_tick, st.level, L.nb, L.blk, L.bmin,
                        all_active, L.plan, L.tnext, L.bcnt);
     hipLaunchKernelGGL(k_b_plan, dim3(1), dim3(kBThreads), 0, s, L.nc, L.off, L.ord, L.tnext, L.plan,
-                       3 * (order / 2), L.k_items, L.itile, L.ctr);
+                       3 * (order / 2), L.k_items, L.itile, L.halves, L.grain, L.force_grid, L.ctr);
     hipLaunchKernelGGL(k_b_compact, g, dim3(kBThreads), 0, s, L.off, st.t_tick, st.level, L.nb, L.blk, L.tnext,
                        L.bcnt, all_active, L.plan, L.act);
     return hipGetLastError();

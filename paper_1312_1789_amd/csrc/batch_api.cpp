@@ -107,6 +107,10 @@ bool aligned8(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0
 
 }  // namespace
 
+// Ensembles below this many particles run 64-row tiles as two items of one row
+// per lane: most of their steps have fewer items than the chip has waves.
+constexpr int64_t kHalfTilesBelow = int64_t(1) << 20;
+
 struct nbody_batch {
     nbody_config cfg;
     int nc;
@@ -241,6 +245,8 @@ nbody_status nbody_batch_create(const nbody_config *cfg, int32_t n_clusters, con
     L.n_hard = cfg->eps2 == 0.0 ? (int64_t(1) << 40) : cfg->n_hard;
     L.per_wg = 8;
     L.itile = 64;
+    L.halves = cfg->n < kHalfTilesBelow ? 2 : 1;
+    L.grain = cfg->precision == NBODY_MIXED ? nb::kMixedChunk : 64;
     nb::BatchPlan hp{};
     hp.t_end = INT64_MAX;
     hp.n_live = 0;
@@ -255,7 +261,7 @@ nbody_status nbody_batch_create(const nbody_config *cfg, int32_t n_clusters, con
     hipError_t e = hipGetDevice(&b->device);
     if (e == hipSuccess) {
         b->force_grid_req = 0;
-        L.force_grid = nb::batch_force_resident(cfg->order, cfg->precision, L.itile, b->device);
+        L.force_grid = nb::batch_force_resident(cfg->order, cfg->precision, L.itile, L.halves, b->device);
         if (L.force_grid <= 0) e = hipErrorInvalidDeviceFunction;
         L.k_items = int(std::min<int64_t>(int64_t(L.force_grid) * L.per_wg, nb::kBatchMaxRows / L.itile));
     }
@@ -470,7 +476,7 @@ nbody_status nbody_batch_set_launch(nbody_batch *b, int32_t force_grid, int32_t 
     L.itile = i_tile > 0 ? i_tile : 64;
     L.per_wg = per_wg > 0 ? per_wg : 8;
     b->force_grid_req = force_grid;
-    L.force_grid = force_grid > 0 ? force_grid : nb::batch_force_resident(b->cfg.order, b->cfg.precision, L.itile, b->device);
+    L.force_grid = force_grid > 0 ? force_grid : nb::batch_force_resident(b->cfg.order, b->cfg.precision, L.itile, L.halves, b->device);
     if (L.force_grid <= 0) return fail(NBODY_E_HIP, "occupancy query of the batched force kernel failed");
     L.k_items = int(std::min<int64_t>(int64_t(L.force_grid) * L.per_wg, nb::kBatchMaxRows / L.itile));
     return NBODY_OK;

@@ -126,6 +126,58 @@ def test_batch_force_all_active(order, precision):
             assert st["rms"] <= LOW_TOL[key] and st["max"] <= 10 * LOW_TOL[key], (key, st)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_batch_large_ensemble(precision):
+    """An ensemble of more than 2^20 particles, whose 64-row tiles are one item
+    with two rows per lane (smaller ones take two items of one row per lane):
+    active sets around the edges of the row tiles and lane groups, then a
+    step of many items (more than the workgroups are dealt)."""
+    models = [nbody_ics.plummer(53000 + 37 * c, 960 + c) for c in range(20)]
+    B = _batch(models, 4, precision, n_hard=0, k_min=6, k_max=16)
+    assert B.n >= 1 << 20
+    B.init()
+    B.synchronize()   # the batch has a stream of its own
+    counts = [1, 2, 3, 4, 5, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129]
+    lv = torch.full((B.n,), 9, dtype=torch.int32)
+    for c, k in enumerate(counts):
+        lv[B.off[c]:B.off[c] + k] = 12
+    B.level.copy_(lv.to(B.device))
+    ocfg = _ocfg(B)
+    errs = {k: [] for k in KEYS}
+    torch.cuda.synchronize()
+    h0 = B.to_numpy()
+    B.step(1)
+    aoff, act, f = B.last_step()
+    assert list(np.diff(aoff)) == counts
+    _force_errors(B, models, h0, aoff, act.cpu().numpy(), f.cpu().numpy(), ocfg, 4, errs)
+    # every particle of four clusters at once; some rows of each checked
+    lv = torch.full((B.n,), 6, dtype=torch.int32)
+    lv[:B.off[4]] = 8
+    B.level.copy_(lv.to(B.device))
+    B.t_tick.zero_()
+    torch.cuda.synchronize()
+    h0 = B.to_numpy()
+    B.step(1)
+    aoff, act, f = B.last_step()
+    f = f.cpu().numpy()
+    for c in range(4):
+        hc = B.cluster(h0, c)
+        assert aoff[c + 1] - aoff[c] == models[c].n
+        rows = np.concatenate([np.arange(3), np.arange(models[c].n - 40, models[c].n)]).astype(np.int32)
+        os0 = _ostate(hc, 4)
+        xp, vp, ap, jp = oracle.predict(ocfg, os0, 1 << (TICK_BITS - 8))
+        F = oracle.force(ocfg, os0.m, xp, vp, None, None, act=rows, with_pot=False)
+        for k, key in enumerate(KEYS[:2]):
+            errs[key].append(rel_err(f[k][:, aoff[c]:aoff[c + 1]][:, rows], F[key]))
+    for key in KEYS[:2]:
+        st = err_stats(np.concatenate(errs[key]))
+        say("batch large ensemble %s %s rms %.2e max %.2e" % (precision, key, st["rms"], st["max"]))
+        if precision == "fp64":
+            assert st["rms"] <= 1e-12 and st["max"] <= 1e-9, (key, st)
+        else:
+            assert st["rms"] <= LOW_TOL[key] and st["max"] <= 10 * LOW_TOL[key], (key, st)
+
+
 @pytest.mark.parametrize("shape,precision", [((64, 4), "fp64"), ((256, 4), "fp64"), ((64, 16), "fp64"),
                                              ((256, 1), "fp64"), ((64, 1), "fp64"), ((128, 4), "fp64"),
                                              ((64, 32), "fp64"), ((64, 4), "mixed"), ((128, 32), "mixed")])
