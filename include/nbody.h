@@ -368,9 +368,9 @@ nbody_status nbody_batch_set_end(nbody_batch *b, int64_t t_end_tick);
 /* Enqueue k batched steps directly (asynchronous; no host round trip). */
 nbody_status nbody_batch_step(nbody_batch *b, nbody_state *state, int64_t k);
 
-/* Capture one batched step on `state` (its pointers are baked in) into a HIP
- * graph; nbody_batch_replay launches it k times.  A new capture replaces the
- * old one. */
+/* Capture batched steps on `state` (its pointers are baked in) into HIP graphs
+ * of one and of eight steps; nbody_batch_replay launches k steps' worth of
+ * them.  A new capture replaces the old one. */
 nbody_status nbody_batch_capture(nbody_batch *b, nbody_state *state);
 nbody_status nbody_batch_replay(nbody_batch *b, int64_t k);
 

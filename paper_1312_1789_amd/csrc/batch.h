@@ -68,6 +68,8 @@ struct BatchLaunch {
     int64_t *tnext;             // [nc]   next block time of each cluster
     int64_t *bmin;              // [nc][nb]
     int32_t *bcnt;              // [nc][nb]
+    int32_t *brow;              // [nblk]  first row of each scheduling block in the active list
+    unsigned *arrive;           // arrival counters of the schedule (zero between launches)
     BatchPlan *plan;
     BatchCounters *ctr;
     int32_t *act;               // [n] concatenated active lists
@@ -84,15 +86,21 @@ struct BatchLaunch {
 };
 
 hipError_t batch_cid(const BatchLaunch &L, hipStream_t s);
+// The step's schedule and plan (order: of the pair terms the partials hold);
+// all_active: every particle at t = 0.
 hipError_t batch_schedule(const BatchLaunch &L, const nbody_state &st, int all_active, int order, hipStream_t s);
-hipError_t batch_predict(const BatchLaunch &L, const nbody_state &st, int order, int precision, void *rec,
+// The active lists of a schedule: of all particles (initialisation), or of a
+// step with every particle of the stepping clusters predicted.
+hipError_t batch_list_all(const BatchLaunch &L, const nbody_state &st, hipStream_t s);
+hipError_t batch_advance(const BatchLaunch &L, const nbody_state &st, int order, int precision, void *rec,
                          hipStream_t s);
 // Reset the work queues (a second force pass on the same plan).
 hipError_t batch_requeue(const BatchLaunch &L, hipStream_t s);
 hipError_t batch_force(const BatchLaunch &L, int order, int precision, const void *rec, hipStream_t s);
 hipError_t batch_reduce(const BatchLaunch &L, int order, double *o0, double *o1, double *o2, double *o3,
                         hipStream_t s);
-hipError_t batch_correct(const BatchLaunch &L, const nbody_config &c, const nbody_state &st, hipStream_t s);
+// Split sums and corrector of the step.
+hipError_t batch_finish(const BatchLaunch &L, const nbody_config &c, const nbody_state &st, hipStream_t s);
 // Workgroups of the persistent force kernel (i-tile itile) that fit on the
 // device at once.
 int batch_force_resident(int order, int precision, int itile, int halves, int device);

@@ -5,17 +5,23 @@
 // replayed without the host.
 //
 // Sequence of one batched step:
-//   k_b_min / k_b_count  per (cluster, 1024-particle block): next-time minima,
-//                        the cluster's t_next, active counts;
-//   k_b_plan             one block: active offsets, j-splits and work items
-//                        per cluster (largest clusters first), counters, and
-//                        the reset of the work queues;
-//   k_b_compact          ordered active lists;
-//   k_b_predict          every particle to its cluster's t_next;
+//   k_b_schedule         per (cluster, 1024-particle block): next-time minima and
+//                        counts, the clusters' t_next and active counts (by each
+//                        cluster's last workgroup), the plan (by the last of all:
+//                        active offsets, j-splits and work items per cluster,
+//                        largest clusters first, counters, work queues);
+//   k_b_advance          ordered active lists, and every particle predicted to
+//                        its cluster's t_next;
 //   k_b_force            persistent: workgroups take (cluster, i-tile, j-split)
 //                        items from per-XCD queues until all are empty;
-//   k_b_reduce           split partials summed in split order;
-//   k_b_correct          corrector, interpolation and new steps.
+//   k_b_finish           split partials summed in split order, corrector,
+//                        interpolation and new steps.
+// Most steps of a small ensemble are a few microseconds of work per kernel: as
+// eight kernels (three for the schedule, compaction, predictor, force, split sum,
+// corrector) the seven small ones took 42 us a step at 32 clusters of 2^10 to
+// 2^14, with 2 us between kernels and 9 between graphs of one step; the three
+// take 27, in graphs of eight steps without gaps: t = 1/256 in 13.3 ms instead of
+// 16.2 with the same force kernel.
 // Method as in the single-system kernels (paper: Abstract; Sec. "Codes
 // description"): Hermite block steps of order 4, 6 or 8 and direct-summation
 // softened gravity with its derivatives (Nitadori & Makino 2008).
@@ -31,6 +37,7 @@ namespace {
 constexpr int kBBlock = kBatchSchedBlock;
 constexpr int kBTile = 32;   // records per LDS tile of the one-wave force workgroups
 constexpr int64_t kBItemMin = 32768;   // pair evaluations of a work item worth claiming
+constexpr int kBSub = 32;               // clusters per arrival counter
 constexpr int kBThreads = 256;  // threads per scheduling block (4 particles each)
 
 __device__ __forceinline__ int64_t b_next(const int64_t *t_tick, const int32_t *level, int64_t i)
@@ -38,78 +45,62 @@ __device__ __forceinline__ int64_t b_next(const int64_t *t_tick, const int32_t *
     return t_tick[i] + (int64_t(1) << (kLevelMax - level[i]));
 }
 
-// Block b of cluster c covers [off[c] + b*kBBlock, min(off[c] + (b+1)*kBBlock, off[c+1])); the
-// launch has one workgroup per such block, (c, b) = blk[2x], blk[2x + 1].
-// Also clears the cluster's active count, which k_b_count accumulates.
-__global__ void __launch_bounds__(kBThreads)
-k_b_min(const int64_t *__restrict__ off, const int64_t *__restrict__ t_tick, const int32_t *__restrict__ level,
-        int nb, const int32_t *__restrict__ blk, int64_t *__restrict__ bmin, BatchPlan *__restrict__ pl)
+// Accesses that other workgroups of the same launch see, and the wait that
+// orders them before an arrival is counted (as in the single-system step).
+template <class T> __device__ __forceinline__ T shared_load(const T *p)
 {
-    __shared__ int64_t sm[kBThreads];
-    const int c = blk[2 * blockIdx.x], b = blk[2 * blockIdx.x + 1];
-    if (b == 0 && threadIdx.x == 0) pl->nact[c] = 0;
-    const int64_t lo = off[c] + int64_t(b) * kBBlock, hi = off[c + 1];
-    int64_t mn = INT64_MAX;
-    for (int k = 0; k < kBBlock / kBThreads; ++k) {
-        const int64_t i = lo + int64_t(k) * kBThreads + threadIdx.x;
-        if (i < hi && i < lo + kBBlock) {
-            const int64_t t = b_next(t_tick, level, i);
-            mn = t < mn ? t : mn;
-        }
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T> __device__ __forceinline__ void shared_store(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+constexpr int kBWaves = kBThreads / 64;
+
+// Least time and number of particles at it over the block; every thread gets
+// both.
+__device__ __forceinline__ void block_min_count(int64_t &m, int64_t &c, int64_t *sm, int64_t *sc)
+{
+    for (int o = 32; o > 0; o >>= 1) {
+        const int64_t m2 = __shfl_xor(m, o, 64), c2 = __shfl_xor(c, o, 64);
+        c = m2 < m ? c2 : (m2 == m ? c + c2 : c);
+        m = m2 < m ? m2 : m;
     }
-    sm[threadIdx.x] = mn;
+    __syncthreads();   // sm, sc are no longer read
+    if ((threadIdx.x & 63) == 0) {
+        sm[threadIdx.x >> 6] = m;
+        sc[threadIdx.x >> 6] = c;
+    }
     __syncthreads();
-    for (int s = kBThreads / 2; s > 0; s >>= 1) {
-        if (int(threadIdx.x) < s && sm[threadIdx.x + s] < sm[threadIdx.x]) sm[threadIdx.x] = sm[threadIdx.x + s];
-        __syncthreads();
+    m = sm[0];
+    c = sc[0];
+    for (int k = 1; k < kBWaves; ++k) {
+        c = sm[k] < m ? sc[k] : (sm[k] == m ? c + sc[k] : c);
+        m = sm[k] < m ? sm[k] : m;
     }
-    if (threadIdx.x == 0) bmin[int64_t(c) * nb + b] = sm[0];
 }
 
-// Cluster minimum (from the block minima), then this block's active count,
-// also added into the cluster's count (integer atomics: the total does not
-// depend on their order).  all_active != 0 marks every particle active
-// (initialisation).
-__global__ void __launch_bounds__(kBThreads)
-k_b_count(const int64_t *__restrict__ off, const int64_t *__restrict__ t_tick, const int32_t *__restrict__ level,
-          int nb, const int32_t *__restrict__ blk, const int64_t *__restrict__ bmin, int all_active,
-          BatchPlan *__restrict__ pl, int64_t *__restrict__ tnext, int32_t *__restrict__ bcnt)
+// Exclusive scan of one value per thread over the block; *total the sum.
+__device__ __forceinline__ int64_t block_excl(int64_t x, int64_t *sh, int64_t *total)
 {
-    __shared__ int64_t sm[kBThreads];
-    __shared__ int cnt[kBThreads];
-    const int c = blk[2 * blockIdx.x], b = blk[2 * blockIdx.x + 1];
-    const int nbc = int((off[c + 1] - off[c] + kBBlock - 1) / kBBlock);   // the cluster's blocks
-    int64_t mn = INT64_MAX;
-    for (int k = threadIdx.x; k < nbc; k += kBThreads) {
-        const int64_t v = bmin[int64_t(c) * nb + k];
-        mn = v < mn ? v : mn;
+    const int lane = int(threadIdx.x) & 63, w = int(threadIdx.x) >> 6;
+    int64_t incl = x;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
     }
-    sm[threadIdx.x] = mn;
+    __syncthreads();   // sh is no longer read
+    if (lane == 63) sh[w] = incl;
     __syncthreads();
-    for (int s = kBThreads / 2; s > 0; s >>= 1) {
-        if (int(threadIdx.x) < s && sm[threadIdx.x + s] < sm[threadIdx.x]) sm[threadIdx.x] = sm[threadIdx.x + s];
-        __syncthreads();
+    int64_t before = 0, tot = 0;
+    for (int k = 0; k < kBWaves; ++k) {
+        if (k < w) before += sh[k];
+        tot += sh[k];
     }
-    // initialisation: every particle at t = 0; otherwise clusters past t_end rest
-    const int64_t tn = all_active ? 0 : sm[0];
-    const bool live = all_active || tn <= pl->t_end;
-    const int64_t lo = off[c] + int64_t(b) * kBBlock, hi = off[c + 1];
-    int k0 = 0;
-    for (int k = 0; k < kBBlock / kBThreads; ++k) {
-        const int64_t i = lo + int64_t(k) * kBThreads + threadIdx.x;
-        if (live && i < hi && i < lo + kBBlock && (all_active || b_next(t_tick, level, i) == tn)) ++k0;
-    }
-    cnt[threadIdx.x] = k0;
-    __syncthreads();
-    for (int s = kBThreads / 2; s > 0; s >>= 1) {
-        if (int(threadIdx.x) < s) cnt[threadIdx.x] += cnt[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        bcnt[int64_t(c) * nb + b] = cnt[0];
-        if (cnt[0] > 0) atomicAdd(reinterpret_cast<unsigned long long *>(&pl->nact[c]), (unsigned long long)cnt[0]);
-        if (b == 0) tnext[c] = tn;
-    }
+    *total = tot;
+    return before + incl - x;
 }
 
 // Exclusive scan of v[0..n) in one block (chunks of kBThreads, running carry).
@@ -118,18 +109,10 @@ __device__ void block_scan(int64_t *v, int n, int64_t *sh)
     int64_t carry = 0;
     for (int c0 = 0; c0 < n; c0 += kBThreads) {
         const int c = c0 + threadIdx.x;
-        const int64_t x = c < n ? v[c] : 0;
-        sh[threadIdx.x] = x;
-        __syncthreads();
-        for (int o = 1; o < kBThreads; o <<= 1) {
-            const int64_t add = int(threadIdx.x) >= o ? sh[threadIdx.x - o] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += add;
-            __syncthreads();
-        }
-        if (c < n) v[c] = carry + sh[threadIdx.x] - x;
-        carry += sh[kBThreads - 1];
-        __syncthreads();
+        int64_t tot = 0;
+        const int64_t ex = block_excl(c < n ? v[c] : 0, sh, &tot);
+        if (c < n) v[c] = carry + ex;
+        carry += tot;
     }
     if (threadIdx.x == 0) v[n] = carry;
     __syncthreads();
@@ -139,15 +122,9 @@ __device__ void block_scan(int64_t *v, int n, int64_t *sh)
 // every thread).
 __device__ int64_t block_sum(int64_t v, int64_t *sh)
 {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int st = kBThreads / 2; st > 0; st >>= 1) {
-        if (int(threadIdx.x) < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
-    }
-    const int64_t r = sh[0];
-    __syncthreads();
-    return r;
+    int64_t tot = 0;
+    (void)block_excl(v, sh, &tot);
+    return tot;
 }
 
 // Workgroups of range x's XCD: the items of the range that are dealt to them.
@@ -161,6 +138,41 @@ __device__ __forceinline__ uint32_t b_queue_start(int64_t total, int grid, int x
     return uint32_t(len < dealt ? len : dealt);
 }
 
+// Work items of a row tile and split.
+__device__ __forceinline__ int b_tile_items(const BatchLaunch &L) { return L.itile == 64 ? L.halves : 1; }
+
+// The work of one cluster in a step: row tiles, j-splits sp of jc particles.
+struct BatchCut {
+    int32_t tiles, sp, jc;
+};
+__device__ __forceinline__ BatchCut b_cut(int64_t na, int64_t nn, int itile, int grain, int64_t w_item)
+{
+    BatchCut k;
+    k.tiles = int32_t((unsigned(na) + unsigned(itile) - 1u) / unsigned(itile));
+    int64_t sp = (int64_t(itile) * nn + w_item - 1) / w_item;
+    const int64_t sp_max = (nn + grain - 1) / grain;   // pieces of at least a grain (MIXED: an FP32 chunk)
+    sp = sp < 1 ? 1 : (sp > sp_max ? sp_max : sp);
+    unsigned jc = (unsigned(nn) + unsigned(sp) - 1u) / unsigned(sp);
+    jc = (jc + unsigned(grain) - 1u) / unsigned(grain) * unsigned(grain);
+    k.jc = int32_t(jc);
+    k.sp = int32_t((unsigned(nn) + jc - 1u) / jc);
+    return k;
+}
+
+// Pair evaluations per item for W in all.  Items of at least kBItemMin pairs (an
+// item costs a few microseconds of loads before its first pair, and the claim
+// of one from a counter that an eighth of the chip shares some 50 ns), up to the
+// number asked for; a step of less than four such items per workgroup is cut
+// into as many as there are workgroups (an eighth less, as the cuts round up),
+// all dealt.
+__device__ __forceinline__ int64_t b_item_size(const BatchLaunch &L, int64_t W)
+{
+    int64_t k = W / kBItemMin;
+    if (k < 4 * int64_t(L.force_grid)) k = int64_t(L.force_grid) * 7 / 8;
+    if (k > L.k_items) k = L.k_items;
+    return W * b_tile_items(L) / k + 1;
+}
+
 // The plan of one batched step (one block).  For every cluster: active
 // offset, j-splits and work items.  Items are sized by cost: the step's
 // padded work W = sum_c tiles_c * itile * N_c is cut into about k_items items
@@ -170,17 +182,17 @@ __device__ __forceinline__ uint32_t b_queue_start(int64_t total, int grid, int x
 // ord[] (largest clusters first).  Bound used for the partial buffer:
 // s_c <= itile N_c k_items / W + 1, so sum_c s_c a_c <= itile k_items + n.
 // Also resets the work queues and adds the step's interactions to the counters.
-__global__ void __launch_bounds__(kBThreads)
-k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ ord, const int64_t *__restrict__ tnext,
-         BatchPlan *__restrict__ pl, int ncomp, int k_items, int itile, int halves, int grain, int grid,
-         BatchCounters *__restrict__ ctr)
+__device__ __forceinline__ void plan_step(const BatchLaunch &L, int ncomp, int64_t *sh)
 {
-    __shared__ int64_t sh[kBThreads];
+    const int nc = L.nc, itile = L.itile, grid = L.force_grid, grain = L.grain;
+    const int64_t *off = L.off;
+    const int32_t *ord = L.ord;
+    BatchPlan *pl = L.plan;
     int64_t w = 0, inter = 0, live = 0;
     for (int c = threadIdx.x; c < nc; c += kBThreads) {
-        const int64_t a = pl->nact[c], nn = off[c + 1] - off[c];
+        const int64_t a = shared_load(&pl->nact[c]), nn = off[c + 1] - off[c];
         pl->aoff[c] = a;
-        if (a > 0) pl->tcur[c] = tnext[c];
+        if (a > 0) pl->tcur[c] = shared_load(&L.tnext[c]);
         w += (a + itile - 1) / itile * itile * nn;
         inter += a * nn;
         live += a > 0 ? 1 : 0;
@@ -188,32 +200,17 @@ k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ or
     const int64_t W = block_sum(w, sh);
     inter = block_sum(inter, sh);
     live = block_sum(live, sh);
-    // Items of at least kBItemMin pairs (an item costs a few microseconds of
-    // loads before its first pair, and the claim of one from a counter that an
-    // eighth of the chip shares some 50 ns), up to the number asked for; a step
-    // of less than four such items per workgroup is cut into as many as there
-    // are workgroups (an eighth less, as the cuts round up), all dealt.
-    const int64_t tiles_per = itile == 64 ? halves : 1;   // items of a row tile and split
-    int64_t k = W / kBItemMin;
-    if (k < 4 * int64_t(grid)) k = int64_t(grid) * 7 / 8;
-    if (k > k_items) k = k_items;
-    const int64_t w_item = W * tiles_per / k + 1;
+    const int64_t w_item = b_item_size(L, W);
     block_scan(pl->aoff, nc, sh);
     // splits, items (in rank order), partial rows (in cluster order)
     for (int r = threadIdx.x; r < nc; r += kBThreads) {
         const int c = ord[r];
-        const int64_t na = pl->nact[c], nn = off[c + 1] - off[c];
-        const int64_t tiles = (na + itile - 1) / itile;
-        int64_t sp = (int64_t(itile) * nn + w_item - 1) / w_item;
-        const int64_t sp_max = (nn + grain - 1) / grain;   // pieces of at least a grain (MIXED: an FP32 chunk)
-        sp = sp < 1 ? 1 : (sp > sp_max ? sp_max : sp);
-        int64_t jc = (nn + sp - 1) / sp;
-        jc = (jc + grain - 1) / grain * grain;
-        sp = (nn + jc - 1) / jc;
-        pl->split[c] = int32_t(sp);
-        pl->jchunk[c] = jc;
-        pl->ioff[r] = tiles * sp * tiles_per;
-        pl->poff[c] = sp * na * ncomp;
+        const int64_t na = shared_load(&pl->nact[c]), nn = off[c + 1] - off[c];
+        const BatchCut k = b_cut(na, nn, itile, grain, w_item);
+        pl->split[c] = k.sp;
+        pl->jchunk[c] = k.jc;
+        pl->ioff[r] = int64_t(k.tiles) * k.sp * b_tile_items(L);
+        pl->poff[c] = int64_t(k.sp) * na * ncomp;
     }
     __syncthreads();
     block_scan(pl->ioff, nc, sh);
@@ -228,7 +225,7 @@ k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ or
         d.poff = pl->poff[c];
         d.aoff = pl->aoff[c];
         d.nn = int32_t(off[c + 1] - off[c]);
-        d.na = int32_t(pl->nact[c]);
+        d.na = int32_t(shared_load(&pl->nact[c]));
         d.sp = pl->split[c];
         d.c = c;
         pl->rank[r] = d;
@@ -236,51 +233,194 @@ k_b_plan(int nc, const int64_t *__restrict__ off, const int32_t *__restrict__ or
     if (threadIdx.x < kXcds) pl->queue[threadIdx.x * 16] = b_queue_start(pl->ioff[nc], grid, int(threadIdx.x));
     if (threadIdx.x == 0) {
         pl->n_live = live;
-        ctr->interactions += inter;
-        ctr->sum_n_act += pl->aoff[nc];
-        ctr->steps += 1;
+        L.ctr->interactions += inter;
+        L.ctr->sum_n_act += pl->aoff[nc];
+        L.ctr->steps += 1;
     }
 }
 
-// Ordered active lists: block (b, c) writes its actives after those of the
-// cluster's earlier blocks, at aoff[c] + sum of bcnt[c][0 .. b).
-__global__ void __launch_bounds__(kBThreads)
-k_b_compact(const int64_t *__restrict__ off, const int64_t *__restrict__ t_tick, const int32_t *__restrict__ level,
-            int nb, const int32_t *__restrict__ blk, const int64_t *__restrict__ tnext,
-            const int32_t *__restrict__ bcnt, int all_active, const BatchPlan *__restrict__ pl,
-            int32_t *__restrict__ act)
+// The same plan for up to kBThreads clusters, one per thread: the values stay in
+// registers and LDS instead of passing through memory between the scans (14 us
+// for the schedule kernel at 32 clusters with plan_step, 12 with this).
+__device__ __forceinline__ void plan_small(const BatchLaunch &L, int ncomp, int64_t *sh)
 {
-    __shared__ int s[kBThreads];
-    __shared__ int64_t sb[kBThreads];
-    constexpr int PER = kBBlock / kBThreads;
-    const int c = blk[2 * blockIdx.x], b = blk[2 * blockIdx.x + 1];
-    int64_t before = 0;
-    for (int k = threadIdx.x; k < b; k += kBThreads) before += bcnt[int64_t(c) * nb + k];
-    const int64_t block_off = pl->aoff[c] + block_sum(before, sb);
-    const int64_t lo = off[c] + int64_t(b) * kBBlock, hi = off[c + 1];
-    const int64_t tn = tnext[c];
-    const bool live = pl->nact[c] > 0;
-    const int64_t base = lo + int64_t(threadIdx.x) * PER;
-    int flags[PER];
-    int k0 = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int64_t i = base + k;
-        flags[k] = (live && i < hi && (all_active || b_next(t_tick, level, i) == tn)) ? 1 : 0;
-        k0 += flags[k];
+    __shared__ int64_t s_base[kBThreads], s_aoff[kBThreads];
+    __shared__ int32_t s_nn[kBThreads], s_na[kBThreads];
+    const int t = int(threadIdx.x), nc = L.nc, itile = L.itile;
+    BatchPlan *pl = L.plan;
+    const bool on = t < nc;
+    const int cr = on ? L.ord[t] : 0;   // cluster of rank t
+    const int64_t a = on ? shared_load(&pl->nact[t]) : 0, tn = on ? shared_load(&L.tnext[t]) : 0;
+    const int64_t base = on ? L.off[t] : 0, nn = on ? L.off[t + 1] - base : 0;
+    int64_t n_act = 0;
+    const int64_t aoff = block_excl(a, sh, &n_act);
+    const int64_t W = block_sum(int64_t((unsigned(a) + unsigned(itile) - 1u) / unsigned(itile)) * itile * nn, sh);
+    const int64_t inter = block_sum(a * nn, sh), live = block_sum(a > 0 ? 1 : 0, sh);
+    const int64_t w_item = b_item_size(L, W);
+    if (on) {
+        pl->aoff[t] = aoff;
+        if (a > 0) pl->tcur[t] = tn;
+        s_base[t] = base;
+        s_aoff[t] = aoff;
+        s_nn[t] = int32_t(nn);
+        s_na[t] = int32_t(a);
     }
-    s[threadIdx.x] = k0;
     __syncthreads();
-    for (int o = 1; o < kBThreads; o <<= 1) {
-        const int add = int(threadIdx.x) >= o ? s[threadIdx.x - o] : 0;
-        __syncthreads();
-        s[threadIdx.x] += add;
-        __syncthreads();
+    BatchRank d{};
+    BatchCut k{0, 0, 0};
+    if (on) {
+        d.c = cr;
+        d.base = s_base[cr];
+        d.aoff = s_aoff[cr];
+        d.nn = s_nn[cr];
+        d.na = s_na[cr];
+        k = b_cut(d.na, d.nn, itile, L.grain, w_item);
+        d.sp = k.sp;
+        d.jc = k.jc;
     }
-    int64_t pos = block_off + s[threadIdx.x] - k0;
+    const int64_t items = int64_t(k.tiles) * k.sp * b_tile_items(L);
+    int64_t n_items = 0, n_part = 0;
+    d.i0 = block_excl(items, sh, &n_items);
+    d.i1 = d.i0 + items;
+    d.poff = block_excl(int64_t(d.sp) * d.na * ncomp, sh, &n_part);
+    if (on) {
+        pl->rank[t] = d;
+        pl->split[cr] = d.sp;
+        pl->poff[cr] = d.poff;
+    }
+    if (t < kXcds) pl->queue[t * 16] = b_queue_start(n_items, L.force_grid, t);
+    if (t == 0) {
+        pl->aoff[nc] = n_act;
+        pl->ioff[nc] = n_items;
+        pl->n_live = live;
+        L.ctr->interactions += inter;
+        L.ctr->sum_n_act += n_act;
+        L.ctr->steps += 1;
+    }
+}
+
+// Block b of cluster c covers [off[c] + b*kBBlock, min(off[c] + (b+1)*kBBlock, off[c+1])); the
+// launch has one workgroup per such block, (c, b) = blk[2x], blk[2x + 1].  Each
+// takes its block's least next time and the particles at it; the last of a
+// cluster's workgroups takes the cluster's (clusters past t_end rest: no
+// active particles), and the last of all makes the step's plan.  all_active
+// marks every particle active at t = 0 (initialisation).  Arrivals are counted
+// per cluster, per kBSub clusters, and in all.
+__global__ void __launch_bounds__(kBThreads)
+k_b_schedule(BatchLaunch L, const int64_t *__restrict__ t_tick, const int32_t *__restrict__ level, int all_active,
+             int ncomp)
+{
+    __shared__ int64_t sm[kBWaves], sc[kBWaves], sh[kBWaves];
+    __shared__ int s_last;
+    const int c = L.blk[2 * blockIdx.x], b = L.blk[2 * blockIdx.x + 1], tid = int(threadIdx.x);
+    const int64_t lo = L.off[c] + int64_t(b) * kBBlock, hi = L.off[c + 1];
+    const int nbc = int((hi - L.off[c] + kBBlock - 1) / kBBlock);   // the cluster's blocks
+    int64_t mn = INT64_MAX, cn = 0;
 #pragma unroll
-    for (int k = 0; k < PER; ++k)
-        if (flags[k]) act[pos++] = int32_t(base + k);
+    for (int k = 0; k < kBBlock / kBThreads; ++k) {
+        const int64_t i = lo + int64_t(k) * kBThreads + tid;
+        if (i < hi && i < lo + kBBlock) {
+            const int64_t t = all_active ? 0 : b_next(t_tick, level, i);
+            cn = t < mn ? 1 : (t == mn ? cn + 1 : cn);
+            mn = t < mn ? t : mn;
+        }
+    }
+    block_min_count(mn, cn, sm, sc);
+    unsigned *of_cluster = L.arrive, *of_sub = L.arrive + L.nc, *of_all = of_sub + (L.nc + kBSub - 1) / kBSub;
+    if (tid == 0) {
+        shared_store(&L.bmin[int64_t(c) * L.nb + b], mn);
+        shared_store(&L.bcnt[int64_t(c) * L.nb + b], int32_t(cn));
+        bool last = true;
+        if (nbc > 1) {
+            stores_done();
+            last = atomicAdd(&of_cluster[c], 1u) == unsigned(nbc) - 1;
+            if (last) shared_store(&of_cluster[c], 0u);   // for the next launch
+        }
+        s_last = last ? 1 : 0;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (nbc > 1) {
+        mn = INT64_MAX;
+        cn = 0;
+        for (int k = tid; k < nbc; k += kBThreads) {
+            const int64_t t = shared_load(&L.bmin[int64_t(c) * L.nb + k]);
+            const int64_t q = shared_load(&L.bcnt[int64_t(c) * L.nb + k]);
+            cn = t < mn ? q : (t == mn ? cn + q : cn);
+            mn = t < mn ? t : mn;
+        }
+        block_min_count(mn, cn, sm, sc);
+    }
+    __syncthreads();   // s_last has been read
+    if (tid == 0) {
+        const bool live = all_active || mn <= L.plan->t_end;
+        shared_store(&L.tnext[c], mn);
+        shared_store(&L.plan->nact[c], live ? cn : int64_t(0));
+        stores_done();
+        const int sub = c / kBSub, subs = (L.nc + kBSub - 1) / kBSub;
+        const unsigned size = unsigned(L.nc - sub * kBSub < kBSub ? L.nc - sub * kBSub : kBSub);
+        bool last = atomicAdd(&of_sub[sub], 1u) == size - 1;
+        if (last) {
+            shared_store(&of_sub[sub], 0u);
+            last = subs == 1 || atomicAdd(of_all, 1u) == unsigned(subs) - 1;
+            if (last) shared_store(of_all, 0u);
+        }
+        s_last = last ? 1 : 0;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (L.nc <= kBThreads) plan_small(L, ncomp, sh);
+    else plan_step(L, ncomp, sh);
+}
+
+// The active particles of block (c, b), written after those of the cluster's
+// earlier blocks, at aoff[c] + the sum of their counts at the cluster's time (kept
+// in brow[] for the step's end); and, unless PREC is negative (initialisation),
+// every particle of the block predicted to the cluster's time.  Workgroup y of a
+// block predicts a quarter of it; the first writes the list as well.
+template <int P, int PREC>
+__global__ void __launch_bounds__(kBThreads)
+k_b_advance(BatchLaunch L, nbody_state st, int all_active, void *__restrict__ rec_out)
+{
+    __shared__ int64_t sh[kBWaves];
+    constexpr int PER = kBBlock / kBThreads;
+    const int c = L.blk[2 * blockIdx.x], b = L.blk[2 * blockIdx.x + 1], tid = int(threadIdx.x);
+    const BatchPlan *pl = L.plan;
+    if (pl->nact[c] == 0) return;   // a resting cluster: its records are not read
+    const int64_t tn = L.tnext[c];
+    const int64_t *bmin = L.bmin + int64_t(c) * L.nb;
+    const int32_t *bcnt = L.bcnt + int64_t(c) * L.nb;
+    const int64_t lo = L.off[c] + int64_t(b) * kBBlock;
+    const int64_t hi = L.off[c + 1] < lo + kBBlock ? L.off[c + 1] : lo + kBBlock;
+    if constexpr (PREC >= 0) {
+        const double *ds[6] = {st.d[0], st.d[1], st.d[2], st.d[3], st.d[4], st.d[5]};
+        const int64_t i = lo + int64_t(blockIdx.y) * kBThreads + tid;
+        if (i < hi) {
+            const double dt = double(tn - st.t_tick[i]) * (1.0 / double(kTicksPerUnit));
+            predict_one<P, PREC>(L.n, i, dt, st.m, st.x, st.v, ds, rec_out);
+        }
+    }
+    if (blockIdx.y != 0 || bmin[b] != tn) return;   // uniform over the workgroup
+    {
+        int64_t before = 0;
+        for (int k = tid; k < b; k += kBThreads) before += bmin[k] == tn ? bcnt[k] : 0;
+        const int64_t row0 = pl->aoff[c] + block_sum(before, sh);
+        if (tid == 0) L.brow[blockIdx.x] = int32_t(row0);
+        const int64_t base = lo + int64_t(tid) * PER;
+        int flags[PER];
+        int k0 = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int64_t i = base + k;
+            flags[k] = (i < hi && (all_active || b_next(st.t_tick, st.level, i) == tn)) ? 1 : 0;
+            k0 += flags[k];
+        }
+        int64_t tot = 0;
+        int64_t pos = row0 + block_excl(k0, sh, &tot);
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (flags[k]) L.act[pos++] = int32_t(base + k);
+    }
 }
 
 __device__ __forceinline__ int find_cluster(const int64_t *__restrict__ off, int nc, int64_t i)
@@ -298,24 +438,6 @@ k_b_cid(const int64_t *__restrict__ off, int nc, int64_t n, int32_t *__restrict_
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) cid[i] = find_cluster(off, nc, i);
-}
-
-template <int P, int PREC>
-__global__ void __launch_bounds__(256)
-k_b_predict(int64_t n, const int32_t *__restrict__ cid, const int64_t *__restrict__ tnext,
-            const BatchPlan *__restrict__ pl,
-            const double *__restrict__ m, const double *__restrict__ x, const double *__restrict__ v,
-            const double *__restrict__ d0, const double *__restrict__ d1, const double *__restrict__ d2,
-            const double *__restrict__ d3, const double *__restrict__ d4, const double *__restrict__ d5,
-            const int64_t *__restrict__ t_tick, void *__restrict__ rec_out)
-{
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int c = cid[i];
-    if (pl->nact[c] == 0) return;   // resting cluster: its records are not read
-    const double dt = double(tnext[c] - t_tick[i]) * (1.0 / double(kTicksPerUnit));
-    const double *ds[6] = {d0, d1, d2, d3, d4, d5};
-    predict_one<P, PREC>(n, i, dt, m, x, v, ds, rec_out);
 }
 
 // One work item of a 64-lane workgroup: the rows of one i-tile against the
@@ -667,24 +789,64 @@ k_b_reduce(int nc, int64_t n, const BatchPlan *__restrict__ pl, const int32_t *_
     }
 }
 
+// The end of a step for block (c, b): the split partials of its active rows
+// summed (as k_b_reduce: a group of kRedLanes lanes per row, the same order) to the
+// step's forces, then the rows corrected, kFinRows at a time.  The workgroups y of
+// a block share its rows.
+constexpr int kFinRows = 128;
+
 template <int P>
-__global__ void __launch_bounds__(256)
-k_b_correct(int64_t n, int nc, const int32_t *__restrict__ act, const int32_t *__restrict__ cid,
-            const int64_t *__restrict__ tnext, const BatchPlan *__restrict__ pl, double *__restrict__ x,
-            double *__restrict__ v, double *__restrict__ d0, double *__restrict__ d1, double *__restrict__ d2,
-            double *__restrict__ d3, double *__restrict__ d4, double *__restrict__ d5, int64_t *__restrict__ t_tick,
-            int32_t *__restrict__ level, const double *__restrict__ force, double eta, int rule, int k_min, int k_max,
-            BatchCounters *__restrict__ ctr)
+__global__ void __launch_bounds__(kBThreads)
+k_b_finish(BatchLaunch L, nbody_state st, double eta, int rule, int k_min, int k_max)
 {
-    const int64_t total = pl->aoff[nc];
-    double *dst[6] = {d0, d1, d2, d3, d4, d5};
-    const double *fnew[4] = {force, force + 3 * n, force + 6 * n, force + 9 * n};
-    for (int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; r < total; r += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t i = act[r];
-        if (i < 0 || i >= n) continue;
-        const int fl = correct_one<P>(n, i, tnext[cid[i]], fnew, n, r, x, v, dst, t_tick, level, eta, rule, k_min, k_max);
-        if (fl & 2) atomicAdd(&ctr->underflow, 1ull);
-        if (fl & 1) atomicAdd(&ctr->nonfinite, 1ull);
+    constexpr int NV = 3 * (P / 2);
+    __shared__ double f[NV][kFinRows];
+    const int c = L.blk[2 * blockIdx.x], b = L.blk[2 * blockIdx.x + 1], tid = int(threadIdx.x);
+    const BatchPlan *pl = L.plan;
+    const int64_t na = pl->nact[c];
+    if (na == 0) return;
+    const int64_t tn = L.tnext[c];
+    if (L.bmin[int64_t(c) * L.nb + b] != tn) return;
+    const int all = L.bcnt[int64_t(c) * L.nb + b], first = all * int(blockIdx.y) / int(gridDim.y);
+    const int cnt = all * (int(blockIdx.y) + 1) / int(gridDim.y) - first;
+    const int64_t row0 = L.brow[blockIdx.x] + first;   // of the step's active list
+    const int64_t q0 = row0 - pl->aoff[c];         // of the cluster's
+    const double *src = L.part + pl->poff[c];
+    const int sp = pl->split[c], ncomp = NV;
+    double *const d[6] = {st.d[0], st.d[1], st.d[2], st.d[3], st.d[4], st.d[5]};
+    const double *const fnew[4] = {f[0], f[3], NV > 6 ? f[6 % NV] : nullptr, NV > 9 ? f[9 % NV] : nullptr};
+    const int l = tid % kRedLanes;
+    for (int r0 = 0; r0 < cnt; r0 += kFinRows) {
+        const int rows = cnt - r0 < kFinRows ? cnt - r0 : kFinRows;
+        for (int r = tid / kRedLanes; r < rows; r += kBThreads / kRedLanes) {
+            const int64_t q = q0 + r0 + r;
+            double s[NV];
+#pragma unroll
+            for (int cc = 0; cc < NV; ++cc) s[cc] = 0.0;
+            for (int k = l; k < sp; k += kRedLanes)
+#pragma unroll
+                for (int cc = 0; cc < NV; ++cc) s[cc] += src[(int64_t(k) * ncomp + cc) * na + q];
+#pragma unroll
+            for (int m = kRedLanes / 2; m > 0; m >>= 1)
+#pragma unroll
+                for (int cc = 0; cc < NV; ++cc) s[cc] += __shfl_xor(s[cc], m, 64);
+            // lane l of the group stores component l
+#pragma unroll
+            for (int cc = 0; cc < NV; ++cc)
+                if (l == cc % kRedLanes) {
+                    f[cc][r] = s[cc];
+                    L.force[int64_t(cc) * L.n + row0 + r0 + r] = s[cc];
+                }
+        }
+        __syncthreads();
+        if (tid < rows) {
+            const int64_t i = L.act[row0 + r0 + tid];
+            const int fl = correct_one<P>(L.n, i, tn, fnew, kFinRows, tid, st.x, st.v, d, st.t_tick, st.level, eta, rule,
+                                          k_min, k_max);
+            if (fl & 2) atomicAdd(&L.ctr->underflow, 1ull);
+            if (fl & 1) atomicAdd(&L.ctr->nonfinite, 1ull);
+        }
+        __syncthreads();   // f is no longer read
     }
 }
 
@@ -786,24 +948,23 @@ hipError_t batch_cid(const BatchLaunch &L, hipStream_t s)
 
 hipError_t batch_schedule(const BatchLaunch &L, const nbody_state &st, int all_active, int order, hipStream_t s)
 {
-    const dim3 g(unsigned(L.nblk));   // the clusters' scheduling blocks, flat
-    hipLaunchKernelGGL(k_b_min, g, dim3(kBThreads), 0, s, L.off, st.t_tick, st.level, L.nb, L.blk, L.bmin, L.plan);
-    hipLaunchKernelGGL(k_b_count, g, dim3(kBThreads), 0, s, L.off, st.t_tick, st.level, L.nb, L.blk, L.bmin,
-                       all_active, L.plan, L.tnext, L.bcnt);
-    hipLaunchKernelGGL(k_b_plan, dim3(1), dim3(kBThreads), 0, s, L.nc, L.off, L.ord, L.tnext, L.plan,
-                       3 * (order / 2), L.k_items, L.itile, L.halves, L.grain, L.force_grid, L.ctr);
-    hipLaunchKernelGGL(k_b_compact, g, dim3(kBThreads), 0, s, L.off, st.t_tick, st.level, L.nb, L.blk, L.tnext,
-                       L.bcnt, all_active, L.plan, L.act);
+    hipLaunchKernelGGL(k_b_schedule, dim3(unsigned(L.nblk)), dim3(kBThreads), 0, s, L, st.t_tick, st.level, all_active,
+                       3 * (order / 2));
     return hipGetLastError();
 }
 
-hipError_t batch_predict(const BatchLaunch &L, const nbody_state &st, int order, int precision, void *rec,
+hipError_t batch_list_all(const BatchLaunch &L, const nbody_state &st, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_b_advance<4, -1>), dim3(unsigned(L.nblk)), dim3(kBThreads), 0, s, L, st, 1, nullptr);
+    return hipGetLastError();
+}
+
+hipError_t batch_advance(const BatchLaunch &L, const nbody_state &st, int order, int precision, void *rec,
                          hipStream_t s)
 {
-    const unsigned g = nblk(L.n, 256);
-#define NB_BP(P, PREC)                                                                                       \
-    hipLaunchKernelGGL((k_b_predict<P, PREC>), dim3(g), dim3(256), 0, s, L.n, L.cid, L.tnext, L.plan, st.m, st.x, st.v, \
-                       st.d[0], st.d[1], st.d[2], st.d[3], st.d[4], st.d[5], st.t_tick, rec)
+#define NB_BP(P, PREC) \
+    hipLaunchKernelGGL((k_b_advance<P, PREC>), dim3(unsigned(L.nblk), kBBlock / kBThreads), dim3(kBThreads), 0, s, L, st, \
+                       0, rec)
 #define NB_BP_P(P)                                          \
     if (precision == NBODY_FP64) NB_BP(P, NBODY_FP64);     \
     else NB_BP(P, NBODY_MIXED)
@@ -830,14 +991,15 @@ hipError_t batch_reduce(const BatchLaunch &L, int order, double *o0, double *o1,
     return reduce_p<8>(L, o0, o1, o2, o3, s);
 }
 
-hipError_t batch_correct(const BatchLaunch &L, const nbody_config &c, const nbody_state &st, hipStream_t s)
+hipError_t batch_finish(const BatchLaunch &L, const nbody_config &c, const nbody_state &st, hipStream_t s)
 {
-    const unsigned g0 = nblk(L.n, 256);
-    const unsigned g = g0 < kStrideGrid ? g0 : kStrideGrid;
-#define NB_BC(P)                                                                                              \
-    hipLaunchKernelGGL((k_b_correct<P>), dim3(g), dim3(256), 0, s, L.n, L.nc, L.act, L.cid, L.tnext, L.plan,     \
-                       st.x, st.v, st.d[0], st.d[1], st.d[2], st.d[3], st.d[4], st.d[5], st.t_tick, st.level,    \
-                       L.force, c.eta, dt_rule_of(c), int(c.k_min), int(c.k_max), L.ctr)
+    // workgroups per block: enough that a block of 1024 active rows is not one
+    // workgroup's 64 rounds of row sums, few enough that a large ensemble does
+    // not launch mostly empty ones
+    const unsigned y = L.nblk <= 512 ? 8u : (L.nblk <= 2048 ? 4u : 2u);
+#define NB_BC(P)                                                                                               \
+    hipLaunchKernelGGL((k_b_finish<P>), dim3(unsigned(L.nblk), y), dim3(kBThreads), 0, s, L, st, c.eta, dt_rule_of(c), \
+                       int(c.k_min), int(c.k_max))
     if (c.order == 4) NB_BC(4);
     else if (c.order == 6) NB_BC(6);
     else NB_BC(8);

@@ -17,7 +17,7 @@ using nb::fail;
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct BatchLayout {
-    size_t off, ord, cid, tnext, bmin, bcnt, blk, plan, nact, aoff, ioff, poff, jchunk, split, tcur, rank, ctr, act,
+    size_t off, ord, cid, tnext, bmin, bcnt, blk, brow, arrive, plan, nact, aoff, ioff, poff, jchunk, split, tcur, rank, ctr, act,
         part, force, rec, total;
 };
 
@@ -53,6 +53,8 @@ BatchLayout make_batch_layout(const nbody_config &c, const std::vector<int64_t> 
     L.bmin = take(cells * sizeof(int64_t));
     L.bcnt = take(cells * sizeof(int32_t));
     L.blk = take(2 * size_t(sched_blocks(off)) * sizeof(int32_t));
+    L.brow = take(size_t(sched_blocks(off)) * sizeof(int32_t));
+    L.arrive = take((2 * nc + 2) * sizeof(unsigned));   // one per cluster, per group of clusters, and one
     L.plan = take(sizeof(nb::BatchPlan));
     L.nact = take(nc * sizeof(int64_t));
     L.aoff = take((nc + 1) * sizeof(int64_t));
@@ -111,6 +113,11 @@ bool aligned8(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0
 // per lane: most of their steps have fewer items than the chip has waves.
 constexpr int64_t kHalfTilesBelow = int64_t(1) << 20;
 
+// Steps of the longer of the two captured graphs: the kernels of a graph follow
+// each other without a gap, graphs some 8 us apart (a step of a small ensemble
+// is some 40).
+constexpr int kGraphSteps = 8;
+
 struct nbody_batch {
     nbody_config cfg;
     int nc;
@@ -123,8 +130,8 @@ struct nbody_batch {
     nb::BatchLaunch L;
     int device;
     int force_grid_req;
-    hipGraph_t graph;
-    hipGraphExec_t exec;
+    hipGraph_t graph[2];       // one step, kGraphSteps steps
+    hipGraphExec_t exec[2];
 };
 
 namespace {
@@ -148,23 +155,43 @@ nbody_status enqueue_step(nbody_batch *b, const nbody_state &st)
 {
     const nbody_config &c = b->cfg;
     const nb::BatchLaunch &L = b->L;
-    double *F = L.force;
-    const int64_t n = c.n;
     void *rec = b->ws + b->lay.rec;
     NB_HIP(nb::batch_schedule(L, st, 0, c.order, b->stream));
-    NB_HIP(nb::batch_predict(L, st, c.order, c.precision, rec, b->stream));
+    NB_HIP(nb::batch_advance(L, st, c.order, c.precision, rec, b->stream));
     NB_HIP(nb::batch_force(L, c.order, c.precision, rec, b->stream));
-    NB_HIP(nb::batch_reduce(L, c.order, F, F + 3 * n, F + 6 * n, F + 9 * n, b->stream));
-    NB_HIP(nb::batch_correct(L, c, st, b->stream));
+    NB_HIP(nb::batch_finish(L, c, st, b->stream));
     return NBODY_OK;
 }
 
 void drop_graph(nbody_batch *b)
 {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
+    for (int k = 0; k < 2; ++k) {
+        if (b->exec[k]) (void)hipGraphExecDestroy(b->exec[k]);
+        if (b->graph[k]) (void)hipGraphDestroy(b->graph[k]);
+        b->exec[k] = nullptr;
+        b->graph[k] = nullptr;
+    }
+}
+
+// Graph k of `steps` steps.
+nbody_status capture_steps(nbody_batch *b, const nbody_state &st, int k, int steps)
+{
+    NB_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+    nbody_status s = NBODY_OK;
+    for (int r = 0; s == NBODY_OK && r < steps; ++r) s = enqueue_step(b, st);
+    hipGraph_t g = nullptr;
+    const hipError_t e = hipStreamEndCapture(b->stream, &g);
+    if (s != NBODY_OK || e != hipSuccess) {
+        if (g) (void)hipGraphDestroy(g);
+        return s != NBODY_OK ? s : fail(NBODY_E_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+    }
+    b->graph[k] = g;
+    const hipError_t e2 = hipGraphInstantiate(&b->exec[k], g, nullptr, nullptr, 0);
+    if (e2 != hipSuccess) {
+        b->exec[k] = nullptr;
+        return fail(NBODY_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e2));
+    }
+    return NBODY_OK;
 }
 
 nbody_status sync(nbody_batch *b)
@@ -209,8 +236,6 @@ nbody_status nbody_batch_create(const nbody_config *cfg, int32_t n_clusters, con
     b->stream = static_cast<hipStream_t>(stream);
     b->ws = static_cast<char *>(workspace);
     b->lay = lay;
-    b->graph = nullptr;
-    b->exec = nullptr;
     // clusters by decreasing size (ties by index): the largest work items first
     b->ord.resize(size_t(n_clusters));
     std::iota(b->ord.begin(), b->ord.end(), 0);
@@ -236,6 +261,8 @@ nbody_status nbody_batch_create(const nbody_config *cfg, int32_t n_clusters, con
     }
     L.nblk = int(b->blk.size() / 2);
     L.blk = at<int32_t>(b, lay.blk);
+    L.brow = at<int32_t>(b, lay.brow);
+    L.arrive = at<unsigned>(b, lay.arrive);
     L.plan = at<nb::BatchPlan>(b, lay.plan);
     L.ctr = at<nb::BatchCounters>(b, lay.ctr);
     L.act = at<int32_t>(b, lay.act);
@@ -273,6 +300,7 @@ nbody_status nbody_batch_create(const nbody_config *cfg, int32_t n_clusters, con
     if (e == hipSuccess) e = hipMemcpyAsync(const_cast<int32_t *>(L.blk), b->blk.data(), b->blk.size() * sizeof(int32_t),
                                             hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipMemsetAsync(L.ctr, 0, sizeof(nb::BatchCounters), b->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(L.arrive, 0, (2 * size_t(n_clusters) + 2) * sizeof(unsigned), b->stream);
     if (e == hipSuccess) e = hipMemsetAsync(hp.tcur, 0, size_t(n_clusters) * sizeof(int64_t), b->stream);
     if (e == hipSuccess) e = hipMemsetAsync(hp.aoff, 0, size_t(n_clusters + 1) * sizeof(int64_t), b->stream);
     if (e == hipSuccess) e = nb::batch_cid(L, b->stream);
@@ -303,6 +331,7 @@ nbody_status nbody_batch_init(nbody_batch *b, nbody_state *st)
     void *rec = b->ws + b->lay.rec;
     // every particle active at t = 0; the plan's partials hold the terms of order 8
     NB_HIP(nb::batch_schedule(L, *st, 1, 8, b->stream));
+    NB_HIP(nb::batch_list_all(L, *st, b->stream));
     // pass 1: acceleration and jerk from positions and velocities, the terms of order 4
     NB_HIP(nb::launch_pack_f64(c.n, st->m, st->x, st->v, nullptr, nullptr, rec, b->stream));
     NB_HIP(nb::batch_force(L, 4, NBODY_FP64, rec, b->stream));
@@ -350,30 +379,19 @@ nbody_status nbody_batch_capture(nbody_batch *b, nbody_state *st)
     if (s != NBODY_OK) return s;
     if (!b->stream) return fail(NBODY_E_UNSUPPORTED, "graph capture needs a stream other than the default stream");
     drop_graph(b);
-    NB_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    s = enqueue_step(b, *st);
-    hipGraph_t g = nullptr;
-    const hipError_t e = hipStreamEndCapture(b->stream, &g);
-    if (s != NBODY_OK || e != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
-        return s != NBODY_OK ? s : fail(NBODY_E_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    }
-    b->graph = g;
-    const hipError_t e2 = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
-    if (e2 != hipSuccess) {
-        b->exec = nullptr;
-        drop_graph(b);
-        return fail(NBODY_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e2));
-    }
-    return NBODY_OK;
+    s = capture_steps(b, *st, 0, 1);
+    if (s == NBODY_OK) s = capture_steps(b, *st, 1, kGraphSteps);
+    if (s != NBODY_OK) drop_graph(b);
+    return s;
 }
 
 nbody_status nbody_batch_replay(nbody_batch *b, int64_t k)
 {
     if (!b) return fail(NBODY_E_INVALID, "batch is NULL");
-    if (!b->exec) return fail(NBODY_E_STATE, "nbody_batch_replay before nbody_batch_capture");
+    if (!b->exec[0]) return fail(NBODY_E_STATE, "nbody_batch_replay before nbody_batch_capture");
     if (k < 0) return fail(NBODY_E_INVALID, "k must be >= 0");
-    for (int64_t r = 0; r < k; ++r) NB_HIP(hipGraphLaunch(b->exec, b->stream));
+    for (int64_t r = 0; r < k / kGraphSteps; ++r) NB_HIP(hipGraphLaunch(b->exec[1], b->stream));
+    for (int64_t r = 0; r < k % kGraphSteps; ++r) NB_HIP(hipGraphLaunch(b->exec[0], b->stream));
     return NBODY_OK;
 }
 
@@ -536,7 +554,7 @@ nbody_status nbody_batch_autotune(nbody_batch *b, nbody_state *st, int32_t steps
                 if (s == NBODY_OK && nb::batch_schedule(L, *st, 0, c.order, b->stream) != hipSuccess)
                     s = fail(NBODY_E_HIP, "schedule launch failed");
                 if (s == NBODY_OK && !predicted) {
-                    if (nb::batch_predict(L, *st, c.order, c.precision, rec, b->stream) != hipSuccess)
+                    if (nb::batch_advance(L, *st, c.order, c.precision, rec, b->stream) != hipSuccess)
                         s = fail(NBODY_E_HIP, "predictor launch failed");
                     predicted = true;
                 }

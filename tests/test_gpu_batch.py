@@ -126,6 +126,39 @@ def test_batch_force_all_active(order, precision):
             assert st["rms"] <= LOW_TOL[key] and st["max"] <= 10 * LOW_TOL[key], (key, st)
 
 
+@pytest.mark.parametrize("n_clusters", [1, 31, 33, 256, 257, 300])
+def test_batch_cluster_counts(n_clusters):
+    """Numbers of clusters around the arrival counters' groups (32) and the
+    plan's one cluster per thread (256): active sets and forces of three steps,
+    one of them with resting clusters (an end time between their next steps)."""
+    models = [nbody_ics.plummer(6 + (7 * c) % 50, 970 + c) for c in range(n_clusters - 1)]
+    models.append(nbody_ics.plummer(2100, 969))   # three scheduling blocks
+    B = _batch(models, 6, "fp64", n_hard=0)
+    B.init()
+    ocfg = _ocfg(B)
+    errs = {k: [] for k in KEYS}
+    for step in range(2):
+        h0 = B.to_numpy()
+        B.step(1)
+        aoff, act, f = B.last_step()
+        _force_errors(B, models, h0, aoff, act.cpu().numpy(), f.cpu().numpy(), ocfg, 6, errs)
+    for key in KEYS[:3]:
+        st = err_stats(np.concatenate(errs[key]))
+        assert st["rms"] <= 1e-12 and st["max"] <= 1e-9, (key, st)
+    h0 = B.to_numpy()
+    due = [_next(B.cluster(h0, c)) for c in range(B.nc)]
+    end = sorted(T for T, _ in due)[B.nc // 2]
+    B.set_end(end)
+    B.step(1)
+    aoff, act, _ = B.last_step()
+    act = act.cpu().numpy()
+    for c, (T, want) in enumerate(due):
+        np.testing.assert_array_equal(act[aoff[c]:aoff[c + 1]] - B.off[c], want if T <= end else want[:0])
+    live, tcur = B.poll()
+    assert live == sum(T <= end for T, _ in due)
+    assert all(t == T for (T, _), t in zip(due, tcur) if T <= end)
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_batch_large_ensemble(precision):
     """An ensemble of more than 2^20 particles, whose 64-row tiles are one item
@@ -271,6 +304,30 @@ def test_batch_graph_replay_matches_eager():
     np.testing.assert_array_equal(ha["x"], hg["x"])
     np.testing.assert_array_equal(ha["t_tick"], hg["t_tick"])
     assert A.stats().steps == G.stats().steps == 12
+
+
+def test_batch_long_replays_match_eager():
+    """Replays of 8 and more steps (a captured graph of eight steps, the rest
+    one by one) against as many eager steps, bit for bit, with eager work and
+    synchronisation between."""
+    models = _clusters(945)
+    A = _batch(models, 4, "mixed")
+    G = _batch(models, 4, "mixed")
+    A.init()
+    G.init()
+    G.capture()
+    done = 0
+    for k in (8, 19, 16, 3, 8):
+        A.step(k)
+        G.replay(k)
+        done += k
+        ha, hg = A.to_numpy(), G.to_numpy()
+        for key in ("x", "v", "t_tick", "level"):
+            np.testing.assert_array_equal(ha[key], hg[key], err_msg="after %d steps %s" % (done, key))
+        for d in range(2):
+            np.testing.assert_array_equal(ha["d"][d], hg["d"][d], err_msg="after %d steps d[%d]" % (done, d))
+        torch.cuda.synchronize()
+    assert A.stats().steps == G.stats().steps == done
 
 
 def test_batch_energy_parity():
