@@ -154,25 +154,41 @@ nbody_status read_scalars(nbody_ctx *ctx, nb::DevScalars *h)
 // step may still run).  The wait polls host memory and, every few thousand
 // polls, the stream: a stream error is returned, and a stream that finished
 // without the result (which should not happen) falls back to the copy.
+// A slot before its schedule is written.  (Slots are used again only kPubSlots
+// schedules later, more than a run has in flight.)
+void clear_published(nb::HostScalars *p)
+{
+    p->t_next = p->n_act = nb::kPubEmpty;
+    p->underflow = p->nonfinite = static_cast<unsigned long long>(nb::kPubEmpty);
+}
+
 nbody_status read_published(nbody_ctx *ctx, int64_t seq, nb::DevScalars *h)
 {
     if (!ctx->pub_host) return read_scalars(ctx, h);
-    const nb::HostScalars *p = ctx->pub_host + (seq & (nb::kPubSlots - 1));
+    nb::HostScalars *p = ctx->pub_host + (seq & (nb::kPubSlots - 1));
+    // The step kernel writes the words in no order: each is awaited, against the
+    // value that no schedule has (clear_published).
+    const auto arrived = [&] {
+        if (__atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) != seq) return false;
+        h->t_next = __atomic_load_n(&p->t_next, __ATOMIC_ACQUIRE);
+        h->n_act = __atomic_load_n(&p->n_act, __ATOMIC_ACQUIRE);
+        h->underflow = __atomic_load_n(&p->underflow, __ATOMIC_ACQUIRE);
+        h->nonfinite = __atomic_load_n(&p->nonfinite, __ATOMIC_ACQUIRE);
+        return h->t_next != nb::kPubEmpty && h->n_act != nb::kPubEmpty && int64_t(h->underflow) != nb::kPubEmpty &&
+               int64_t(h->nonfinite) != nb::kPubEmpty;
+    };
     unsigned spins = 0;
-    while (__atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) != seq) {
+    while (!arrived()) {
         if ((++spins & 4095u) == 0) {
             const hipError_t e = hipStreamQuery(ctx->stream);
             if (e == hipSuccess) {
-                if (__atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) == seq) break;
+                if (arrived()) break;
                 return read_scalars(ctx, h);
             }
             if (e != hipErrorNotReady) return fail(NBODY_E_HIP, "scheduler: %s", hipGetErrorString(e));
         }
     }
-    h->t_next = p->t_next;
-    h->n_act = p->n_act;
-    h->underflow = p->underflow;
-    h->nonfinite = p->nonfinite;
+    clear_published(p);
     h->seq = seq;
     return NBODY_OK;
 }
@@ -271,7 +287,10 @@ nbody_status nbody_create(const nbody_config *cfg, void *workspace, size_t bytes
     if (e == hipSuccess &&
         hipHostMalloc(reinterpret_cast<void **>(&ctx->pub_host), nb::kPubSlots * sizeof(nb::HostScalars),
                       hipHostMallocCoherent) == hipSuccess) {
-        for (int k = 0; k < nb::kPubSlots; ++k) ctx->pub_host[k].seq = 0;
+        for (int k = 0; k < nb::kPubSlots; ++k) {
+            ctx->pub_host[k].seq = 0;
+            clear_published(ctx->pub_host + k);
+        }
         if (hipHostGetDevicePointer(reinterpret_cast<void **>(&ctx->pub_dev), ctx->pub_host, 0) != hipSuccess) {
             (void)hipHostFree(ctx->pub_host);
             ctx->pub_host = nullptr;
@@ -828,7 +847,12 @@ nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t
         *n_act_out = n_act;
     }
     *steps_out = steps;
-    if (s == NBODY_OK) NB_HIP(hipStreamSynchronize(ctx->stream));
+    if (s == NBODY_OK) {
+        NB_HIP(hipStreamSynchronize(ctx->stream));
+    } else if (hipStreamSynchronize(ctx->stream) == hipSuccess) {
+        // schedules of steps in flight that were not read
+        for (int k = 0; k < nb::kPubSlots; ++k) clear_published(ctx->pub_host + k);
+    }
     return s;
 }
 

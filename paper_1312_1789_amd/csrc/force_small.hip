@@ -253,11 +253,13 @@ k_force_small(PredIn in, int64_t n, const int32_t *__restrict__ act, int64_t n_a
     Rec *tiles = reinterpret_cast<Rec *>(lds);
     double(*red)[kSlots] = reinterpret_cast<double(*)[kSlots]>(lds);
     if (dev) {
-        if (!small_step(*dev, tab, t_limit)) return;
+        int sp = tab.n_split[threadIdx.x & 63], jc = tab.j_chunk[threadIdx.x & 63];
+        asm volatile("" : "+v"(sp), "+v"(jc));   // in flight together with the scheduler's result
+        if (!small_step(*dev, sp, t_limit)) return;
         n_act = dev->n_act;
         in.t = dev->t_next;
-        n_split = tab.n_split[n_act - 1];
-        j_chunk = tab.j_chunk[n_act - 1];
+        n_split = of_lane(sp, n_act - 1);
+        j_chunk = of_lane(jc, n_act - 1);
     }
 #define NB_SMALL(CUT) small_run<CUT, Pol, P, PREC>(in, n, act, n_act, eps2, n_hard, j_chunk, n_split, dev != nullptr, \
                                                    o, part, tiles, red)

@@ -167,20 +167,56 @@ __device__ __forceinline__ double interp(int m, const double *Ps, const double *
     return s;
 }
 
-// Corrector + interpolation + new step of particle i, whose step ends at t1.
+// What the corrector reads of a particle's stored state.
+template <int P> struct HermiteState {
+    double x[3], v[3], A[P / 2][3];
+    int64_t t;
+    int level;
+};
+template <int P>
+__device__ __forceinline__ void load_state(HermiteState<P> &s, int64_t n, int64_t i, const double *x, const double *v,
+                                           double *const *d, int64_t t, int level)
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        s.x[c] = x[c * n + i];
+        s.v[c] = v[c * n + i];
+#pragma unroll
+        for (int k = 0; k < P / 2; ++k) s.A[k][c] = d[k][c * n + i];
+    }
+    s.t = t;
+    s.level = level;
+}
+
+// Corrector + interpolation + new step of particle i with stored state s,
+// whose step ends at t1.
 // fnew[k][stride * c + row] are the force derivatives a^(k) at t1 (k < p/2).
 // rule (orders 6, 8): 1 = generalised criterion of order P, 2 = its order-4
 // form, which reads only a .. a^(3).  Returns flags: bit 0 = a corrected
-// value is not finite, bit 1 = dt_crit fell below 2^-k_max.
-template <int P>
-__device__ __forceinline__ int correct_one(int64_t n, int64_t i, int64_t t1, const double *const *fnew,
-                                           int64_t stride, int64_t row, double *__restrict__ x,
-                                           double *__restrict__ v, double *const *dst,
-                                           int64_t *__restrict__ t_tick, int32_t *__restrict__ level, double eta,
-                                           int rule, int k_min, int k_max)
+// value is not finite, bit 1 = dt_crit fell below 2^-k_max.  level_new: the
+// new level.  POW2: the step is 2^-s.level exactly, so that dividing by its
+// powers and multiplying by those of 2^level are the same.
+template <int P, bool POW2>
+__device__ __forceinline__ int correct_state(const HermiteState<P> &s, int64_t n, int64_t i, int64_t t1,
+                                             const double *const *fnew, int64_t stride, int64_t row,
+                                             double *__restrict__ x, double *__restrict__ v, double *const *dst,
+                                             int64_t *__restrict__ t_tick, int32_t *__restrict__ level, double eta,
+                                             int rule, int k_min, int k_max, int *level_new)
 {
     constexpr int q = P / 2;
-    const double h = double(t1 - t_tick[i]) * (1.0 / double(kTicksPerUnit));
+    const double h = double(t1 - s.t) * (1.0 / double(kTicksPerUnit));
+    double inv[q];      // h^-(q+m)
+    if constexpr (POW2) {
+        const double r = __builtin_ldexp(1.0, s.level);
+        double rk = r;
+#pragma unroll
+        for (int k = 1; k < q; ++k) rk *= r;
+#pragma unroll
+        for (int m = 0; m < q; ++m) {
+            inv[m] = rk;
+            rk *= r;
+        }
+    }
     double all[P][3];   // a^(0..p-1) at t1
     double xn[3], vn[3];
     bool finite = true;
@@ -189,10 +225,10 @@ __device__ __forceinline__ int correct_one(int64_t n, int64_t i, int64_t t1, con
         double A0[q], A1[q];
 #pragma unroll
         for (int k = 0; k < q; ++k) {
-            A0[k] = dst[k][c * n + i];
+            A0[k] = s.A[k][c];
             A1[k] = fnew[k][c * stride + row];
         }
-        const double x0 = x[c * n + i], v0 = v[c * n + i];
+        const double x0 = s.x[c], v0 = s.v[c];
         // velocity: integral of the interpolant of a(t); position: the same
         // quadrature applied to v(t) with the corrected end velocity
         double v1, x1;
@@ -231,7 +267,8 @@ __device__ __forceinline__ int correct_one(int64_t n, int64_t i, int64_t t1, con
         }
 #pragma unroll
         for (int m = 0; m < q; ++m) {
-            all[q + m][c] = interp<P>(m, Ps, Qs) / hk;
+            if constexpr (POW2) all[q + m][c] = interp<P>(m, Ps, Qs) * inv[m];
+            else all[q + m][c] = interp<P>(m, Ps, Qs) / hk;
             hk *= h;
         }
     }
@@ -258,7 +295,7 @@ __device__ __forceinline__ int correct_one(int64_t n, int64_t i, int64_t t1, con
             dtc = (P == 6) ? eta * cbrt(a1 / ak) : eta * pow(a1 / ak, 0.2);
         }
     }
-    const int old = level[i];
+    const int old = s.level;
     int k = level_for(dtc, k_min, k_max);
     if (k < old) {
         const int kd = old - 1;
@@ -267,7 +304,22 @@ __device__ __forceinline__ int correct_one(int64_t n, int64_t i, int64_t t1, con
     }
     level[i] = k;
     t_tick[i] = t1;
+    *level_new = k;
     return (finite ? 0 : 1) | ((dtc >= ldexp(1.0, -k_max)) ? 0 : 2);
+}
+
+// The same from memory.
+template <int P>
+__device__ __forceinline__ int correct_one(int64_t n, int64_t i, int64_t t1, const double *const *fnew,
+                                           int64_t stride, int64_t row, double *__restrict__ x,
+                                           double *__restrict__ v, double *const *dst,
+                                           int64_t *__restrict__ t_tick, int32_t *__restrict__ level, double eta,
+                                           int rule, int k_min, int k_max)
+{
+    HermiteState<P> s;
+    load_state<P>(s, n, i, x, v, dst, t_tick[i], level[i]);
+    int k;
+    return correct_state<P, false>(s, n, i, t1, fnew, stride, row, x, v, dst, t_tick, level, eta, rule, k_min, k_max, &k);
 }
 
 }  // namespace

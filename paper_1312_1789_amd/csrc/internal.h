@@ -89,16 +89,23 @@ struct DevScalars {
 
 // Active sets that the small-step kernels take, and the split of each size
 // (n_split 0: not taken).
-constexpr int kSmallMax = 64;
+constexpr int kSmallMax = 64;   // a lane of a wave each
 struct SmallTable {
     int32_t n_split[kSmallMax];
     int32_t j_chunk[kSmallMax];
 };
 
-// Whether the step the scheduler found is one for the small-step kernels.
-__device__ __forceinline__ bool small_step(const DevScalars &d, const SmallTable &t, int64_t t_limit)
+// The value lane `lane` (uniform) holds.  (The small-step kernels load their table
+// into the lanes of a wave while the scheduler's result, its index, is in
+// flight: a launch's arguments are as far away as any memory.)
+__device__ __forceinline__ int of_lane(int v, int64_t lane) { return __builtin_amdgcn_readlane(v, int(lane)); }
+
+// Whether the step the scheduler found is one for the small-step kernels;
+// lane l holds n_split[l] of their table.
+__device__ __forceinline__ bool small_step(const DevScalars &d, int n_split, int64_t t_limit)
 {
-    return d.n_act >= 1 && d.n_act <= kSmallMax && d.t_next <= t_limit && !d.halt && t.n_split[d.n_act - 1] > 0;
+    const int64_t na = d.n_act;
+    return (na >= 1) & (na <= kSmallMax) & (d.t_next <= t_limit) & !d.halt & (of_lane(n_split, (na - 1) & 63) > 0);
 }
 
 // Lanes that share the sum of one output over n partials: each adds at most about 8.
@@ -273,11 +280,13 @@ hipError_t launch_unpack(int order, int precision, int64_t n, const void *rec, d
                          double *jp, hipStream_t s);
 
 // The scheduler's result for the host: written by the scheduler into
-// pinned, coherent host memory, the sequence number last, so that the host
-// can wait for it by polling instead of a copy and a stream synchronisation.
+// pinned, coherent host memory, so that the host can wait for it by polling
+// (all words written, see read_published) instead of a copy and a stream
+// synchronisation.
 // One slot per sequence number modulo kPubSlots (a run has a few steps in
 // flight).
 constexpr int kPubSlots = 8;
+constexpr int64_t kPubEmpty = INT64_MIN;   // a word not written yet: no time, count or counter has this value
 struct HostScalars {
     int64_t t_next;
     int64_t n_act;

@@ -16,11 +16,21 @@
 // The scheduler's result is also what the next small step's kernels read on the
 // device (DevScalars), so the host may enqueue them before it has seen it.
 //
-// A small step is then the force kernel and this one, 6 and 10 us at n = 1024,
-// 8 and 12 at n = 30000 (9 to 14 dependent memory round trips), with 1 to 2 us
-// between kernels: whole runs (n = 1024 FP64 order 4, t = 1/32) 7632 -> 4252 us,
-// (n = 30002 FP64 order 4 with a post-Newtonian binary, t = 1/128) 22202 -> 14532
-// us, (n = 80000 MIXED order 6, t = 1/512) 14861 -> 14297 us.
+// A small step is then the force kernel and this one, with 1 to 2 us between
+// kernels: whole runs (n = 1024 FP64 order 4, t = 1/32) 7632 -> 4252 us, (n = 30002
+// FP64 order 4 with a post-Newtonian binary, t = 1/128) 22202 -> 14532 us, (n =
+// 80000 MIXED order 6, t = 1/512) 14861 -> 14297 us.
+//
+// It is a chain of dependent round trips to memory, most of them to lines that
+// another XCD has written (about 1 us each), and of serial arithmetic on a few
+// lanes.  So all that a stage reads is loaded together with what decides whether
+// it is needed: the particles' times with the scheduler's result, the active
+// ones' state before their forces are summed, the first candidates of every
+// block with its time; least times and prefix sums are taken with moves between
+// lanes, the corrector multiplies by powers of two instead of dividing, and the
+// words for the host are stored without an order.  n = 1024: 7.2 -> 6.2 us, n =
+// 30002 with the binary 10.4 -> 9.2, n = 80000 10.8 -> 10.1; the runs 2620 -> 2390,
+// 13650 -> 12830, 15090 -> 14920 us (another realisation of the same sizes).
 #include <climits>
 
 #include "pn.h"
@@ -34,12 +44,11 @@ constexpr int kStepBlocks = int(kStepMaxN / kStepBlock);
 __device__ __forceinline__ int64_t next_of(int64_t t, int32_t level) { return t + (int64_t(1) << (kLevelMax - level)); }
 
 // Rank of this thread among the threads of the block with `flag`, in thread
-// order, and their number.  Synchronises the block twice.
+// order, and their number.  Synchronises the block once (wcnt is not used again).
 __device__ __forceinline__ int block_rank(bool flag, int *wcnt, int *total)
 {
     const int lane = int(threadIdx.x) & 63, w = int(threadIdx.x) >> 6;
     const unsigned long long m = __ballot(flag);
-    __syncthreads();   // wcnt is no longer read
     if (lane == 0) wcnt[w] = __popcll(m);
     __syncthreads();
     int before = __popcll(m & ((1ull << lane) - 1ull)), tot = 0;
@@ -51,18 +60,41 @@ __device__ __forceinline__ int block_rank(bool flag, int *wcnt, int *total)
     return before;
 }
 
-__device__ __forceinline__ int64_t block_min(int64_t v, int64_t *wm)
+// Wave-wide least value and inclusive sum by moves between lanes inside the VALU
+// (a quarter of the latency of cross-lane exchanges through the LDS unit).
+// Control words: shifts right by 1, 2, 4, 8 within rows of 16 lanes, then the
+// last lane of a row to the next row (rows 1 and 3), and lane 31 to rows 2 and 3.
+template <int CTRL, int ROWS> __device__ __forceinline__ int lane_move(int old, int v)
 {
-    for (int o = 32; o > 0; o >>= 1) {
-        const int64_t u = __shfl_xor(v, o, 64);
-        v = u < v ? u : v;
-    }
-    __syncthreads();   // wm is no longer read
-    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int64_t r = wm[0];
-    for (int k = 1; k < kSW; ++k) r = wm[k] < r ? wm[k] : r;
-    return r;
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ int64_t min_move(int64_t v)
+{
+    const int lo = int(uint32_t(uint64_t(v))), hi = int(v >> 32);
+    const int64_t u = int64_t(uint64_t(uint32_t(lane_move<CTRL, ROWS>(lo, lo))) |
+                              (uint64_t(uint32_t(lane_move<CTRL, ROWS>(hi, hi))) << 32));
+    return u < v ? u : v;
+}
+__device__ __forceinline__ int64_t wave_min(int64_t v)   // of all 64 lanes, to all
+{
+    v = min_move<0x111, 0xf>(v);
+    v = min_move<0x112, 0xf>(v);
+    v = min_move<0x114, 0xf>(v);
+    v = min_move<0x118, 0xf>(v);
+    v = min_move<0x142, 0xa>(v);
+    v = min_move<0x143, 0xc>(v);
+    const int lo = of_lane(int(uint32_t(uint64_t(v))), 63), hi = of_lane(int(v >> 32), 63);
+    return int64_t(uint64_t(uint32_t(lo)) | (uint64_t(uint32_t(hi)) << 32));
+}
+__device__ __forceinline__ int wave_sum_to(int v)   // inclusive, in lane order
+{
+    v += lane_move<0x111, 0xf>(0, v);
+    v += lane_move<0x112, 0xf>(0, v);
+    v += lane_move<0x114, 0xf>(0, v);
+    v += lane_move<0x118, 0xf>(0, v);
+    v += lane_move<0x142, 0xa>(0, v);
+    v += lane_move<0x143, 0xc>(0, v);
+    return v;
 }
 
 // Sums of the partial groups of rows [q0, q0 + cnt), in the order of k_reduce, to
@@ -110,69 +142,91 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // number, the published schedule, and the list when it is short enough.  PER
 // consecutive blocks per thread.
 template <int PER>
-__device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm, int *wcnt, int32_t *soff)
+__device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm, int *wcnt, int *wbig, int32_t *soff)
 {
     const int tid = int(threadIdx.x);
     const StepScratch &w = a.w;
     const int b0 = tid * PER;
+    // all that it reads, in flight together
+    DevScalars *sc = a.sc;
+    const unsigned long long nf = shared_load(&sc->nonfinite), uf = shared_load(&sc->underflow);
+    const unsigned long long nf0 = a.mode == kStepSchedule ? nf : sc->nonfinite0;
+    const int64_t seq = a.mode == kStepSchedule ? a.seq : sc->seq + 1;
     int64_t bt[PER];
     int bc[PER];
+    constexpr int kAhead = PER <= 4 ? 2 : 1;   // candidates of each block loaded with its time
+    int32_t c0[PER][kAhead];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int bb = b0 + k < nb ? b0 + k : nb - 1;
         bt[k] = shared_load(&w.blk[bb].t_next);
         bc[k] = int(shared_load(&w.blk[bb].count));
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) c0[k][u] = shared_load(&w.cand[int64_t(bb) * kStepBlock + u]);
     }
+    // each wave's least time, its active particles and their prefix; then the
+    // block's from the four waves'
     int64_t mn = INT64_MAX;
 #pragma unroll
     for (int k = 0; k < PER; ++k) mn = bt[k] < mn ? bt[k] : mn;   // (a repeated last block changes nothing)
-    const int64_t tn = block_min(mn, wm);
+    const int64_t wmin = wave_min(mn);
     int mine = 0;
+    bool more = false;   // a block with more candidates than are here
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        if (b0 + k >= nb || bt[k] != tn) bc[k] = 0;
+        if (b0 + k >= nb || bt[k] != wmin) bc[k] = 0;
         mine += bc[k];
+        more = more || bc[k] > kAhead;
     }
-    // exclusive prefix over the threads
     const int lane = tid & 63, wv = tid >> 6;
-    int incl = mine;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
+    const int incl = wave_sum_to(mine);
+    const bool wmore = __ballot(more) != 0;
+    if (lane == 63) {
+        wm[wv] = wmin;
+        wcnt[wv] = incl;
+        wbig[wv] = wmore ? 1 : 0;
     }
-    if (lane == 63) wcnt[wv] = incl;
     __syncthreads();
-    int off = incl - mine, total = 0;
+    int64_t tn = wm[0];
+    for (int k = 1; k < kSW; ++k) tn = wm[k] < tn ? wm[k] : tn;
+    int off = incl - mine, total = 0, search = 0;
     for (int k = 0; k < kSW; ++k) {
-        if (k < wv) off += wcnt[k];
-        total += wcnt[k];
+        const int c = wm[k] == tn ? wcnt[k] : 0;
+        if (k < wv) off += c;
+        total += c;
+        search |= wm[k] == tn ? wbig[k] : 0;
     }
-    if (tid == 0) {
-        DevScalars *sc = a.sc;
-        const unsigned long long nf = shared_load(&sc->nonfinite), uf = shared_load(&sc->underflow);
-        const int64_t seq = a.mode == kStepSchedule ? a.seq : sc->seq + 1;
+    if (wmin != tn)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) bc[k] = 0;
+    // the last wave publishes, without an order among the words: the host waits
+    // for each of them (read_published); the others go on to the list
+    if (tid == kStepBlock - 64) {
         HostScalars *pub = a.pub + (seq & (kPubSlots - 1));
         __hip_atomic_store(&pub->t_next, tn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&pub->n_act, int64_t(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&pub->underflow, uf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&pub->nonfinite, nf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        if (a.mode == kStepSchedule) sc->nonfinite0 = nf;
-        sc->halt = (a.mode == kStepSchedule || nf == sc->nonfinite0) ? 0 : 1;
+        __hip_atomic_store(&pub->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        sc->nonfinite0 = nf0;
+        sc->halt = nf == nf0 ? 0 : 1;
         sc->seq = seq;
         sc->t_next = tn;
         sc->n_act = total;
-        stores_done();
-        __hip_atomic_store(&pub->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k)
         if (b0 + k < nb) {
             soff[b0 + k] = off;
             w.boff[b0 + k] = off;
+            if (total <= kStepGather)
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+                    if (u < bc[k]) w.act[off + u] = c0[k][u];
             off += bc[k];
         }
+    if (total > kStepGather || !search) return;   // listed by k_step_gather, or already
     __syncthreads();
-    if (total > kStepGather) return;   // listed by k_step_gather
     for (int e = tid; e < total; e += kStepBlock) {
         // the block of entry e: the last one with soff <= e (blocks without
         // active particles share their successor's offset)
@@ -181,7 +235,7 @@ __device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm,
             const int mid = (lo + hi) / 2;
             if (soff[mid] <= e) lo = mid; else hi = mid;
         }
-        w.act[e] = shared_load(&w.cand[int64_t(lo) * kStepBlock + (e - soff[lo])]);
+        if (e - soff[lo] >= kAhead) w.act[e] = shared_load(&w.cand[int64_t(lo) * kStepBlock + (e - soff[lo])]);
     }
 }
 
@@ -192,33 +246,41 @@ k_step(StepArgs a)
     constexpr int NV = 3 * (P / 2);
     __shared__ double f[NV][kSmallMax];
     __shared__ int64_t wm[kSW];
-    __shared__ int wcnt[kSW];
+    __shared__ int wcnt[kSW], wbig[kSW], wact[kSW];
     __shared__ int32_t soff[kStepBlocks];
     __shared__ int s_last;
     const int64_t n = a.cfg.n;
     const int b = int(blockIdx.x), nb = int(gridDim.x), tid = int(threadIdx.x);
     const int64_t i = int64_t(b) * kStepBlock + tid;
-    if (a.mode == kStepSmall && !small_step(*a.sc, a.tab, a.t_limit)) return;
     int64_t *t_tick = a.st.t_tick;
     int32_t *level = a.st.level;
-    int64_t next = i < n ? next_of(t_tick[i], level[i]) : INT64_MAX;
+    int64_t t0 = i < n ? t_tick[i] : 0;
+    int l0 = i < n ? level[i] : 0;
+    int q0 = a.w.boff[b];   // of the step to end
+    int sp = a.tab.n_split[tid & 63];
+    asm volatile("" : "+v"(t0), "+v"(l0), "+v"(q0), "+v"(sp));   // in flight together with what the next line reads
+    if (a.mode == kStepSmall && !small_step(*a.sc, sp, a.t_limit)) return;
+    int64_t next = i < n ? next_of(t0, l0) : INT64_MAX;
     if (a.mode != kStepSchedule) {
         const int64_t na = a.sc->n_act, tn = a.sc->t_next;
         const bool active = i < n && next == tn;
+        double *x = a.st.x, *v = a.st.v;
+        double *const d[6] = {a.st.d[0], a.st.d[1], a.st.d[2], a.st.d[3], a.st.d[4], a.st.d[5]};
+        HermiteState<P> s0;
+        if (active) load_state<P>(s0, n, i, x, v, d, t0, l0);   // in flight while the partial forces are summed
         int cnt = 0;
-        const int rank = block_rank(active, wcnt, &cnt);
+        const int rank = block_rank(active, wact, &cnt);
         if (cnt > 0) {   // uniform over the block
-            const int64_t q0 = a.w.boff[b];
             double *fp[4];
             int64_t stride, row;
             if (a.mode == kStepSmall) {
                 const int gs = na <= 16 ? 8 : (na <= 32 ? 4 : 2);   // small_group
-                const int ng = (a.tab.n_split[na - 1] + gs - 1) / gs;
+                const int ng = (of_lane(sp, na - 1) + gs - 1) / gs;
                 const int L = reduce_lanes(ng);
-                if (L == 1) sum_rows<1, NV>(a.part, na, ng, int(q0), cnt, f);
-                else if (L == 4) sum_rows<4, NV>(a.part, na, ng, int(q0), cnt, f);
-                else if (L == 16) sum_rows<16, NV>(a.part, na, ng, int(q0), cnt, f);
-                else sum_rows<64, NV>(a.part, na, ng, int(q0), cnt, f);
+                if (L == 1) sum_rows<1, NV>(a.part, na, ng, q0, cnt, f);
+                else if (L == 4) sum_rows<4, NV>(a.part, na, ng, q0, cnt, f);
+                else if (L == 16) sum_rows<16, NV>(a.part, na, ng, q0, cnt, f);
+                else sum_rows<64, NV>(a.part, na, ng, q0, cnt, f);
                 __syncthreads();
                 stride = kSmallMax;
                 row = rank;
@@ -226,12 +288,10 @@ k_step(StepArgs a)
                 for (int k = 0; k < 4; ++k) fp[k] = k < P / 2 ? f[3 * k] : nullptr;
             } else {
                 stride = na;
-                row = q0 + rank;
+                row = int64_t(q0) + rank;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) fp[k] = a.f[k];
             }
-            double *x = a.st.x, *v = a.st.v;
-            double *const d[6] = {a.st.d[0], a.st.d[1], a.st.d[2], a.st.d[3], a.st.d[4], a.st.d[5]};
             if constexpr (PN) {
                 // the hard particles are all in the first block: their terms from
                 // the stored state, before any of them is corrected
@@ -251,18 +311,32 @@ k_step(StepArgs a)
             }
             if (active) {
                 const double *const fnew[4] = {fp[0], fp[1], fp[2], fp[3]};
-                const int fl = correct_one<P>(n, i, tn, fnew, stride, row, x, v, d, t_tick, level, a.cfg.eta,
-                                              a.rule, int(a.cfg.k_min), int(a.cfg.k_max));
+                int l1;
+                const int fl = correct_state<P, true>(s0, n, i, tn, fnew, stride, row, x, v, d, t_tick, level, a.cfg.eta,
+                                                      a.rule, int(a.cfg.k_min), int(a.cfg.k_max), &l1);
                 if (fl & 2) atomicAdd(&a.sc->underflow, 1ull);
                 if (fl & 1) atomicAdd(&a.sc->nonfinite, 1ull);
-                next = next_of(t_tick[i], level[i]);
+                next = next_of(tn, l1);
             }
         }
     }
     // the block's next time, and its particles at it in increasing order
-    const int64_t bm = block_min(next, wm);
-    int cnt = 0;
-    const int rank = block_rank(i < n && next == bm, wcnt, &cnt);
+    const int64_t wmin = wave_min(next);
+    const int lane = tid & 63, wv = tid >> 6;
+    const unsigned long long at = __ballot(i < n && next == wmin);
+    if (lane == 0) {
+        wm[wv] = wmin;
+        wcnt[wv] = __popcll(at);
+    }
+    __syncthreads();
+    int64_t bm = wm[0];
+    for (int k = 1; k < kSW; ++k) bm = wm[k] < bm ? wm[k] : bm;
+    int cnt = 0, rank = __popcll(at & ((1ull << lane) - 1ull));
+    for (int k = 0; k < kSW; ++k) {
+        const int c = wm[k] == bm ? wcnt[k] : 0;
+        if (k < wv) rank += c;
+        cnt += c;
+    }
     if (i < n && next == bm) shared_store(&a.w.cand[int64_t(b) * kStepBlock + rank], int32_t(i));
     if (tid == 0) {
         shared_store(&a.w.blk[b].t_next, bm);
@@ -286,9 +360,9 @@ k_step(StepArgs a)
     }
     __syncthreads();
     if (!s_last) return;
-    if (nb <= kStepBlock) schedule<1>(a, nb, wm, wcnt, soff);
-    else if (nb <= 4 * kStepBlock) schedule<4>(a, nb, wm, wcnt, soff);
-    else schedule<kStepBlocks / kStepBlock>(a, nb, wm, wcnt, soff);
+    if (nb <= kStepBlock) schedule<1>(a, nb, wm, wcnt, wbig, soff);
+    else if (nb <= 4 * kStepBlock) schedule<4>(a, nb, wm, wcnt, wbig, soff);
+    else schedule<kStepBlocks / kStepBlock>(a, nb, wm, wcnt, wbig, soff);
 }
 
 __global__ void __launch_bounds__(kStepBlock)

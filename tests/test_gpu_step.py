@@ -91,6 +91,30 @@ def test_synchronised_blocks_are_listed():
     _compare(a, b)
 
 
+# the first candidates of a block come with its time (two, or one when a thread
+# has sixteen blocks), those beyond are searched for
+@pytest.mark.parametrize("n", [900, 70001, (1 << 18) + 300])
+@pytest.mark.parametrize("most", [1, 2, 3, 9])
+def test_active_sets_by_block(n, most):
+    """Up to `most` due particles in each of a few blocks, the last one among
+    them."""
+    model = nbody_ics.plummer(n, 2350 + most)
+    a, b = _sim(model), _sim(model)
+    b.set_timing(True)
+    lv = torch.full((n,), 5, dtype=torch.int32)
+    due = 0
+    for k, base in enumerate([0, 256, 768 if n > 1024 else 512, (n - 1) // 256 * 256]):
+        cnt = min(most if k % 2 == 0 else 1, n - base)
+        lv[base:base + 3 * cnt:3] = 14
+        due = int((lv == 14).sum())
+    for sim in (a, b):
+        sim.level.copy_(lv.to(sim.device))
+    assert a.step() == b.step() == (TICKS >> 14, due)
+    for _ in range(3):
+        assert a.step() == b.step()
+    _compare(a, b)
+
+
 @pytest.mark.parametrize("n_hard", [2, 255, 257])
 def test_post_newtonian_steps(n_hard):
     """Post-Newtonian terms added by the step kernel (up to 256 hard
