@@ -183,6 +183,9 @@ k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *
 // neighbour lists one after the other (increasing j, at most max_nb entries);
 // then lane l adds the irregular terms of list entries l, l + 64, ... and the
 // lanes' sums are folded with a fixed butterfly.
+// Bound by the latency of its dependent loads (one wave per row, a wave or two per
+// SIMD): with the loads of all splits and of the lists' first entries in flight
+// together 14.9 us at 342 splits of 1024 rows instead of 22.7.
 template <class Pol>
 __global__ void __launch_bounds__(64)
 k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
@@ -197,18 +200,7 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
     const int l = int(threadIdx.x);
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-        // the loads of eight of this lane's splits in flight together, added in split order
-        const double *src = part + (int64_t(c) * n_act + q) * n_split;
-        double s = 0.0;
-        int sp = l;
-        for (; sp + 7 * 64 < n_split; sp += 8 * 64) {
-            double v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = src[sp + u * 64];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
-        }
-        for (; sp < n_split; sp += 64) s += src[sp];
+        double s = lane_sum<64>(part + (int64_t(c) * n_act + q) * n_split, l, n_split, 1);
 #pragma unroll
         for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
         if (l == 0) (c < 3 ? acc_reg : jrk_reg)[(c % 3) * n_act + q] = s;
@@ -216,12 +208,13 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
     // the lists: 64 splits at a time, lane l taking split s0 + l; a prefix sum
     // over the lanes places each split's entries after those of the splits
     // before it, and at most max_nb entries are kept in all.  The counts of
-    // up to kNbPass passes are loaded together first (one memory round trip
-    // for them instead of one per pass).
+    // up to kNbPass passes are loaded together first, then the first entries of
+    // the lists that have one (most have none or one): two memory round trips for
+    // them instead of two per pass.
     constexpr int kNbPass = 16;
     int64_t total = 0;
     int written = 0;
-    int cnts[kNbPass];
+    int cnts[kNbPass], firsts[kNbPass];
     for (int s0 = 0; s0 < n_split; s0 += 64) {
         const int pass = (s0 / 64) % kNbPass;
         if (pass == 0) {
@@ -230,11 +223,19 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
                 const int spk = s0 + 64 * k + l;
                 cnts[k] = spk < n_split ? seg_cnt[q * n_split + spk] : 0;
             }
+#pragma unroll
+            for (int k = 0; k < kNbPass; ++k) {
+                const int spk = s0 + 64 * k + l;
+                firsts[k] = cnts[k] > 0 && max_nb > 0 ? seg[(int64_t(spk) * n_act + q) * max_nb] : 0;
+            }
         }
         const int sp = s0 + l;
-        int c = 0;
+        int c = 0, first = 0;
 #pragma unroll
-        for (int k = 0; k < kNbPass; ++k) c = k == pass ? cnts[k] : c;
+        for (int k = 0; k < kNbPass; ++k) {
+            c = k == pass ? cnts[k] : c;
+            first = k == pass ? firsts[k] : first;
+        }
         const int stored = c < max_nb ? c : max_nb;
         int incl = stored;
 #pragma unroll
@@ -246,7 +247,8 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
         const int room = max_nb - base;
         const int take = room <= 0 ? 0 : (stored < room ? stored : room);
         const int32_t *src = seg + (int64_t(sp < n_split ? sp : 0) * n_act + q) * max_nb;
-        for (int k = 0; k < take; ++k) nb_list[q * max_nb + base + k] = src[k];
+        if (take > 0) nb_list[q * max_nb + base] = first;
+        for (int k = 1; k < take; ++k) nb_list[q * max_nb + base + k] = src[k];
         const int all = __shfl(incl, 63, 64);
         written = written + all < max_nb ? written + all : max_nb;
         int64_t cs = c;

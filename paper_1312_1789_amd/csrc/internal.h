@@ -111,6 +111,24 @@ __device__ __forceinline__ bool small_step(const DevScalars &d, int n_split, int
 // Lanes that share the sum of one output over n partials: each adds at most about 8.
 __host__ __device__ constexpr int reduce_lanes(int n) { return n <= 8 ? 1 : n <= 32 ? 4 : n <= 128 ? 16 : 64; }
 
+// Lane l of the L that share a sum over n partials: src[k * step], k = l, l + L, ...,
+// added in order, eight loads in flight together (one memory round trip for
+// all of them, also where fewer are left; the zeros in their place change
+// nothing).
+template <int L>
+__device__ __forceinline__ double lane_sum(const double *__restrict__ src, int l, int n, int64_t step)
+{
+    double s = 0.0;
+    for (int k = l; k < n; k += 8 * L) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = k + u * L < n ? src[int64_t(k + u * L) * step] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    return s;
+}
+
 // Force launch request.
 struct ForceArgs {
     const void *rec;        // predicted records

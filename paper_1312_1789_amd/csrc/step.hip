@@ -98,29 +98,48 @@ __device__ __forceinline__ int wave_sum_to(int v)   // inclusive, in lane order
 }
 
 // Sums of the partial groups of rows [q0, q0 + cnt), in the order of k_reduce, to
-// f[component][row].
+// f[component][row].  Every load of up to three passes over the outputs is in
+// flight before the first sum (k_step at n = 80000 order 6, 64 lanes an output: 10.1
+// -> 9.0 us; with the ends of the sums one load after another it had been up to
+// twelve round trips).
 template <int L, int NV>
 __device__ __forceinline__ void sum_rows(const double *__restrict__ part, int64_t na, int ng, int q0, int cnt,
                                          double (*f)[kSmallMax])
 {
+    // outputs a pass, and passes in flight together (short sums have enough outputs to a pass)
+    constexpr int G = kStepBlock / L, E = L >= 16 ? 3 : 1;
     const int l = int(threadIdx.x) % L;
-    for (int e = int(threadIdx.x) / L; e < cnt * NV; e += kStepBlock / L) {
-        const int c = e / cnt, row = e - c * cnt;
-        const double *src = part + (int64_t(c) * na + q0 + row) * ng;
-        double s = 0.0;
-        int k = l;
-        for (; k + 7 * L < ng; k += 8 * L) {
-            double v[8];
+    for (int e0 = int(threadIdx.x) / L; e0 < cnt * NV; e0 += G * E) {
+        // (the last output again where there are fewer)
+        const double *src[E];
+        int c[E], row[E];
+        double s[E];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = src[k + u * L];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+        for (int x = 0; x < E; ++x) {
+            const int e = e0 + x * G < cnt * NV ? e0 + x * G : cnt * NV - 1;
+            c[x] = e / cnt, row[x] = e - c[x] * cnt;
+            src[x] = part + (int64_t(c[x]) * na + q0 + row[x]) * ng;
+            s[x] = 0.0;
         }
-        for (; k < ng; k += L) s += src[k];
-        // the lanes of a group share e, so their partners run the same iterations
+        for (int k = l; k < ng; k += 8 * L) {
+            double v[E][8];
 #pragma unroll
-        for (int m = L / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
-        if (l == 0) f[c][row] = s;
+            for (int x = 0; x < E; ++x)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[x][u] = k + u * L < ng ? src[x][k + u * L] : 0.0;
+#pragma unroll
+            for (int x = 0; x < E; ++x)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s[x] += v[x][u];
+        }
+        // the lanes of a group share e0, so their partners run the same iterations
+#pragma unroll
+        for (int m = L / 2; m > 0; m >>= 1)
+#pragma unroll
+            for (int x = 0; x < E; ++x) s[x] += __shfl_xor(s[x], m, 64);
+        if (l == 0)
+#pragma unroll
+            for (int x = 0; x < E; ++x) f[c[x]][row[x]] = s[x];
     }
 }
 
