@@ -575,7 +575,7 @@ nbody_status nbody_force_block_nb(nbody_ctx *ctx, int64_t n_act, const int32_t *
     if (max_nb > 0 && (!nb_list || (reinterpret_cast<uintptr_t>(nb_list) & 3u)))
         return fail(NBODY_E_INVALID, "nb_list must be non-NULL, 4-byte aligned when max_nb > 0");
     const int64_t scratch = nb::part_rows_for(c.n) * nb::kMaxComp * int64_t(sizeof(double));
-    const int sp = nb::nb_split(c.n, n_act, max_nb, scratch, 0);
+    const int sp = nb::nb_split(c.precision, c.n, n_act, max_nb, scratch);
     if (sp < 1)
         return fail(NBODY_E_INVALID, "n_act * (13 + max_nb) = %lld exceeds the scratch (%lld); call with fewer rows",
                     (long long)(n_act * (13 + int64_t(max_nb))), (long long)(scratch / 4));
@@ -595,8 +595,7 @@ nbody_status nbody_force_block_nb(nbody_ctx *ctx, int64_t n_act, const int32_t *
     a.jrk_reg = jrk_reg;
     a.nb_count = nb_count;
     a.nb_list = nb_list;
-    int used = 0;
-    NB_HIP(nb::launch_force_nb(c.precision, a, sp, ctx->stream, &used));
+    NB_HIP(nb::launch_force_nb(c.precision, a, sp, ctx->stream));
     ctx->stats.interactions += double(n_act) * double(c.n);
     return NBODY_OK;
 }

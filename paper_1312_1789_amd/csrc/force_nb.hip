@@ -17,10 +17,19 @@
 // the non-neighbours (the neighbours are masked out of the same FMA sequence
 // as the full force) and appending the neighbours to its split's part of the
 // list.  The j below n_hard (unsoftened when i is hard too) are taken one by
-// one with their checks; the rest streams through LDS tiles of kNbBlock
-// records with no per-pair index test: the self pair (difference zero, r^2 =
-// eps^2 > 0) either is a neighbour, and is dropped at the append, or adds
-// exact zeros to the regular part.  Kernel 2, one wave per
+// one with their checks; the rest streams through double-buffered LDS tiles of
+// kNbTile records with no per-pair index test: the self pair (difference zero,
+// r^2 = eps^2 > 0) either is a neighbour, and is dropped at the append, or adds
+// exact zeros to the regular part.  Bound by VALU issue (3.7 cycles an
+// instruction with 342 splits, 5.3 waves to a SIMD; 3.2 with 1024), so: one wave
+// to a workgroup with tiles of 32, which leaves six waves (MIXED) or five (FP64)
+// to a SIMD (tiles of 64 left four); neighbours, rare in a wave, are masked and noted under one wave-wide
+// test of two pairs, and their list entries are written after the tile; entries
+// of two bytes (offsets in the split) where a split is short enough, so that the
+// scratch holds more splits.  The call at n = 131072, 1024 rows, lists of 128, MIXED
+// 167 -> 152 us (512 splits instead of 342), n = 262144, 2048 rows MIXED 510 -> 475, FP64
+// 716 -> 670, n = 8192, 64 rows MIXED 38 -> 32; n = 20000, 700 rows MIXED 46 -> 49.  One
+// scalar load of each record by the wave instead of LDS tiles: 206 us.  Kernel 2, one wave per
 // row: the regular partial sums added in split order, the split lists
 // concatenated, and the irregular part summed over the list (lanes take
 // every 64th entry, then a fixed butterfly).  A row whose list was cut at
@@ -30,7 +39,11 @@
 namespace nb {
 namespace {
 
-constexpr int kNbBlock = 128;
+constexpr int kNbBlock = 64;
+constexpr int kNbChunk = 128;   // j of one FP32 sum
+constexpr int kNbTile = 32;     // j of one LDS tile, a bit each in a lane's word of neighbours
+constexpr int kNbGroup = 2;     // j of one test for neighbours
+constexpr int64_t kShortChunk = 65536;   // j of a split whose list entries take two bytes, at most
 
 // One pair of the regular sum: the differences, the softened r^2 + eps_ij^2,
 // the neighbour test r^2 + eps_ij^2 < h^2 + eps_ij^2 (the unsoftened test,
@@ -51,37 +64,42 @@ __device__ __forceinline__ bool nb_pair(const typename PolF64<4, false>::I &i, c
     return is_nb;
 }
 
-// The pair of the LDS-tile loop: softened (eps2 > 0, so r^2 > 0), no
-// validity test (the self pair is handled as stated above).
-__device__ __forceinline__ bool nb_pair_soft(const typename PolF64<4, false>::I &i, const RecF64<4> &j, double e2,
-                                             double hh_e, double *A)
-{
-    const double dx = j.x - i.x, dy = j.y - i.y, dz = j.z - i.z;
-    const double wx = j.vx - i.vx, wy = j.vy - i.vy, wz = j.vz - i.vz;
-    const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, e2)));
-    const bool is_nb = r2 < hh_e;
-    const double rinv = rsqrt64(r2);
-    const double mr = is_nb ? 0.0 : j.m * rinv;
-    core_fma<4, false, double>(dx, dy, dz, wx, wy, wz, 0, 0, 0, 0, 0, 0, mr, rinv * rinv, A);
-    return is_nb;
-}
-
-__device__ __forceinline__ bool nb_pair_soft(const typename DSIn<4>::I &i, const RecDS<4> &j, float e2, float hh_e,
-                                             float *A)
-{
-    const float dx = (j.xh - i.xh) + (j.xl - i.xl);
-    const float dy = (j.yh - i.yh) + (j.yl - i.yl);
-    const float dz = (j.zh - i.zh) + (j.zl - i.zl);
-    const float wx = (j.vxh - i.vxh) + (j.vxl - i.vxl);
-    const float wy = (j.vyh - i.vyh) + (j.vyl - i.vyl);
-    const float wz = (j.vzh - i.vzh) + (j.vzl - i.vzl);
-    const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, __builtin_fmaf(dz, dz, e2)));
-    const bool is_nb = r2 < hh_e;
-    const float rinv = __builtin_amdgcn_rsqf(r2);
-    const float mr = is_nb ? 0.0f : j.m * rinv;
-    core_fma<4, false, float>(dx, dy, dz, wx, wy, wz, 0, 0, 0, 0, 0, 0, mr, rinv * rinv, A);
-    return is_nb;
-}
+// A pair of the LDS-tile loop: softened (eps2 > 0, so r^2 > 0), no validity
+// test (the self pair is handled as stated above).  set() forms all that the
+// neighbour test and the sums need; add() adds the order-4 terms of mr = m / r
+// (zeroed by the caller for a neighbour).
+template <class T> struct SoftPair {
+    T dx, dy, dz, wx, wy, wz, mr, rinv2;
+    bool is_nb;
+    __device__ __forceinline__ void finish(T r2, T rinv, T m, T hh_e)
+    {
+        is_nb = r2 < hh_e;
+        mr = m * rinv;
+        rinv2 = rinv * rinv;
+    }
+    __device__ __forceinline__ void set(const typename PolF64<4, false>::I &i, const RecF64<4> &j, double e2, double hh_e)
+    {
+        dx = j.x - i.x, dy = j.y - i.y, dz = j.z - i.z;
+        wx = j.vx - i.vx, wy = j.vy - i.vy, wz = j.vz - i.vz;
+        const double r2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, e2)));
+        finish(r2, rsqrt64(r2), j.m, hh_e);
+    }
+    __device__ __forceinline__ void set(const typename DSIn<4>::I &i, const RecDS<4> &j, float e2, float hh_e)
+    {
+        dx = (j.xh - i.xh) + (j.xl - i.xl);
+        dy = (j.yh - i.yh) + (j.yl - i.yl);
+        dz = (j.zh - i.zh) + (j.zl - i.zl);
+        wx = (j.vxh - i.vxh) + (j.vxl - i.vxl);
+        wy = (j.vyh - i.vyh) + (j.vyl - i.vyl);
+        wz = (j.vzh - i.vzh) + (j.vzl - i.vzl);
+        const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, __builtin_fmaf(dz, dz, e2)));
+        finish(r2, __builtin_amdgcn_rsqf(r2), j.m, hh_e);
+    }
+    __device__ __forceinline__ void add(T *A) const
+    {
+        core_fma<4, false, T>(dx, dy, dz, wx, wy, wz, 0, 0, 0, 0, 0, 0, mr, rinv2, A);
+    }
+};
 
 __device__ __forceinline__ bool nb_pair(const typename DSIn<4>::I &i, const RecDS<4> &j, float el, float hh_e,
                                         bool valid, float *A)
@@ -101,11 +119,12 @@ __device__ __forceinline__ bool nb_pair(const typename DSIn<4>::I &i, const RecD
     return is_nb;
 }
 
-template <class Pol>
-__global__ void __launch_bounds__(kNbBlock)
+// SegT: the type of a list entry, j minus the split's first j.
+template <class Pol, class SegT>
+__global__ void __launch_bounds__(kNbBlock, Pol::kChunk ? 6 : 5)
 k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
            const double *__restrict__ h2, double eps2, int64_t n_hard, int64_t j_chunk, int max_nb,
-           double *__restrict__ part, int32_t *__restrict__ seg_cnt, int32_t *__restrict__ seg)
+           double *__restrict__ part, int32_t *__restrict__ seg_cnt, SegT *__restrict__ seg)
 {
     using Rec = typename Pol::Rec;
     using ET = typename Pol::ET;
@@ -129,9 +148,9 @@ k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *
         acc[c] = 0.0;
         zero_part(p[c]);
     }
-    static_assert(Pol::kChunk == 0 || Pol::kChunk == kNbBlock, "one FP32 chunk per tile");
+    static_assert(Pol::kChunk == 0 || Pol::kChunk == kNbChunk, "the FP32 chunk");
     int cnt = 0;
-    int32_t *my_seg = seg + (int64_t(split) * n_act + qq) * max_nb;
+    SegT *my_seg = seg + (int64_t(split) * n_act + qq) * max_nb;
     // j below n_hard: each pair's terms added into FP64 on their own
     const int64_t jh1 = j1 < n_hard ? j1 : n_hard;
     for (int64_t j = j0; j < jh1; ++j) {
@@ -141,34 +160,81 @@ k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *
         for (int c = 0; c < 13; ++c) zero_part(ph[c]);
         const bool is_nb = nb_pair(ip, rj, i_hard ? ET(0) : e2, i_hard ? hh_0 : hh_e, j != i, ph);
         if (is_nb) {
-            if (row && cnt < max_nb) my_seg[cnt] = int32_t(j);
+            if (row && cnt < max_nb) my_seg[cnt] = SegT(j - j0);
             ++cnt;
         }
 #pragma unroll
         for (int c = 0; c < 6; ++c) acc[c] += to_double(ph[c]);
     }
-    // the rest (softened pairs) through LDS tiles; the FP32 sums are flushed
-    // after every tile (one chunk)
-    __shared__ Rec tile[kNbBlock];
+    // the rest (softened pairs) through double-buffered LDS tiles; the FP32 sums
+    // are flushed after every chunk
+    constexpr int PIECES = int(sizeof(Rec) / 16) * kNbTile / kNbBlock;   // 16-byte pieces a lane moves per tile
+    typedef uint4 __attribute__((may_alias)) piece_t;
+    __shared__ Rec tile[2][kNbTile];
     const int64_t js0 = j0 > n_hard ? j0 : n_hard;
-    for (int64_t jt = js0; jt < j1; jt += kNbBlock) {
-        const int64_t jl = jt + threadIdx.x;
-        if (jl < j1) tile[threadIdx.x] = rec[jl];
+    const int left0 = int(j1 - js0);   // at most one split
+    const piece_t *src = reinterpret_cast<const piece_t *>(rec + js0) + threadIdx.x;
+    const int64_t last = int64_t(left0) * int(sizeof(Rec) / 16) - 1 - int(threadIdx.x);   // of src's pieces
+    piece_t pre[PIECES];
+#pragma unroll
+    for (int k = 0; k < PIECES; ++k) pre[k] = piece_t{0u, 0u, 0u, 0u};
+    if (left0 > 0)
+#pragma unroll
+        for (int k = 0; k < PIECES; ++k)
+            if (k * kNbBlock <= last) pre[k] = src[k * kNbBlock];
+    const int self = int(i - js0);   // |i - js0| < 2^26
+    int buf = 0;
+    for (int t = 0; t < left0; t += kNbTile) {
+        piece_t *dst = reinterpret_cast<piece_t *>(tile[buf]) + threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < PIECES; ++k) dst[k * kNbBlock] = pre[k];
         __syncthreads();
-        const int m = j1 - jt < kNbBlock ? int(j1 - jt) : kNbBlock;
-        for (int u = 0; u < m; ++u) {
-            const Rec rj = tile[u];
-            if (nb_pair_soft(ip, rj, e2, hh_e, p)) {
-                const int64_t j = jt + u;
-                if (j != i) {
-                    if (row && cnt < max_nb) my_seg[cnt] = int32_t(j);
-                    ++cnt;
+        const int at = (t + kNbTile) * int(sizeof(Rec) / 16);
+#pragma unroll
+        for (int k = 0; k < PIECES; ++k)
+            if (at + k * kNbBlock <= last) pre[k] = src[at + k * kNbBlock];
+        const Rec *tr = tile[buf];
+        unsigned hits = 0;
+        if (left0 - t >= kNbTile) {
+#pragma unroll 1
+            for (int u = 0; u < kNbTile; u += kNbGroup) {
+                SoftPair<ET> sp[kNbGroup];
+                bool any = false;
+#pragma unroll
+                for (int k = 0; k < kNbGroup; ++k) {
+                    sp[k].set(ip, tr[u + k], e2, hh_e);
+                    any = any || sp[k].is_nb;
                 }
+                if (__builtin_amdgcn_ballot_w64(any)) {
+#pragma unroll
+                    for (int k = 0; k < kNbGroup; ++k) {
+                        sp[k].mr = sp[k].is_nb ? ET(0) : sp[k].mr;
+                        hits |= sp[k].is_nb ? 1u << (u + k) : 0u;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < kNbGroup; ++k) sp[k].add(p);
+            }
+        } else {
+            for (int u = 0; u < left0 - t; ++u) {
+                SoftPair<ET> sp;
+                sp.set(ip, tr[u], e2, hh_e);
+                sp.mr = sp.is_nb ? ET(0) : sp.mr;
+                hits |= sp.is_nb ? 1u << u : 0u;
+                sp.add(p);
             }
         }
-        flush<Part, 1>(&p, &acc);
-        __syncthreads();
+        while (hits) {
+            const int u = t + __builtin_ctz(hits);
+            hits &= hits - 1;
+            if (u == self) continue;
+            if (row && cnt < max_nb) my_seg[cnt] = SegT(js0 - j0 + u);
+            ++cnt;
+        }
+        if (((t + kNbTile) & (kNbChunk - 1)) == 0) flush<Part, 1>(&p, &acc);
+        buf ^= 1;
     }
+    flush<Part, 1>(&p, &acc);
     if (!row) return;
     // split-fastest: the finishing kernel's lanes read consecutive splits
     const int n_split = int(gridDim.y);
@@ -186,11 +252,11 @@ k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *
 // Bound by the latency of its dependent loads (one wave per row, a wave or two per
 // SIMD): with the loads of all splits and of the lists' first entries in flight
 // together 14.9 us at 342 splits of 1024 rows instead of 22.7.
-template <class Pol>
+template <class Pol, class SegT>
 __global__ void __launch_bounds__(64)
 k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
-            double eps2, int64_t n_hard, int n_split, int max_nb, const double *__restrict__ part,
-            const int32_t *__restrict__ seg_cnt, const int32_t *__restrict__ seg, double *__restrict__ acc_irr,
+            double eps2, int64_t n_hard, int n_split, int64_t j_chunk, int max_nb, const double *__restrict__ part,
+            const int32_t *__restrict__ seg_cnt, const SegT *__restrict__ seg, double *__restrict__ acc_irr,
             double *__restrict__ jrk_irr, double *__restrict__ acc_reg, double *__restrict__ jrk_reg,
             int32_t *__restrict__ nb_count, int32_t *__restrict__ nb_list)
 {
@@ -226,7 +292,7 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
 #pragma unroll
             for (int k = 0; k < kNbPass; ++k) {
                 const int spk = s0 + 64 * k + l;
-                firsts[k] = cnts[k] > 0 && max_nb > 0 ? seg[(int64_t(spk) * n_act + q) * max_nb] : 0;
+                firsts[k] = cnts[k] > 0 && max_nb > 0 ? int(seg[(int64_t(spk) * n_act + q) * max_nb]) : 0;
             }
         }
         const int sp = s0 + l;
@@ -246,9 +312,10 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
         const int base = written + (incl - stored);
         const int room = max_nb - base;
         const int take = room <= 0 ? 0 : (stored < room ? stored : room);
-        const int32_t *src = seg + (int64_t(sp < n_split ? sp : 0) * n_act + q) * max_nb;
-        if (take > 0) nb_list[q * max_nb + base] = first;
-        for (int k = 1; k < take; ++k) nb_list[q * max_nb + base + k] = src[k];
+        const int32_t j0 = int32_t(sp * j_chunk);   // (only used when the split is there)
+        const SegT *src = seg + (int64_t(sp < n_split ? sp : 0) * n_act + q) * max_nb;
+        if (take > 0) nb_list[q * max_nb + base] = j0 + first;
+        for (int k = 1; k < take; ++k) nb_list[q * max_nb + base + k] = j0 + int32_t(src[k]);
         const int all = __shfl(incl, 63, 64);
         written = written + all < max_nb ? written + all : max_nb;
         int64_t cs = c;
@@ -285,54 +352,74 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
     }
 }
 
-template <class Pol>
+template <class Pol, class SegT>
 hipError_t run_nb(const NbArgs &a, hipStream_t s, int n_split, int64_t j_chunk)
 {
     const unsigned tiles = unsigned((a.n_act + kNbBlock - 1) / kNbBlock);
     double *part = a.scratch;
     int32_t *seg_cnt = reinterpret_cast<int32_t *>(part + int64_t(n_split) * 6 * a.n_act);
-    int32_t *seg = seg_cnt + int64_t(n_split) * a.n_act;
-    hipLaunchKernelGGL((k_force_nb<Pol>), dim3(tiles, unsigned(n_split)), dim3(kNbBlock), 0, s,
+    SegT *seg = reinterpret_cast<SegT *>(seg_cnt + int64_t(n_split) * a.n_act);
+    hipLaunchKernelGGL((k_force_nb<Pol, SegT>), dim3(tiles, unsigned(n_split)), dim3(kNbBlock), 0, s,
                        static_cast<const typename Pol::Rec *>(a.rec), a.n, a.act, a.n_act, a.h2, a.eps2, a.n_hard,
                        j_chunk, a.max_nb, part, seg_cnt, seg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_nb_finish<Pol>), dim3(unsigned(a.n_act)), dim3(64), 0, s,
+    hipLaunchKernelGGL((k_nb_finish<Pol, SegT>), dim3(unsigned(a.n_act)), dim3(64), 0, s,
                        static_cast<const typename Pol::Rec *>(a.rec), a.n, a.act, a.n_act, a.eps2, a.n_hard, n_split,
-                       a.max_nb, part, seg_cnt, seg, a.acc_irr, a.jrk_irr, a.acc_reg, a.jrk_reg, a.nb_count,
+                       j_chunk, a.max_nb, part, seg_cnt, seg, a.acc_irr, a.jrk_irr, a.acc_reg, a.jrk_reg, a.nb_count,
                        a.nb_list);
     return hipGetLastError();
 }
 
-}  // namespace
+template <class Pol> hipError_t run_seg(const NbArgs &a, hipStream_t s, int n_split, int64_t j_chunk)
+{
+    if (j_chunk <= kShortChunk) return run_nb<Pol, uint16_t>(a, s, n_split, j_chunk);
+    return run_nb<Pol, int32_t>(a, s, n_split, j_chunk);
+}
+
+// Splits are whole FP32 chunks in MIXED; FP64 has none to keep.
+int64_t nb_grain(int precision) { return precision == NBODY_MIXED ? kNbChunk : 32; }
+
+int64_t nb_chunk(int precision, int64_t n, int64_t n_split)
+{
+    const int64_t g = nb_grain(precision), c = (n + n_split - 1) / n_split;
+    return (c + g - 1) / g * g;
+}
 
 // Bytes of scratch one (split, row) pair needs: 6 partial sums, a count and
 // max_nb list entries.
-int64_t nb_scratch_per_row(int max_nb) { return 6 * 8 + 4 + 4 * int64_t(max_nb); }
+int64_t nb_scratch_per_row(int max_nb, int64_t entry) { return 6 * 8 + 4 + entry * int64_t(max_nb); }
 
-int nb_split(int64_t n, int64_t n_act, int max_nb, int64_t scratch_bytes, int n_split_req)
+}  // namespace
+
+// About 8192 waves (8 to a SIMD, where five or six fit: the ends of the first
+// fill with the rest), splits of at least one grain, and what the scratch
+// holds: it must hold one split with entries of four bytes.
+int nb_split(int precision, int64_t n, int64_t n_act, int max_nb, int64_t scratch_bytes)
 {
-    const int64_t tiles = (n_act + kNbBlock - 1) / kNbBlock;
-    // about 4096 workgroups of 128 lanes (8 waves per SIMD; the kernel fits
-    // 6 at a time), splits of at least one tile, and what the scratch holds
-    int64_t sp = n_split_req > 0 ? n_split_req : (4096 + tiles - 1) / tiles;
-    const int64_t by_n = (n + kNbBlock - 1) / kNbBlock;
-    const int64_t by_scratch = scratch_bytes / (nb_scratch_per_row(max_nb) * (n_act > 0 ? n_act : 1));
-    if (sp > by_n) sp = by_n;
-    if (sp > by_scratch) sp = by_scratch;
+    const int64_t rows = n_act > 0 ? n_act : 1;
+    const int64_t tiles = (rows + kNbBlock - 1) / kNbBlock;
+    const int64_t fit4 = scratch_bytes / (nb_scratch_per_row(max_nb, 4) * rows);
+    const int64_t fit2 = scratch_bytes / (nb_scratch_per_row(max_nb, 2) * rows);
+    if (fit4 < 1) return 0;
+    int64_t sp = (8192 + tiles - 1) / tiles;
+    // (FP64: shorter than 128 particles only up to 512 splits, whose sums and lists
+    // kernel 2 adds up: n = 40000, 300 rows 56 us with 313 splits, 80 with 1250)
+    const int64_t by_n = (n + kNbChunk - 1) / kNbChunk, by_grain = (n + nb_grain(precision) - 1) / nb_grain(precision);
+    const int64_t fine = by_grain < 512 ? by_grain : 512;
+    if (sp > (by_n > fine ? by_n : fine)) sp = by_n > fine ? by_n : fine;
     if (sp > 65535) sp = 65535;
-    return int(sp);   // 0: the scratch cannot hold one split
+    const int64_t sp2 = sp < fit2 ? sp : fit2;
+    if (nb_chunk(precision, n, sp2) <= kShortChunk) return int(sp2);
+    return int(sp < fit4 ? sp : fit4);
 }
 
-hipError_t launch_force_nb(int precision, const NbArgs &a, int n_split, hipStream_t s, int *used_split)
+hipError_t launch_force_nb(int precision, const NbArgs &a, int n_split, hipStream_t s)
 {
-    // split length: whole tiles of kNbBlock j (a multiple of the MIXED chunk)
-    int64_t j_chunk = (a.n + n_split - 1) / n_split;
-    j_chunk = (j_chunk + kNbBlock - 1) / kNbBlock * kNbBlock;
+    const int64_t j_chunk = nb_chunk(precision, a.n, n_split);
     const int sp = int((a.n + j_chunk - 1) / j_chunk);
-    if (used_split) *used_split = sp;
-    if (precision == NBODY_MIXED) return run_nb<PolMx<4, false>>(a, s, sp, j_chunk);
-    return run_nb<PolF64<4, false>>(a, s, sp, j_chunk);
+    if (precision == NBODY_MIXED) return run_seg<PolMx<4, false>>(a, s, sp, j_chunk);
+    return run_seg<PolF64<4, false>>(a, s, sp, j_chunk);
 }
 
 }  // namespace nb

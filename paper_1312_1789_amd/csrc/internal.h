@@ -253,11 +253,10 @@ struct NbArgs {
     int32_t *nb_count;      // [n_act]
     int32_t *nb_list;       // [n_act][max_nb] (may be null when max_nb == 0)
 };
-// Scratch bytes per (split, row); the split count for a scratch of the given
-// size (0 when it cannot hold one split); the launch (FP64 or MIXED).
-int64_t nb_scratch_per_row(int max_nb);
-int nb_split(int64_t n, int64_t n_act, int max_nb, int64_t scratch_bytes, int n_split_req);
-hipError_t launch_force_nb(int precision, const NbArgs &a, int n_split, hipStream_t s, int *used_split);
+// The split count for a scratch of the given size (0 when it cannot hold one
+// split); the launch (FP64 or MIXED).
+int nb_split(int precision, int64_t n, int64_t n_act, int max_nb, int64_t scratch_bytes);
+hipError_t launch_force_nb(int precision, const NbArgs &a, int n_split, hipStream_t s);
 
 // The default split count of a j path.
 int auto_split(int precision, int64_t n, int64_t n_act, int ni, int jpath, int64_t part_rows);

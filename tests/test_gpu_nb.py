@@ -136,6 +136,40 @@ def test_nb_list_cap_and_no_list(nb_case, precision):
     sim.close()
 
 
+# edges of LDS tiles (32 particles), of groups of two, of splits (32 in FP64, 128
+# in MIXED), with pairs of hard particles before them
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n, n_hard", [(17, 0), (32, 0), (33, 2), (63, 0), (129, 5), (290, 2), (1057, 0)])
+def test_nb_tile_edges(n, n_hard, precision):
+    model = nbody_ics.plummer(n, 840 + n)
+    act = np.arange(n, dtype=np.int32)
+    h2, margin = band_free_radii(model.x, act, 841 + n, k_max=8)
+    ref = oracle.force_nb(OracleConfig(order=4, eps2=1e-8, n_hard=n_hard), model.m, model.x, model.v, act, h2, 16)
+    sim = _sim(model, precision, 1e-8, n_hard)
+    _compare(_run(sim, act, h2, 16), ref, n, 16, precision, "n=%d" % n)
+    sim.close()
+
+
+def test_nb_long_split():
+    """10000 rows with room for 4096 neighbours each leave the scratch one split
+    of 140000 particles, too long for list entries of two bytes; checked on 60
+    rows, and on the same rows alone (short splits)."""
+    n = 140000
+    model = nbody_ics.plummer(n, 88)
+    sim = _sim(model, "mixed", 1e-8, 0)
+    act = np.arange(n - 10000, n, dtype=np.int32)
+    h2 = np.full(act.size, 1e-5)
+    pick = np.arange(0, 10000, 167)
+    h2r, margin = band_free_radii(model.x, act[pick], 881, k_max=30)
+    h2[pick] = h2r
+    got = _run(sim, act, h2, 4096)
+    ref = oracle.force_nb(OracleConfig(order=4, eps2=1e-8), model.m, model.x, model.v, act[pick], h2r, 4096)
+    sub = {k: (v[:, pick] if v.ndim == 2 and k in PARTS else v[pick]) for k, v in got.items()}
+    _compare(sub, ref, pick.size, 4096, "mixed", "long split")
+    _compare(_run(sim, act[pick], h2r, 4096), ref, pick.size, 4096, "mixed", "short splits")
+    sim.close()
+
+
 def test_nb_one_split_and_scratch_limit():
     """15000 rows of a 20000-particle system with room for 2048 neighbours
     each fit the scratch only as one j-split; 20000 rows with 4096 do not fit
