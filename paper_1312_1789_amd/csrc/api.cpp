@@ -96,7 +96,7 @@ nb::ForceArgs force_args(nbody_ctx *ctx, int precision, const void *rec, int64_t
         a.fine = true;
         a.jpath = ctx->tune[r].jpath;
     } else {
-        nb::default_shape(precision, a.n, n_act, &a.ni, &a.block, &a.jpath);
+        nb::default_shape(precision, ctx->cfg.order, pot != nullptr, a.n, n_act, &a.ni, &a.block, &a.jpath);
         a.n_split = 0;
     }
     return a;

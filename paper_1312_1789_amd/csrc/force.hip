@@ -420,13 +420,17 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
 // The default j-split of kernels A and B, sized in waves of 64 NI rows (wt row
 // tiles) that walk c particles each:
 //  - many (wt n / 128 >= 16384, several rounds of waves on the chip): about
-//    32768 waves of at least 128 particles (256 if that still gives 16384), so
-//    that the last round is a small part of the call, and at most 8192 (a wave
-//    is then some microseconds of work to a 100-byte partial row).  About 8192 waves, two or
+//    32768 waves of at least 128 particles (256 in MIXED and DS, or if that still
+//    gives 16384), so that the last round is a small part of the call, and at
+//    most 8192 (a wave is then some microseconds of work to a 100-byte partial
+//    row; n = 32768, n_act = 4096 MIXED order 8 with the potential 334 us with 256
+//    splits, 297 with 128).  About 8192 waves, two or
 //    three rounds, had cost 10-30% of it: n_act = n = 90000 MIXED order 6 11219
 //    us with 6 splits, 9280 with 23; n = 262144, n_act = 3001 994 with 171, 926
 //    with 683;
-//  - otherwise a MIXED row takes its FP32 chunks (128 particles) one to a wave;
+//  - otherwise a MIXED row takes its FP32 chunks (128 particles) one to a wave, and
+//    two above 8192 waves (n = 262144, 400 rows order 4: 2048 partial sums a value
+//    cost 134 us for the call, 1024 127);
 //  - FP64 and DS sums have no chunks to keep, and a wave that walks 128
 //    particles alone on its SIMD is all latency (28 us at order 4, FP64, for
 //    any n): as few as 32 each, about 3072 waves, at most about 1250 splits (the
@@ -439,10 +443,10 @@ int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
     const auto up = [](int64_t v, int64_t g) { return (v + g - 1) / g * g; };
     if (wt * n >= int64_t(16384) * 128) {
         int64_t c = up(wt * n / 32768, 128);
-        if (c < 256 && wt * n >= int64_t(16384) * 256) c = 256;
+        if (c < 256 && (precision != NBODY_FP64 || wt * n >= int64_t(16384) * 256)) c = 256;
         return c < 8192 ? c : 8192;
     }
-    if (precision == NBODY_MIXED) return kMixedChunk;
+    if (precision == NBODY_MIXED) return wt * n >= int64_t(8192) * kMixedChunk ? 2 * kMixedChunk : kMixedChunk;
     int64_t c = wt * n / 3072 > n / 1250 ? wt * n / 3072 : n / 1250;
     c = up(c, 32);
     return c < 32 ? 32 : (c > 128 ? 128 : c);
@@ -505,24 +509,40 @@ void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool 
 // up to 64 (one row per lane leaves a chip of 1024 SIMDs nearly idle there: n =
 // 30000, 64 rows, FP64 order 8 45.7 us with kernel A, 19.9 with C; MIXED keeps
 // the order of its FP32 sums).  One row per lane beyond: with many waves
-// (default_chunk) the scalar path, whose j records cost no LDS bandwidth (90000
-// rows MIXED order 4: LDS 6261, scalar 5459 us), in workgroups of 128; with few,
+// the scalar path, whose j records cost no LDS bandwidth (90000 rows MIXED order 4:
+// LDS 6261, scalar 5459 us), in workgroups of 128 (MIXED from twice as many on: n =
+// 32768, 4096 rows order 6 scalar 205, LDS 196 us, n = 120000, 2500 rows 384 and 398);
+// but DS, whose
+// adds keep more registers, and MIXED order 4 with the potential, whose self pairs
+// are compared in scalar registers, stay on LDS tiles (n = 120000, 2500 rows DS order
+// 8 scalar 1150, LDS 970 us, order 4 with the potential 538 and 501; MIXED order 4 with it
+// 343 and 312; DS order 4 without it is the exception, 433 and 454); with few waves,
 // the LDS path, whose loads run ahead (n = 80000, 200 rows FP64 order 8: scalar
-// 107, LDS 91 us), one wave to a workgroup.
-void default_shape(int precision, int64_t n, int64_t n_act, int *ni, int *block, int *jpath)
+// 107, LDS 91 us).  On the LDS path four waves share a tile where there are enough
+// rows for that (padded by an eighth at most) and three waves to a SIMD: tiles of
+// its own leave a wave's SIMD two to five waves (n = 20000, 4000 rows MIXED order 6 136
+// us with one wave to a workgroup, 118 with four, order 8 218 and 176; but n = 262144,
+// 201 rows FP64 order 8 234 and 249).
+void default_shape(int precision, int order, bool pot, int64_t n, int64_t n_act, int *ni, int *block, int *jpath)
 {
     *ni = 1;
-    const int64_t wt = (n_act + 63) / 64;
     if (n_act <= (precision == NBODY_MIXED ? 32 : 64)) {
         *block = 64;
         *jpath = 3;
-    } else if (wt * n >= int64_t(16384) * 128) {
+        return;
+    }
+    const int64_t wt = (n_act + 63) / 64;
+    const bool scalar = precision == NBODY_FP64    ? wt * n >= int64_t(16384) * 128
+                        : precision == NBODY_MIXED ? wt * n >= int64_t(32768) * 128 && !(order == 4 && pot)
+                                                   : false;
+    if (scalar) {
         *block = 128;
         *jpath = 1;
-    } else {
-        *block = 64;
-        *jpath = 2;
+        return;
     }
+    const int64_t c = default_chunk(precision, n, n_act, 1), waves = wt * ((n + c - 1) / c);
+    *block = wt >= 24 && waves >= 3072 ? 256 : 64;
+    *jpath = 2;
 }
 
 hipError_t launch_split_reduce_sf(int order, const ForceArgs &a, int n_split, hipStream_t s)

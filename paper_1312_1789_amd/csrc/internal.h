@@ -165,7 +165,7 @@ hipError_t launch_force_high(const ForceArgs &a, hipStream_t s, UsedShape *used)
 void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool fine, int ni, int jpath,
                  int64_t part_rows, int *n_split, int64_t *j_chunk);
 // The shape of an untuned call.
-void default_shape(int precision, int64_t n, int64_t n_act, int *ni, int *block, int *jpath);
+void default_shape(int precision, int order, bool pot, int64_t n, int64_t n_act, int *ni, int *block, int *jpath);
 
 // Fixed-order sum of n_split partial results in part[component][row][split]
 // into a.out.
