@@ -208,7 +208,9 @@ __device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm,
     __syncthreads();
     int64_t tn = wm[0];
     for (int k = 1; k < kSW; ++k) tn = wm[k] < tn ? wm[k] : tn;
-    int off = incl - mine, total = 0, search = 0;
+    // (a wave whose least time is not the step's has no active particles: its
+    // prefix counts others, and its blocks share their successor's offset)
+    int off = wmin == tn ? incl - mine : 0, total = 0, search = 0;
     for (int k = 0; k < kSW; ++k) {
         const int c = wm[k] == tn ? wcnt[k] : 0;
         if (k < wv) off += c;

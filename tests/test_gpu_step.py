@@ -115,6 +115,34 @@ def test_active_sets_by_block(n, most):
     _compare(a, b)
 
 
+# the blocks of the last workgroup's four waves: 64 to a wave with one block per
+# thread (n <= 65536), 256 with four, 1024 with sixteen
+@pytest.mark.parametrize("n, per_wave", [(20000, 64), (60000, 64), (200000, 256), (600000, 1024)])
+@pytest.mark.parametrize("where", ["last", "middle", "apart"])
+@pytest.mark.parametrize("due", [3, 9, 70])
+def test_active_sets_in_late_waves(n, per_wave, where, due):
+    """Due particles only in blocks that whole waves without any precede, with
+    more of them to a block than come with its time; every other block has all
+    its particles at one later time."""
+    model = nbody_ics.plummer(n, 2360)
+    a, b = _sim(model), _sim(model)
+    b.set_timing(True)
+    wave = 256 * per_wave
+    waves = (n + wave - 1) // wave
+    bases = {"last": [(n - 1) // 256 * 256], "middle": [waves // 2 * wave + 256],
+             "apart": [0, 2 * wave + 768] if waves > 2 else [512, wave + 768]}[where]
+    lv = torch.full((n,), 5, dtype=torch.int32)
+    for base in bases:
+        lv[base:min(base + due, n)] = 14
+    total = int((lv == 14).sum())
+    for sim in (a, b):
+        sim.level.copy_(lv.to(sim.device))
+    assert a.step() == b.step() == (TICKS >> 14, total)
+    for _ in range(3):
+        assert a.step() == b.step()
+    _compare(a, b)
+
+
 @pytest.mark.parametrize("n_hard", [2, 255, 257])
 def test_post_newtonian_steps(n_hard):
     """Post-Newtonian terms added by the step kernel (up to 256 hard
