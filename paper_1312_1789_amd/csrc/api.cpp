@@ -797,6 +797,9 @@ nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t
     nbody_status s = NBODY_OK;
     sa.mode = nb::kStepSchedule;
     sa.seq = seq;
+    // a value that became non-finite before the run ends it here: the small step
+    // enqueued before its schedule is read leaves without effect
+    sa.nonfinite = static_cast<unsigned long long>(ctx->stats.nonfinite);
     NB_HIP(nb::launch_step(sa, ctx->stream));
     for (;;) {
         while (any_small && ahead < allowed && steps + ahead < max_steps) {

@@ -83,7 +83,7 @@ struct DevScalars {
     unsigned long long nonfinite;
     int64_t seq;                    // of the last schedule published by the step kernel
     int64_t halt;                   // a corrected value was not finite: no further small step
-    unsigned long long nonfinite0;  // nonfinite when the run began
+    unsigned long long nonfinite0;  // nonfinite as the host last read it before the run
     int64_t pad;
 };
 
@@ -228,6 +228,7 @@ struct StepArgs {
     struct HostScalars *pub;     // slots of the published schedules
     StepMode mode;
     int64_t seq;
+    unsigned long long nonfinite;   // kStepSchedule: non-finite values the host knows of
     SmallTable tab;              // kStepSmall
     const double *part;          // kStepSmall
     double *f[4];                // kStepForces

@@ -169,7 +169,7 @@ __device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm,
     // all that it reads, in flight together
     DevScalars *sc = a.sc;
     const unsigned long long nf = shared_load(&sc->nonfinite), uf = shared_load(&sc->underflow);
-    const unsigned long long nf0 = a.mode == kStepSchedule ? nf : sc->nonfinite0;
+    const unsigned long long nf0 = a.mode == kStepSchedule ? a.nonfinite : sc->nonfinite0;
     const int64_t seq = a.mode == kStepSchedule ? a.seq : sc->seq + 1;
     int64_t bt[PER];
     int bc[PER];

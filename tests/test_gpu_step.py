@@ -171,3 +171,34 @@ def test_run_stops_at_a_nonfinite_value():
         to.copy_(of)
     assert sim.run(1 << 62, 10)[0] == 10
     assert torch.isfinite(sim.x).all()
+
+
+@pytest.mark.parametrize("call", ["run", "step"])
+@pytest.mark.parametrize("due", [1, 700])
+def test_no_step_after_a_nonfinite_correction(call, due):
+    """A non-finite value from the program's own corrector call ends the next
+    run or step before it: the call reports it and leaves the state alone
+    (due = 1: the first step would be one enqueued before its schedule is
+    read).  The call after that goes on."""
+    from paper_1312_1789_amd import abi
+    model = nbody_ics.plummer(1500, 2601)
+    sim = _sim(model, 6, "fp64")
+    lv = torch.full((model.n,), 10, dtype=torch.int32)
+    lv[:due] = 14
+    sim.level.copy_(lv.to(sim.device))
+    good = [t.clone() for t in (sim.x, sim.v, *sim.d, sim.t_tick, sim.level)]
+    act = torch.tensor([model.n - 1], dtype=torch.int32, device=sim.device)
+    f = {k: torch.full((3, 1), float("nan"), dtype=torch.float64, device=sim.device)
+         for k in ("acc", "jrk", "snp", "crk")}
+    sim.correct(act, TICKS >> 10, f)
+    for to, of in zip((sim.x, sim.v, *sim.d, sim.t_tick, sim.level), good):
+        to.copy_(of)
+    with pytest.raises(abi.NBodyError) as e:
+        sim.run(1 << 62, 5) if call == "run" else sim.step()
+    assert e.value.status == abi.NBODY_E_NONFINITE
+    for now, was in zip((sim.x, sim.v, *sim.d, sim.t_tick, sim.level), good):
+        assert torch.equal(now, was)
+    assert sim.stats().steps == 0
+    assert sim.step() == (TICKS >> 14, due)
+    assert sim.run(1 << 62, 5)[0] == 5
+    assert torch.isfinite(sim.x).all()
