@@ -85,6 +85,45 @@ struct BatchLaunch {
     int grain;                  // shortest j-split: MIXED an FP32 chunk, FP64 and DS two tiles
 };
 
+// How a step's work is cut (also compiled for the host, which tests it).
+constexpr int64_t kBItemMin = 32768;   // pair evaluations of a work item worth claiming
+
+// Work items of a row tile and split.
+__host__ __device__ __forceinline__ int b_tile_items(const BatchLaunch &L) { return L.itile == 64 ? L.halves : 1; }
+
+// The work of one cluster in a step: row tiles, j-splits sp of jc particles.
+struct BatchCut {
+    int32_t tiles, sp, jc;
+};
+__host__ __device__ __forceinline__ BatchCut b_cut(int64_t na, int64_t nn, int itile, int grain, int64_t w_item)
+{
+    BatchCut k;
+    k.tiles = int32_t((unsigned(na) + unsigned(itile) - 1u) / unsigned(itile));
+    int64_t sp = (int64_t(itile) * nn + w_item - 1) / w_item;
+    const int64_t sp_max = (nn + grain - 1) / grain;   // pieces of at least a grain (MIXED: an FP32 chunk)
+    sp = sp < 1 ? 1 : (sp > sp_max ? sp_max : sp);
+    unsigned jc = (unsigned(nn) + unsigned(sp) - 1u) / unsigned(sp);
+    jc = (jc + unsigned(grain) - 1u) / unsigned(grain) * unsigned(grain);
+    k.jc = int32_t(jc);
+    k.sp = int32_t((unsigned(nn) + jc - 1u) / jc);
+    return k;
+}
+
+// Pair evaluations per item for W in all.  Items of at least kBItemMin pairs (an
+// item costs a few microseconds of loads before its first pair, and the claim
+// of one from a counter that an eighth of the chip shares some 50 ns), up to the
+// number asked for; a step of less than four such items per workgroup is cut
+// into as many as there are workgroups (an eighth less, as the cuts round up),
+// all dealt, and at least into one (a single workgroup).
+__host__ __device__ __forceinline__ int64_t b_item_size(const BatchLaunch &L, int64_t W)
+{
+    int64_t k = W / kBItemMin;
+    if (k < 4 * int64_t(L.force_grid)) k = int64_t(L.force_grid) * 7 / 8;
+    if (k > L.k_items) k = L.k_items;
+    if (k < 1) k = 1;
+    return W * b_tile_items(L) / k + 1;
+}
+
 hipError_t batch_cid(const BatchLaunch &L, hipStream_t s);
 // The step's schedule and plan (order: of the pair terms the partials hold);
 // all_active: every particle at t = 0.

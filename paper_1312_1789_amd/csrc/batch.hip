@@ -36,7 +36,6 @@ namespace {
 
 constexpr int kBBlock = kBatchSchedBlock;
 constexpr int kBTile = 32;   // records per LDS tile of the one-wave force workgroups
-constexpr int64_t kBItemMin = 32768;   // pair evaluations of a work item worth claiming
 constexpr int kBSub = 32;               // clusters per arrival counter
 constexpr int kBThreads = 256;  // threads per scheduling block (4 particles each)
 
@@ -136,41 +135,6 @@ __device__ __forceinline__ uint32_t b_queue_start(int64_t total, int grid, int x
     const int64_t len = total * (x + 1) / kXcds - total * x / kXcds;
     const int dealt = b_dealt(grid, x);
     return uint32_t(len < dealt ? len : dealt);
-}
-
-// Work items of a row tile and split.
-__device__ __forceinline__ int b_tile_items(const BatchLaunch &L) { return L.itile == 64 ? L.halves : 1; }
-
-// The work of one cluster in a step: row tiles, j-splits sp of jc particles.
-struct BatchCut {
-    int32_t tiles, sp, jc;
-};
-__device__ __forceinline__ BatchCut b_cut(int64_t na, int64_t nn, int itile, int grain, int64_t w_item)
-{
-    BatchCut k;
-    k.tiles = int32_t((unsigned(na) + unsigned(itile) - 1u) / unsigned(itile));
-    int64_t sp = (int64_t(itile) * nn + w_item - 1) / w_item;
-    const int64_t sp_max = (nn + grain - 1) / grain;   // pieces of at least a grain (MIXED: an FP32 chunk)
-    sp = sp < 1 ? 1 : (sp > sp_max ? sp_max : sp);
-    unsigned jc = (unsigned(nn) + unsigned(sp) - 1u) / unsigned(sp);
-    jc = (jc + unsigned(grain) - 1u) / unsigned(grain) * unsigned(grain);
-    k.jc = int32_t(jc);
-    k.sp = int32_t((unsigned(nn) + jc - 1u) / jc);
-    return k;
-}
-
-// Pair evaluations per item for W in all.  Items of at least kBItemMin pairs (an
-// item costs a few microseconds of loads before its first pair, and the claim
-// of one from a counter that an eighth of the chip shares some 50 ns), up to the
-// number asked for; a step of less than four such items per workgroup is cut
-// into as many as there are workgroups (an eighth less, as the cuts round up),
-// all dealt.
-__device__ __forceinline__ int64_t b_item_size(const BatchLaunch &L, int64_t W)
-{
-    int64_t k = W / kBItemMin;
-    if (k < 4 * int64_t(L.force_grid)) k = int64_t(L.force_grid) * 7 / 8;
-    if (k > L.k_items) k = L.k_items;
-    return W * b_tile_items(L) / k + 1;
 }
 
 // The plan of one batched step (one block).  For every cluster: active

@@ -244,6 +244,46 @@ def test_batch_force_block_steps(order, shape, precision):
             assert st["rms"] <= LOW_TOL[key] and st["max"] <= 10 * LOW_TOL[key], (key, st)
 
 
+@pytest.mark.parametrize("n_clusters", [5, 300])
+def test_batch_few_workgroups(n_clusters):
+    """Force grids of one workgroup and around the eight item ranges, one per
+    XCD (each range's first items are dealt to its workgroups: some ranges have
+    none), on steps too small for four items a workgroup, and a step in which
+    every cluster rests.  One and two workgroups both leave a cluster's j-range
+    in one piece, so their forces are the same bits."""
+    models = [nbody_ics.plummer(20 + (13 * c) % 90, 990 + c) for c in range(n_clusters)]
+    first = {}
+    for grid in (1, 2, 7, 8, 9):
+        B = _batch(models, 4, n_hard=0, k_min=8, k_max=16)
+        B.set_launch(grid, 0, 0)
+        assert B.get_launch()[0] == grid
+        B.init()
+        ocfg = _ocfg(B)
+        errs = {k: [] for k in KEYS}
+        for step in range(2):
+            h0 = B.to_numpy()
+            B.step(1)
+            aoff, act, f = B.last_step()
+            f = f.cpu().numpy()
+            _force_errors(B, models, h0, aoff, act.cpu().numpy(), f, ocfg, 4, errs)
+            if step == 0:
+                first[grid] = f
+        for key in KEYS[:2]:
+            st = err_stats(np.concatenate(errs[key]))
+            assert st["rms"] <= 1e-12 and st["max"] <= 1e-9, (grid, key, st)
+        h0 = B.to_numpy()
+        B.set_end(0)
+        B.step(1)
+        aoff, _, _ = B.last_step()
+        assert aoff[-1] == 0 and B.poll()[0] == 0
+        h1 = B.to_numpy()
+        for key in ("x", "v", "t_tick", "level"):
+            np.testing.assert_array_equal(h0[key], h1[key])
+        B.close()
+    if n_clusters == 5:
+        np.testing.assert_array_equal(first[1], first[2])
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("order", [4, 6, 8])
 def test_batch_step_parity(order, precision):
