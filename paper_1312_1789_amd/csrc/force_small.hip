@@ -221,9 +221,9 @@ __device__ __forceinline__ void small_run(const PredIn &in, int64_t n, const int
                                           double *part, typename Pol::Rec *tiles, double (*red)[kSlots])
 {
     const int ng = (n_split + C::kSplits - 1) / C::kSplits;
-    const int grp = int(blockIdx.x);
+    const int grp = int(blockIdx.y);
     if (grp >= ng) return;
-    const int64_t row0 = int64_t(blockIdx.y) * 64;
+    const int64_t row0 = int64_t(blockIdx.x) * 64;
     const int s0 = grp * C::kSplits;
     walk<C, Pol, P, PREC>(in, n, act, n_act, typename Pol::ET(eps2), n_hard, j_chunk, n_split, s0, row0, tiles, red);
     put<C, Pol, P>(n_act, row0, n_split - s0 < C::kSplits ? n_split - s0 : C::kSplits, grp, ng, !to_part && ng == 1, o,
@@ -280,7 +280,7 @@ struct Launch {
     const PredIn *in;
     int n_split;
     int64_t j_chunk;
-    unsigned groups, tiles;
+    unsigned tiles, groups;   // the grid: tiles of 64 rows (up to 2^20) by groups of splits (up to 2^15)
     const DevScalars *dev;
     const SmallTable *tab;
     int64_t t_limit;
@@ -291,7 +291,7 @@ hipError_t run(const Launch &L, hipStream_t s)
 {
     const ForceArgs &a = *L.a;
     const OutPtrs o{{a.out[0], a.out[1], a.out[2], a.out[3], a.out[4]}};
-    hipLaunchKernelGGL((k_force_small<Pol, P, PREC>), dim3(L.groups, L.tiles), dim3(kWaves * 64), 0, s, *L.in, a.n, a.act,
+    hipLaunchKernelGGL((k_force_small<Pol, P, PREC>), dim3(L.tiles, L.groups), dim3(kWaves * 64), 0, s, *L.in, a.n, a.act,
                        a.n_act, a.eps2, a.n_hard, L.j_chunk, L.n_split, o, a.part, L.dev, *L.tab, L.t_limit);
     return hipGetLastError();
 }
@@ -334,7 +334,7 @@ hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const
     if (used) *used = UsedShape{1, 64, n_split, 3};
     const int gs = small_group(a.n_act), ng = (n_split + gs - 1) / gs;
     const SmallTable none{};
-    const Launch L{&a, &in, n_split, j_chunk, unsigned(ng), unsigned((a.n_act + 63) / 64), nullptr, &none, 0};
+    const Launch L{&a, &in, n_split, j_chunk, unsigned((a.n_act + 63) / 64), unsigned(ng), nullptr, &none, 0};
     const hipError_t e = run_order(order, precision, L, s);
     if (e != hipSuccess || ng == 1) return e;
     return launch_split_reduce_sf(order, a, ng, s);
@@ -348,7 +348,7 @@ hipError_t launch_force_small_dev(int order, int precision, const ForceArgs &a, 
         const int gs = small_group(k + 1), ng = (tab.n_split[k] + gs - 1) / gs;
         if (ng > groups) groups = ng;
     }
-    const Launch L{&a, &in, 0, 0, unsigned(groups), 1u, dev, &tab, t_limit};
+    const Launch L{&a, &in, 0, 0, 1u, unsigned(groups), dev, &tab, t_limit};
     return run_order(order, precision, L, s);
 }
 

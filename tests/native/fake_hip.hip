@@ -1,0 +1,117 @@
+// A stand-in for the HIP runtime: loaded before the library, it takes the
+// library's calls, so that its host code runs where there is no GPU.  Kernels
+// do nothing, but a launch that the device's limits do not allow fails.
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "internal.h"
+
+namespace {
+
+std::map<const void *, std::string> g_names;   // kernels by the address of their host stub
+hipError_t g_last = hipSuccess;
+struct Launch {
+    std::string name;
+    dim3 grid, block;
+};
+std::vector<Launch> g_launches;
+struct Config {
+    dim3 grid, block;
+    size_t shared;
+    hipStream_t stream;
+};
+std::vector<Config> g_config;
+
+hipError_t give(hipError_t e)
+{
+    if (e != hipSuccess) g_last = e;
+    return e;
+}
+
+}  // namespace
+
+extern "C" {
+
+void **__hipRegisterFatBinary(const void *)
+{
+    static void *handle = nullptr;
+    return &handle;
+}
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *stub, char *, const char *name, unsigned, void *, void *, void *, void *,
+                           int *)
+{
+    g_names[stub] = name;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t stream)
+{
+    g_config.push_back({grid, block, shared, stream});
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hipStream_t *stream)
+{
+    const Config c = g_config.back();
+    g_config.pop_back();
+    *grid = c.grid;
+    *block = c.block;
+    *shared = c.shared;
+    *stream = c.stream;
+    return hipSuccess;
+}
+
+hipError_t hipLaunchKernel(const void *stub, dim3 grid, dim3 block, void **, size_t, hipStream_t)
+{
+    g_launches.push_back({g_names[stub], grid, block});
+    const bool in_limits = grid.x > 0 && grid.y > 0 && grid.z > 0 && block.x > 0 && block.x * block.y * block.z <= 1024 &&
+                           uint64_t(grid.x) * block.x < (uint64_t(1) << 32) && grid.y <= 65535 && grid.z <= 65535;
+    return give(in_limits ? hipSuccess : hipErrorInvalidConfiguration);
+}
+
+hipError_t hipGetLastError()
+{
+    const hipError_t e = g_last;
+    g_last = hipSuccess;
+    return e;
+}
+const char *hipGetErrorString(hipError_t) { return "an error of the stand-in"; }
+hipError_t hipGetDevice(int *d)
+{
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned)
+{
+    *p = calloc(1, bytes);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p)
+{
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned)
+{
+    *d = h;
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *, int, size_t, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+
+// For the test: the launches since the last call, "name gx gy gz bx" a line.
+const char *fake_launches()
+{
+    static std::string s;
+    s.clear();
+    for (const Launch &l : g_launches)
+        s += l.name + " " + std::to_string(l.grid.x) + " " + std::to_string(l.grid.y) + " " + std::to_string(l.grid.z) +
+             " " + std::to_string(l.block.x) + "\n";
+    g_launches.clear();
+    return s.c_str();
+}
+
+}  // extern "C"

@@ -60,3 +60,52 @@ def test_batch_plan_cuts(tmp_path):
             assert 1 <= least <= most
         if grid == 1 and sum((a + itile - 1) // itile * itile * n for n, a in zip(nn, na)) < 4 * 32768:
             assert sum(na) == 0 or most == 1   # one workgroup, little work: nothing is split
+
+
+def _with_fake_hip(tmp_path, program):
+    """Run a Python program with the library on top of the stand-in for the HIP
+    runtime (no GPU, no torch): `abi` and `fake` are there; returns what it
+    printed last, as JSON."""
+    lib = _compile("fake_hip.hip", tmp_path / "fake_hip.so")
+    head = ("import ctypes as C, json, sys\n"
+            "fake = C.CDLL(%r, mode=C.RTLD_GLOBAL)\n"
+            "fake.fake_launches.restype = C.c_char_p\n"
+            "sys.path.insert(0, %r)\n"
+            "from paper_1312_1789_amd import abi\n"
+            "assert 'torch' not in sys.modules\n" % (lib, build_lib.ROOT))
+    r = subprocess.run([sys.executable, "-c", head + program], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+LARGE_CALLS = """
+n = 1 << 26
+cfg = abi.nbody_config(4, abi.NBODY_MIXED, n, 0, 1e-8, 0.01, 0.01, 3, 20, 0, 0.0, 0)
+at = 1 << 40   # device addresses, never read here
+ctx = abi.nbody_create(cfg, at, abi.nbody_workspace_size(cfg), 0)
+st = abi.nbody_state(at, at, at, (C.c_void_p * 6)(at, at), at, at)
+seen = []
+for fuse in (1, 0):
+    abi.nbody_set_fusion(ctx, fuse)
+    for n_split in (0, 1, 8):
+        abi.nbody_set_launch(ctx, 1, 64, n_split, 3)
+        for n_act in (64 * 65535, 64 * 65535 + 1, n):
+            fake.fake_launches()
+            abi.nbody_predict_force(ctx, st, 1, n_act, at, at, at, 0, 0, at)
+            rows = [l.split() for l in fake.fake_launches().decode().splitlines()]
+            seen += [(fuse, n_act, l[0], *map(int, l[1:])) for l in rows if "force" in l[0]]
+print(json.dumps(seen))
+"""
+
+
+def test_wave_split_launches_within_limits(tmp_path):
+    """The wave j-split kernels, with the predictor inside and without, take
+    every active set a context can have (a shape set by hand is used for any
+    number of rows): more than 65535 tiles of 64 rows do not fit the second
+    grid dimension."""
+    seen = _with_fake_hip(tmp_path, LARGE_CALLS)
+    assert len(seen) == 18
+    for fuse, n_act, name, gx, gy, gz, bx in seen:
+        rows = 64 if fuse else 16
+        assert ("small" in name) == (fuse == 1)
+        assert gx * rows >= n_act and gy <= 65535 and gz == 1, (name, n_act, gx, gy)
