@@ -169,7 +169,11 @@ __device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm,
     // all that it reads, in flight together
     DevScalars *sc = a.sc;
     const unsigned long long nf = shared_load(&sc->nonfinite), uf = shared_load(&sc->underflow);
-    const unsigned long long nf0 = a.mode == kStepSchedule ? a.nonfinite : sc->nonfinite0;
+    unsigned long long nf0 = a.nonfinite;
+    // (taken into registers here: a choice between its address and the other's
+    // would put the launch's arguments into scratch memory, 832 bytes a lane)
+    asm volatile("" : "+s"(nf0));
+    if (a.mode != kStepSchedule) nf0 = sc->nonfinite0;
     const int64_t seq = a.mode == kStepSchedule ? a.seq : sc->seq + 1;
     int64_t bt[PER];
     int bc[PER];
