@@ -149,23 +149,34 @@ nbody_status read_scalars(nbody_ctx *ctx, nb::DevScalars *h)
     return NBODY_OK;
 }
 
-// The scheduler result with sequence number seq, read from the pinned host
-// copy as soon as the scheduler has written it (the later kernels of the
-// step may still run).  The wait polls host memory and, every few thousand
-// polls, the stream: a stream error is returned, and a stream that finished
-// without the result (which should not happen) falls back to the copy.
-// A slot before its schedule is written.  (Slots are used again only kPubSlots
-// schedules later, more than a run has in flight.)
+// The slot of the schedule numbered seq.  A slot is emptied when it has been
+// read (it is used again kPubSlots schedules later, more than a run has in
+// flight).
+nb::HostScalars *slot(nbody_ctx *ctx, int64_t seq) { return ctx->pub_host + (seq & (nb::kPubSlots - 1)); }
 void clear_published(nb::HostScalars *p)
 {
     p->t_next = p->n_act = nb::kPubEmpty;
     p->underflow = p->nonfinite = static_cast<unsigned long long>(nb::kPubEmpty);
 }
 
+// Empties the slots of schedules that a call which failed left unread.
+nbody_status forget_unread(nbody_ctx *ctx)
+{
+    if (ctx->pub_read == ctx->pub_seq) return NBODY_OK;
+    NB_HIP(hipStreamSynchronize(ctx->stream));
+    for (int k = 0; k < nb::kPubSlots; ++k) clear_published(ctx->pub_host + k);
+    return NBODY_OK;
+}
+
+// The scheduler result with sequence number seq, read from the pinned host
+// copy as soon as the scheduler has written it (the later kernels of the
+// step may still run).  The wait polls host memory and, every few thousand
+// polls, the stream: a stream error is returned, and a stream that finished
+// without the result (which should not happen) falls back to the copy.
 nbody_status read_published(nbody_ctx *ctx, int64_t seq, nb::DevScalars *h)
 {
     if (!ctx->pub_host) return read_scalars(ctx, h);
-    nb::HostScalars *p = ctx->pub_host + (seq & (nb::kPubSlots - 1));
+    nb::HostScalars *p = slot(ctx, seq);
     // The step kernel writes the words in no order: each is awaited, against the
     // value that no schedule has (clear_published).
     const auto arrived = [&] {
@@ -189,6 +200,7 @@ nbody_status read_published(nbody_ctx *ctx, int64_t seq, nb::DevScalars *h)
         }
     }
     clear_published(p);
+    ctx->pub_read = seq;
     h->seq = seq;
     return NBODY_OK;
 }
@@ -300,7 +312,7 @@ nbody_status nbody_create(const nbody_config *cfg, void *workspace, size_t bytes
         ctx->pub_host = nullptr;
         (void)hipGetLastError();
     }
-    ctx->pub_seq = 0;
+    ctx->pub_seq = ctx->pub_read = 0;
     if (e != hipSuccess) {
         delete ctx;
         return fail(NBODY_E_HIP, "nbody_create: %s", hipGetErrorString(e));
@@ -751,14 +763,28 @@ nb::StepScratch step_scratch(nbody_ctx *ctx)
 // step that is not small leave at once, a few microseconds).
 constexpr int64_t kAheadSmall = 2, kAheadLarge = 1;
 
+// Steps of a run so far, the time and the active particles of the last one.
+struct StepsTaken {
+    int64_t steps, t, n_act;
+};
+void count_step(nbody_ctx *ctx, int64_t t, int64_t n_act, StepsTaken *r)
+{
+    ctx->pub_seq += 1;   // the schedule it ends with
+    ctx->stats.steps += 1;
+    ctx->stats.sum_n_act += n_act;
+    r->steps += 1;
+    r->t = t;
+    r->n_act = n_act;
+}
+
 // Block steps until the next one would exceed t_limit, or max_steps of them,
 // with the step kernel: a schedule to begin with, then per small step the force
 // kernel with the predictor inside and the step kernel, both reading the
 // schedule on the device, and per larger step the predictor, force and split
 // reduction kernels and the step kernel.  The host reads each schedule as it
-// is published.
-nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t max_steps, int64_t *steps_out,
-                       int64_t *t_out, int64_t *n_act_out)
+// is published.  Returns with steps in flight when it fails; *r holds the steps
+// taken before those.
+nbody_status step_loop(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t max_steps, StepsTaken *r)
 {
     const nbody_config &c = ctx->cfg;
     int32_t *act = ws_at<int32_t>(ctx, ctx->lay.act);
@@ -793,32 +819,30 @@ nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t
     for (int k = 0; k < 6; ++k) in.d[k] = k <= c.order - 3 ? st->d[k] : nullptr;
     in.t_tick = st->t_tick;
 
-    int64_t seq = ++ctx->pub_seq, steps = 0, ahead = 0, allowed = kAheadLarge;
-    nbody_status s = NBODY_OK;
+    int64_t ahead = 0, allowed = kAheadLarge;
     sa.mode = nb::kStepSchedule;
-    sa.seq = seq;
+    sa.seq = ++ctx->pub_seq;
     // a value that became non-finite before the run ends it here: the small step
     // enqueued before its schedule is read leaves without effect
     sa.nonfinite = static_cast<unsigned long long>(ctx->stats.nonfinite);
     NB_HIP(nb::launch_step(sa, ctx->stream));
     for (;;) {
-        while (any_small && ahead < allowed && steps + ahead < max_steps) {
+        const int64_t seq = ctx->pub_seq;   // of the schedule of the next step
+        while (any_small && ahead < allowed && r->steps + ahead < max_steps) {
             NB_HIP(nb::launch_force_small_dev(c.order, c.precision, fa, in, sa.sc, sa.tab, t_limit, ctx->stream));
             sa.mode = nb::kStepSmall;
             NB_HIP(nb::launch_step(sa, ctx->stream));
             ++ahead;
         }
         nb::DevScalars h;
-        s = read_published(ctx, seq, &h);
+        nbody_status s = read_published(ctx, seq, &h);
         if (s == NBODY_OK && h.seq != seq) s = fail(NBODY_E_HIP, "the schedule of a block step was not published");
-        if (s == NBODY_OK) s = take_counters(ctx, h, *t_out);
-        if (s != NBODY_OK || steps == max_steps) break;
+        if (s == NBODY_OK) s = take_counters(ctx, h, r->t);
+        if (s != NBODY_OK || r->steps == max_steps) return s;
         const int64_t t_next = h.t_next, n_act = h.n_act;
-        if (n_act <= 0 || n_act > c.n) {
-            s = fail(NBODY_E_STATE, "scheduler found %lld active particles", (long long)n_act);
-            break;
-        }
-        if (t_next > t_limit) break;
+        if (n_act <= 0 || n_act > c.n)
+            return fail(NBODY_E_STATE, "scheduler found %lld active particles", (long long)n_act);
+        if (t_next > t_limit) return NBODY_OK;
         if (n_act <= nb::kSmallMax && sa.tab.n_split[n_act - 1] > 0) {
             // the first of the steps enqueued ahead is this one
             --ahead;
@@ -833,7 +857,7 @@ nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t
             if (n_act > nb::kStepGather) NB_HIP(nb::launch_step_gather(sa.w, c.n, sa.sc, ctx->stream));
             double *f[4] = {F, F + 3 * n_act, c.order >= 6 ? F + 6 * n_act : nullptr, c.order >= 8 ? F + 9 * n_act : nullptr};
             s = run_predict_force(ctx, st, t_next, n_act, act, f[0], f[1], f[2], f[3], nullptr, nullptr);
-            if (s != NBODY_OK) break;
+            if (s != NBODY_OK) return s;
             if (pn && !pn_inside)
                 NB_HIP(nb::launch_pn(c, *st, st->t_tick, t_next, act, n_act, f[0], f[1], f[2], f[3], ctx->stream));
             nb::StepArgs big = sa;
@@ -841,19 +865,28 @@ nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t
             for (int k = 0; k < 4; ++k) big.f[k] = f[k];
             NB_HIP(nb::launch_step(big, ctx->stream));
         }
-        seq = ++ctx->pub_seq;
-        ++steps;
-        ctx->stats.steps += 1;
-        ctx->stats.sum_n_act += n_act;
-        *t_out = t_next;
-        *n_act_out = n_act;
+        count_step(ctx, t_next, n_act, r);
     }
-    *steps_out = steps;
-    if (s == NBODY_OK) {
-        NB_HIP(hipStreamSynchronize(ctx->stream));
-    } else if (hipStreamSynchronize(ctx->stream) == hipSuccess) {
-        // schedules of steps in flight that were not read
-        for (int k = 0; k < nb::kPubSlots; ++k) clear_published(ctx->pub_host + k);
+}
+
+// The same with nothing left in flight, and all steps taken in *r.
+nbody_status run_steps(nbody_ctx *ctx, nbody_state *st, int64_t t_limit, int64_t max_steps, StepsTaken *r)
+{
+    nbody_status s = forget_unread(ctx);
+    if (s != NBODY_OK) return s;
+    s = step_loop(ctx, st, t_limit, max_steps, r);
+    const hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess)
+        return s != NBODY_OK ? s : fail(NBODY_E_HIP, "block steps: %s", hipGetErrorString(e));
+    if (s != NBODY_OK) {
+        // steps enqueued ahead whose schedule was not read any more: each has
+        // published the one after it
+        while (slot(ctx, ctx->pub_seq + 1)->seq == ctx->pub_seq + 1) {
+            const nb::HostScalars h = *slot(ctx, ctx->pub_seq);
+            if (h.seq != ctx->pub_seq || h.t_next == nb::kPubEmpty) break;
+            ctx->stats.interactions += double(h.n_act) * double(ctx->cfg.n);
+            count_step(ctx, h.t_next, h.n_act, r);
+        }
     }
     return s;
 }
@@ -869,9 +902,14 @@ nbody_status nbody_step(nbody_ctx *ctx, nbody_state *st, int64_t *t_tick_out, in
     if (!ctx) return fail(NBODY_E_INVALID, "ctx is NULL");
     nbody_status s = check_state(ctx, st);
     if (s != NBODY_OK) return s;
-    int64_t t = 0, na = 0, prev = 0, one = 0;
+    int64_t t = 0, na = 0, prev = 0;
     bool stepped = false;
-    if (steps_by_kernel(ctx)) s = run_steps(ctx, st, INT64_MAX, 1, &one, &t, &na);
+    if (steps_by_kernel(ctx)) {
+        StepsTaken r{};
+        s = run_steps(ctx, st, INT64_MAX, 1, &r);
+        t = r.t;
+        na = r.n_act;
+    }
     else s = step_impl(ctx, st, INT64_MAX, true, &t, &na, &stepped, &prev);
     if (s != NBODY_OK) return s;
     if (t_tick_out) *t_tick_out = t;
@@ -889,7 +927,10 @@ nbody_status nbody_run(nbody_ctx *ctx, nbody_state *st, int64_t t_end_tick, int6
     int64_t steps = 0, t = 0, na = 0, prev = 0;
     bool stepped = true;
     if (steps_by_kernel(ctx) && max_steps > 0) {
-        s = run_steps(ctx, st, t_end_tick, max_steps, &steps, &prev, &na);
+        StepsTaken r{};
+        s = run_steps(ctx, st, t_end_tick, max_steps, &r);
+        steps = r.steps;
+        prev = r.t;
         stepped = false;   // its counters are read
     }
     else while (steps < max_steps) {

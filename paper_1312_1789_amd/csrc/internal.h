@@ -339,7 +339,8 @@ struct nbody_ctx {
     int device;
     nb::HostScalars *pub_host;        // pinned host copy of the scheduler result (null: copy path)
     nb::HostScalars *pub_dev;         // its device address
-    int64_t pub_seq;
+    int64_t pub_seq;                  // the last schedule's number, and that of the last one read from its slot
+    int64_t pub_read;
     bool predicted;
     bool fuse;                        // predictor folded into the wave j-split force (nbody_set_fusion)
     int ni, block, n_split, jpath;   // launch shape fixed by nbody_set_launch (when manual)

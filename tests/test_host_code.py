@@ -70,6 +70,7 @@ def _with_fake_hip(tmp_path, program):
     head = ("import ctypes as C, json, sys\n"
             "fake = C.CDLL(%r, mode=C.RTLD_GLOBAL)\n"
             "fake.fake_launches.restype = C.c_char_p\n"
+            "fake.fake_steps.restype = C.c_int64\n"
             "sys.path.insert(0, %r)\n"
             "from paper_1312_1789_amd import abi\n"
             "assert 'torch' not in sys.modules\n" % (lib, build_lib.ROOT))
@@ -109,3 +110,45 @@ def test_wave_split_launches_within_limits(tmp_path):
         rows = 64 if fuse else 16
         assert ("small" in name) == (fuse == 1)
         assert gx * rows >= n_act and gy <= 65535 and gz == 1, (name, n_act, gx, gy)
+
+
+FAILED_LAUNCHES = """
+n = 1024
+cfg = abi.nbody_config(4, abi.NBODY_FP64, n, 0, 1e-8, 0.01, 0.01, 3, 20, 0, 0.0, 0)
+size = abi.nbody_workspace_size(cfg)
+import numpy as np
+ws = np.zeros(size + 256, np.uint8)   # "device" memory, which the stand-in's step kernel writes
+at = (ws.ctypes.data + 255) // 256 * 256
+ctx = abi.nbody_create(cfg, at, size, 0)
+st = abi.nbody_state(at, at, at, (C.c_void_p * 6)(at, at), at, at)
+lib, seen = abi.lib(), []
+def run(max_steps):
+    steps, t = C.c_int64(-1), C.c_int64(-1)
+    before = fake.fake_steps()
+    rc = lib.nbody_run(ctx, C.byref(st), C.c_int64(1 << 60), C.c_int64(max_steps), C.byref(steps), C.byref(t))
+    s = abi.nbody_get_stats(ctx)
+    return [rc, steps.value, t.value, fake.fake_steps() - before, fake.fake_steps(), fake.fake_queued(), s.steps]
+for n_act in (1, 700):      # steps enqueued ahead, and steps sized by the host
+    for fail_at in range(1, 26):
+        fake.fake_script(C.c_int64(n_act), fail_at)
+        seen.append(run(5))
+        fake.fake_script(C.c_int64(n_act), 0)
+        seen.append(run(3))
+print(json.dumps(seen))
+"""
+
+
+def test_steps_after_a_failed_launch(tmp_path):
+    """A launch of a run that fails, each in turn: the call reports the error and
+    the steps that were taken, steps enqueued ahead included, with nothing left in
+    flight; the next run starts from a schedule of its own, not from one that
+    a step enqueued ahead published for the run before."""
+    seen = _with_fake_hip(tmp_path, FAILED_LAUNCHES)
+    failed = [s for s in seen if s[0] != 0]
+    assert len(failed) >= 20 and all(s[0] == -2 for s in failed)
+    for rc, steps, t, taken, total, queued, counted in seen:
+        assert (steps, counted, queued) == (taken, total, 0)
+        assert t == (total if steps else 0)
+        if rc == 0:
+            assert steps in (3, 5)
+    assert any(0 < s[1] < 5 for s in failed)
