@@ -280,15 +280,43 @@ k_reduce(const double *__restrict__ part, int64_t n_act, int n_split, double *__
     if (o) o[(c % 3) * n_act + q] = s;
 }
 
+// Lane l of the L that share a sum over groups of GS consecutive partials
+// src[0..n): groups l, l + L, ..., each added in order, sixteen loads in flight
+// together (the zeros past the end change nothing).
+template <int L, int GS>
+__device__ __forceinline__ double lane_group_sum(const double *__restrict__ src, int l, int n)
+{
+    constexpr int U = 16 / GS;
+    double s = 0.0;
+    for (int k = l; k * GS < n; k += U * L) {
+        double v[U][GS];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int g = 0; g < GS; ++g) {
+                const int at = (k + u * L) * GS + g;
+                v[u][g] = at < n ? src[at] : 0.0;
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            double t = 0.0;
+#pragma unroll
+            for (int g = 0; g < GS; ++g) t += v[u][g];
+            s += t;
+        }
+    }
+    return s;
+}
+
 // Sum of kernel C's partial results (split-fastest), in the order of the kernel
 // that predicts inside: groups of gs consecutive splits first, each in order,
 // then lane l of an output's L lanes adds groups l, l + L, ... and the lanes
 // are folded as in k_reduce.
 template <int P, int L>
 __global__ void __launch_bounds__(256)
-k_reduce_groups(const double *__restrict__ part, int64_t n_act, int n_split, int gs, int ng,
-                double *__restrict__ o_acc, double *__restrict__ o_jrk, double *__restrict__ o_snp,
-                double *__restrict__ o_crk, double *__restrict__ o_pot)
+k_reduce_groups(const double *__restrict__ part, int64_t n_act, int n_split, int gs, double *__restrict__ o_acc,
+                double *__restrict__ o_jrk, double *__restrict__ o_snp, double *__restrict__ o_crk,
+                double *__restrict__ o_pot)
 {
     constexpr int NV = 3 * (P / 2);
     const int64_t g = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / L;   // output index
@@ -300,15 +328,9 @@ k_reduce_groups(const double *__restrict__ part, int64_t n_act, int n_split, int
     const double *src = part + (int64_t(c) * n_act + q) * n_split;
     double s = 0.0;
     if (valid)
-        for (int k = l; k < ng; k += L) {
-            double v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = (u < gs && k * gs + u < n_split) ? src[k * gs + u] : 0.0;
-            double t = 0.0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) t += v[u];   // the zeros past a group's end change nothing
-            s += t;
-        }
+        s = gs == 2   ? lane_group_sum<L, 2>(src, l, n_split)
+            : gs == 4 ? lane_group_sum<L, 4>(src, l, n_split)
+                      : lane_group_sum<L, 8>(src, l, n_split);
 #pragma unroll
     for (int m = L / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
     if (!valid || l != 0) return;
@@ -321,23 +343,6 @@ k_reduce_groups(const double *__restrict__ part, int64_t n_act, int n_split, int
     if (o) o[(c % 3) * n_act + q] = s;
 }
 
-template <int P>
-hipError_t launch_reduce_groups(const ForceArgs &a, int n_split, hipStream_t s)
-{
-    const int gs = small_group(a.n_act), ng = (n_split + gs - 1) / gs;
-    const int64_t outs = a.n_act * (3 * (P / 2) + (a.out[4] ? 1 : 0));
-    const int L = reduce_lanes(ng);
-    const unsigned blocks = unsigned((outs * L + 255) / 256);
-#define NB_RED(LL) hipLaunchKernelGGL((k_reduce_groups<P, LL>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
-                                      gs, ng, a.out[0], a.out[1], a.out[2], a.out[3], a.out[4])
-    if (L == 1) NB_RED(1);
-    else if (L == 4) NB_RED(4);
-    else if (L == 16) NB_RED(16);
-    else NB_RED(64);
-#undef NB_RED
-    return hipGetLastError();
-}
-
 template <int P, bool SF, int C0 = 0>
 hipError_t launch_reduce(const ForceArgs &a, int n_split, hipStream_t s)
 {
@@ -347,6 +352,24 @@ hipError_t launch_reduce(const ForceArgs &a, int n_split, hipStream_t s)
     const unsigned blocks = unsigned((outs * L + 255) / 256);
 #define NB_RED(LL) hipLaunchKernelGGL((k_reduce<P, LL, SF, C0>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
                                       a.out[0], a.out[1], a.out[2], a.out[3], a.out[4])
+    if (L == 1) NB_RED(1);
+    else if (L == 4) NB_RED(4);
+    else if (L == 16) NB_RED(16);
+    else NB_RED(64);
+#undef NB_RED
+    return hipGetLastError();
+}
+
+template <int P>
+hipError_t launch_reduce_groups(const ForceArgs &a, int n_split, hipStream_t s)
+{
+    const int gs = small_group(a.n_act, n_split), ng = (n_split + gs - 1) / gs;
+    if (gs == 1) return launch_reduce<P, true>(a, n_split, s);
+    const int64_t outs = a.n_act * (3 * (P / 2) + (a.out[4] ? 1 : 0));
+    const int L = reduce_lanes(ng);
+    const unsigned blocks = unsigned((outs * L + 255) / 256);
+#define NB_RED(LL) hipLaunchKernelGGL((k_reduce_groups<P, LL>), dim3(blocks), dim3(256), 0, s, a.part, a.n_act, n_split, \
+                                      gs, a.out[0], a.out[1], a.out[2], a.out[3], a.out[4])
     if (L == 1) NB_RED(1);
     else if (L == 4) NB_RED(4);
     else if (L == 16) NB_RED(16);

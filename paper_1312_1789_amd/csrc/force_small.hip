@@ -32,14 +32,14 @@ constexpr int kSlots = 128;                // (split, row) pairs of a workgroup,
 // FP32 sums), R = 64 / (JS G) rows fill the rest of the wave, G splits where the
 // rows would fill half of it only; T waves take the same splits for T tiles of
 // 16 rows each and share the predicted particles through LDS (each predicts one
-// tile of 64 in T).
+// tile of 64 in T).  gs splits (small_group) make gs T / G waves; others of the
+// workgroup (a launch sized for another row count) have nothing to do.
 template <int JS_, int G_, int T_> struct Cut {
     static constexpr int JS = JS_, G = G_, T = T_;
     static constexpr int R = 64 / (JS * G);           // rows per wave
-    static constexpr int kUsed = G == 2 ? kWaves / 2 : kWaves;   // waves at work
-    static constexpr int kSplits = kUsed / T * G;     // splits per workgroup
     static constexpr int kRows = R * T;               // rows per workgroup
-    static_assert(kSplits * kRows <= kSlots, "slots");
+    static constexpr int kMost = T == 1 ? 8 : 8 / T;  // splits per workgroup, at most
+    static_assert(kMost * kRows <= kSlots && kMost * T / G <= kWaves, "slots and waves");
 };
 using Cut1 = Cut<64, 1, 1>;
 using Cut2 = Cut<16, 2, 1>;
@@ -48,16 +48,15 @@ using Cut8 = Cut<4, 2, 1>;
 using Cut16 = Cut<4, 1, 1>;
 using Cut32 = Cut<4, 1, 2>;
 using Cut64 = Cut<4, 1, 4>;   // and more rows, 64 to a workgroup
-static_assert(Cut1::kSplits == 8 && Cut2::kSplits == 8 && Cut4::kSplits == 8 && Cut8::kSplits == 8 &&
-              Cut16::kSplits == 8 && Cut32::kSplits == 4 && Cut64::kSplits == 2, "small_group below");
+static_assert(Cut16::kMost == 8 && Cut32::kMost == 4 && Cut64::kMost == 2, "small_group");
 
-// One workgroup: rows [row0, row0 + kRows) against the splits from s0 on.
+// One workgroup: rows [row0, row0 + kRows) against the splits [s0, s0 + gs).
 // The sums of (local split, local row, component) end in red[c][slot], slot
 // = split * kRows + row.
 template <class C, class Pol, int P, int PREC>
 __device__ __forceinline__ void walk(const PredIn &in, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
                                      typename Pol::ET e2, int64_t n_hard, int64_t j_chunk, int n_split, int s0,
-                                     int64_t row0, typename Pol::Rec *tiles, double (*red)[kSlots])
+                                     int gs, int64_t row0, typename Pol::Rec *tiles, double (*red)[kSlots])
 {
     using Rec = typename Pol::Rec;
     using Part = typename Pol::Part;
@@ -67,14 +66,15 @@ __device__ __forceinline__ void walk(const PredIn &in, int64_t n, const int32_t 
     constexpr int UN = sizeof(Rec) > 80 ? 1 : (sizeof(Rec) > 64 ? 2 : 4);   // as many records as registers hold
     constexpr int NV = 3 * (P / 2);
     constexpr double kInvTick = 1.0 / double(kTicksPerUnit);
-    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int g = lane / (JS * R), r = (lane / JS) % R, sl = lane % JS;
     const int sub = wave % T, grp = wave / T;
-    const bool used = wave < C::kUsed;
+    const bool used = wave * G < gs * T;   // uniform over the wave
     const int sw = s0 + grp * G;         // the wave's first split
     const int64_t q = row0 + sub * R + r;
     const int64_t qq = q < n_act ? q : n_act - 1;   // padding rows recompute the last row; never stored
     double acc[13];
+    const int64_t steps = (j_chunk + 64 * T - 1) / (64 * T);   // the same for every wave
     if (used) {
         const int64_t ia = act[qq];
         const int64_t i = (ia >= 0 && ia < n) ? ia : 0;
@@ -115,7 +115,6 @@ __device__ __forceinline__ void walk(const PredIn &in, int64_t n, const int32_t 
         // (loaded in place where the registers would not hold it beside the pair loop's)
         constexpr bool kAhead = T == 1 || P == 4 || (P == 6 && std::is_same<Part, float>::value);
         if constexpr (kAhead) fetch(0);
-        const int64_t steps = (j_chunk + 64 * T - 1) / (64 * T);   // the same for every wave
         for (int64_t step = 0; step < steps; ++step) {
             Rec mine[G];
             if constexpr (!kAhead) fetch(step);
@@ -184,6 +183,11 @@ __device__ __forceinline__ void walk(const PredIn &in, int64_t n, const int32_t 
         for (int m = JS / 2; m > 0; m >>= 1)
 #pragma unroll
             for (int c = 0; c < 13; ++c) acc[c] += __shfl_xor(acc[c], m, 64);
+    } else if constexpr (T > 1) {
+        for (int64_t step = 0; step < steps; ++step) {   // the barriers of the others
+            __syncthreads();
+            __syncthreads();
+        }
     }
     __syncthreads();   // the tiles are no longer read: red shares their LDS
     if (used && sl == 0) {
@@ -204,7 +208,7 @@ __device__ __forceinline__ void put(int64_t n_act, int64_t row0, int splits, int
     constexpr int NV = 3 * (P / 2), NC = NV + (Pol::kWithPot ? 1 : 0);
     const int64_t left = n_act - row0;
     const int rows = left < C::kRows ? int(left) : C::kRows;
-    for (int e = int(threadIdx.x); e < rows * NC; e += kWaves * 64) {
+    for (int e = int(threadIdx.x); e < rows * NC; e += int(blockDim.x)) {
         const int c = e / rows, row = e - c * rows;
         double s = 0.0;
         for (int k = 0; k < splits; ++k) s += red[c][k * C::kRows + row];
@@ -217,27 +221,31 @@ __device__ __forceinline__ void put(int64_t n_act, int64_t row0, int splits, int
 
 template <class C, class Pol, int P, int PREC>
 __device__ __forceinline__ void small_run(const PredIn &in, int64_t n, const int32_t *act, int64_t n_act, double eps2,
-                                          int64_t n_hard, int64_t j_chunk, int n_split, bool to_part, const OutPtrs &o,
-                                          double *part, typename Pol::Rec *tiles, double (*red)[kSlots])
+                                          int64_t n_hard, int64_t j_chunk, int n_split, int gs, bool to_part,
+                                          const OutPtrs &o, double *part, typename Pol::Rec *tiles, double (*red)[kSlots])
 {
-    const int ng = (n_split + C::kSplits - 1) / C::kSplits;
+    const int ng = (n_split + gs - 1) / gs;
     const int grp = int(blockIdx.y);
     if (grp >= ng) return;
     const int64_t row0 = int64_t(blockIdx.x) * 64;
-    const int s0 = grp * C::kSplits;
-    walk<C, Pol, P, PREC>(in, n, act, n_act, typename Pol::ET(eps2), n_hard, j_chunk, n_split, s0, row0, tiles, red);
-    put<C, Pol, P>(n_act, row0, n_split - s0 < C::kSplits ? n_split - s0 : C::kSplits, grp, ng, !to_part && ng == 1, o,
-                   part, red);
+    const int s0 = grp * gs;
+    walk<C, Pol, P, PREC>(in, n, act, n_act, typename Pol::ET(eps2), n_hard, j_chunk, n_split, s0, gs, row0, tiles, red);
+    put<C, Pol, P>(n_act, row0, n_split - s0 < gs ? n_split - s0 : gs, grp, ng, !to_part && ng == 1, o, part, red);
 }
 
 // Bound by HBM for up to four rows (every particle's stored state is read
 // once: n = 2^20, order 6, 168 MB) and by VALU issue and latency for more, where
-// a particle meets up to 16 rows in a wave.  Eight waves per workgroup, whose
+// a particle meets up to 16 rows in a wave.  Up to eight waves per workgroup, whose
 // splits' sums are added in LDS, leave an eighth of the partial sums to the
 // reduction, and up to 8 rows share a wave between two splits instead of leaving
 // half its lanes to padding rows (n = 2^20, 5 rows, MIXED order 6: 53.4 us for the
 // call with one wave per workgroup and 16 rows to it, 43.8 now; the state alone
-// takes 33 us to read at the rate of a large copy).  With `dev` the active set, its time and its split come from the
+// takes 33 us to read at the rate of a large copy).  Where eight splits to a
+// workgroup would leave CUs without one, a workgroup takes fewer (small_group), and
+// a wave one: n = 3000, one row MIXED order 8 14.1 -> 8.8 us for the call, n = 600000,
+// one row 44.9 -> 23.8, n = 500, 5 rows MIXED order 6 30.0 -> 22.1; a bound of 512
+// workgroups instead of 256 loses 10% at n = 120000.  With `dev` the active set,
+// its time and its split come from the
 // device (the block step that the scheduler has just found), and nothing is
 // done when that step is not one for this kernel.
 template <class Pol, int P, int PREC>
@@ -261,14 +269,18 @@ k_force_small(PredIn in, int64_t n, const int32_t *__restrict__ act, int64_t n_a
         n_split = of_lane(sp, n_act - 1);
         j_chunk = of_lane(jc, n_act - 1);
     }
-#define NB_SMALL(CUT) small_run<CUT, Pol, P, PREC>(in, n, act, n_act, eps2, n_hard, j_chunk, n_split, dev != nullptr, \
+#define NB_SMALL(CUT) small_run<CUT, Pol, P, PREC>(in, n, act, n_act, eps2, n_hard, j_chunk, n_split, gs, dev != nullptr, \
                                                    o, part, tiles, red)
-    // (the registers hold two splits' states in flight at order 4, and at order 6 beside FP32 sums)
+    const int gs = small_group(n_act, n_split);
+    // Two splits to a wave where all waves would be more than the chip holds two to
+    // a SIMD (gs is 8 then), and the registers hold two splits' states in flight:
+    // order 4, and order 6 beside FP32 sums.
     constexpr bool kTwo = P == 4 || (P == 6 && std::is_same<typename Pol::Part, float>::value);
+    const bool two = kTwo && gs == 8;
     if (n_act <= 1) NB_SMALL(Cut1);
-    else if (kTwo && n_act <= 2) NB_SMALL(Cut2);
+    else if (two && n_act <= 2) NB_SMALL(Cut2);
     else if (n_act <= 4) NB_SMALL(Cut4);
-    else if (kTwo && n_act <= 8) NB_SMALL(Cut8);
+    else if (two && n_act <= 8) NB_SMALL(Cut8);
     else if (n_act <= 16) NB_SMALL(Cut16);
     else if (n_act <= 32) NB_SMALL(Cut32);
     else NB_SMALL(Cut64);
@@ -280,7 +292,8 @@ struct Launch {
     const PredIn *in;
     int n_split;
     int64_t j_chunk;
-    unsigned tiles, groups;   // the grid: tiles of 64 rows (up to 2^20) by groups of splits (up to 2^15)
+    unsigned tiles, groups;   // the grid: tiles of 64 rows (up to 2^20) by groups of splits (up to 2^16)
+    int waves;                // per workgroup
     const DevScalars *dev;
     const SmallTable *tab;
     int64_t t_limit;
@@ -291,7 +304,7 @@ hipError_t run(const Launch &L, hipStream_t s)
 {
     const ForceArgs &a = *L.a;
     const OutPtrs o{{a.out[0], a.out[1], a.out[2], a.out[3], a.out[4]}};
-    hipLaunchKernelGGL((k_force_small<Pol, P, PREC>), dim3(L.tiles, L.groups), dim3(kWaves * 64), 0, s, *L.in, a.n, a.act,
+    hipLaunchKernelGGL((k_force_small<Pol, P, PREC>), dim3(L.tiles, L.groups), dim3(unsigned(L.waves) * 64u), 0, s, *L.in, a.n, a.act,
                        a.n_act, a.eps2, a.n_hard, L.j_chunk, L.n_split, o, a.part, L.dev, *L.tab, L.t_limit);
     return hipGetLastError();
 }
@@ -321,9 +334,10 @@ hipError_t run_order(int order, int precision, const Launch &L, hipStream_t s)
     }
 }
 
-}  // namespace
+// Waves of a workgroup that adds gs splits, at most (two splits to a wave take half).
+int small_waves(int64_t n_act, int gs) { return n_act <= 16 ? gs : (n_act <= 32 ? 2 * gs : 4 * gs); }
 
-int small_group(int64_t n_act) { return n_act <= 16 ? 8 : (n_act <= 32 ? 4 : 2); }
+}  // namespace
 
 hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const PredIn &in, hipStream_t s,
                              UsedShape *used)
@@ -332,9 +346,9 @@ hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const
     int64_t j_chunk = 0;
     split_shape(precision, a.n, a.n_act, a.n_split, a.fine, 1, 3, a.part_rows, &n_split, &j_chunk);
     if (used) *used = UsedShape{1, 64, n_split, 3};
-    const int gs = small_group(a.n_act), ng = (n_split + gs - 1) / gs;
+    const int gs = small_group(a.n_act, n_split), ng = (n_split + gs - 1) / gs;
     const SmallTable none{};
-    const Launch L{&a, &in, n_split, j_chunk, unsigned((a.n_act + 63) / 64), unsigned(ng), nullptr, &none, 0};
+    const Launch L{&a, &in, n_split, j_chunk, unsigned((a.n_act + 63) / 64), unsigned(ng), small_waves(a.n_act, gs), nullptr, &none, 0};
     const hipError_t e = run_order(order, precision, L, s);
     if (e != hipSuccess || ng == 1) return e;
     return launch_split_reduce_sf(order, a, ng, s);
@@ -343,12 +357,14 @@ hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const
 hipError_t launch_force_small_dev(int order, int precision, const ForceArgs &a, const PredIn &in,
                                   const DevScalars *dev, const SmallTable &tab, int64_t t_limit, hipStream_t s)
 {
-    int groups = 1;
+    int groups = 1, waves = 1;
     for (int k = 0; k < kSmallMax; ++k) {
-        const int gs = small_group(k + 1), ng = (tab.n_split[k] + gs - 1) / gs;
+        if (tab.n_split[k] == 0) continue;
+        const int gs = small_group(k + 1, tab.n_split[k]), ng = (tab.n_split[k] + gs - 1) / gs;
         if (ng > groups) groups = ng;
+        if (small_waves(k + 1, gs) > waves) waves = small_waves(k + 1, gs);
     }
-    const Launch L{&a, &in, 0, 0, 1u, unsigned(groups), dev, &tab, t_limit};
+    const Launch L{&a, &in, 0, 0, 1u, unsigned(groups), waves, dev, &tab, t_limit};
     return run_order(order, precision, L, s);
 }
 

@@ -190,12 +190,22 @@ hipError_t launch_force_pred(int order, int precision, const ForceArgs &a, const
                              UsedShape *used);
 // The same for the step that the scheduler has written to dev (active set
 // a.act, split from tab); leaves the partial sums of each group of
-// small_group(n_act) splits in a.part, and does nothing when the step is not
+// small_group splits in a.part, and does nothing when the step is not
 // small or past t_limit.
 hipError_t launch_force_small_dev(int order, int precision, const ForceArgs &a, const PredIn &in,
                                   const DevScalars *dev, const SmallTable &tab, int64_t t_limit, hipStream_t s);
-// Consecutive splits whose sums that kernel adds in one workgroup.
-int small_group(int64_t n_act);
+// Consecutive splits whose sums that kernel adds in one workgroup: as few as give
+// each of the 256 CUs a workgroup, at most 8 (4, 2: a split is then two or four
+// waves).  A CU takes some 40 GB/s from HBM or another XCD's L2, so that 8 splits
+// to a workgroup left calls of few splits waiting for a part of the chip.
+__host__ __device__ inline int small_group(int64_t n_act, int n_split)
+{
+    const int most = n_act <= 16 ? 8 : (n_act <= 32 ? 4 : 2);
+    const int64_t wgs = n_split * ((n_act + 63) / 64);
+    int gs = 1;
+    while (gs < most && wgs > 256 * gs) gs *= 2;
+    return gs;
+}
 
 // The end of a block step and the schedule of the next one (step.hip).
 constexpr int kStepBlock = 256;                    // particles (and threads) per workgroup

@@ -299,8 +299,8 @@ k_step(StepArgs a)
             double *fp[4];
             int64_t stride, row;
             if (a.mode == kStepSmall) {
-                const int gs = na <= 16 ? 8 : (na <= 32 ? 4 : 2);   // small_group
-                const int ng = (of_lane(sp, na - 1) + gs - 1) / gs;
+                const int nsp = of_lane(sp, na - 1), gs = small_group(na, nsp);
+                const int ng = (nsp + gs - 1) / gs;
                 const int L = reduce_lanes(ng);
                 if (L == 1) sum_rows<1, NV>(a.part, na, ng, q0, cnt, f);
                 else if (L == 4) sum_rows<4, NV>(a.part, na, ng, q0, cnt, f);

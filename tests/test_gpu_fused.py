@@ -85,6 +85,33 @@ def test_fused_equals_predict_then_force(block_case, order, precision):
     sim.close()
 
 
+@pytest.mark.parametrize("order, precision", [(4, "fp64"), (6, "mixed"), (8, "mixed"), (4, "ds")])
+def test_fused_split_groups(order, precision):
+    """Split counts at the edges of the rule that says how many splits a
+    workgroup of the fused kernel adds (1, 2, 4, 8: the next one from more than
+    256, 512 and 1024 workgroups on), for every cut of its waves: the same bits
+    as the predictor and the force kernel, whose reduction adds in that order."""
+    from paper_1312_1789_amd import Simulation
+    n = 128 * 2060
+    model = nbody_ics.plummer(n, 76)
+    d = nbody_ics.random_derivs(n, 77, order)
+    t, lv = random_block_state(n, 78)
+    T = int((t + (1 << (TICK_BITS - lv.astype(np.int64)))).min())
+    sim = Simulation(model.m, model.x, model.v, order=order, precision=precision, eps2=1e-8, n_hard=2)
+    sim.load_state(model.x, model.v, d, t, lv)
+    for n_split in (9, 255, 256, 257, 511, 515, 1030, 2060):
+        sim.set_launch(1, 64, n_split, 3)
+        for na in (1, 2, 3, 8, 16, 17, 32, 33, 64, 65):
+            act = torch.as_tensor(nbody_ics.active_subset(n, na, 760 + na), device=sim.device)
+            sim.set_fusion(True)
+            fused = {k: v.clone() for k, v in sim.predict_force(T, act, with_pot=na % 2 == 0).items()}
+            sim.set_fusion(False)
+            plain = sim.predict_force(T, act, with_pot=na % 2 == 0)
+            for k in KEYS[order] + (["pot"] if na % 2 == 0 else []):
+                assert torch.equal(fused[k], plain[k]), (n_split, na, k)
+    sim.close()
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed", "ds"])
 @pytest.mark.parametrize("order", [4, 6, 8])
 def test_fused_force_parity(block_case, order, precision):
