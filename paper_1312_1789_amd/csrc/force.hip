@@ -19,8 +19,8 @@ namespace nb {
 namespace {
 
 // --------------------------------------------------------------------------
-// Pieces shared by both force kernels.  blockIdx.x: i-tile of blockDim.x * NI
-// active particles (lane t holds rows t, t + blockDim.x, ...); blockIdx.y:
+// Pieces shared by both force kernels.  A workgroup (place) has an i-tile of
+// blockDim.x * NI active particles (lane t holds rows t, t + blockDim.x, ...) and a
 // j-split [split * j_chunk, min(n, (split+1) * j_chunk)).  Pairs with both
 // indices below n_hard are unsoftened and their self pair is masked; above
 // n_hard the self pair is evaluated with eps2 > 0 (its acceleration and
@@ -33,6 +33,40 @@ namespace {
 // or four per output) row-fastest, part[split][component][row], so that a
 // workgroup's stores are coalesced.
 constexpr int kSplitFastestAbove = 32;
+
+// Which i-tile and split a workgroup has.  The dispatcher places workgroup g on
+// XCD g mod 8.  Stored split-fastest, 16 consecutive splits of a row share a
+// memory line, and 8-byte stores to one line from several XCDs reach memory one by
+// one; so each unit of 2^shift consecutive splits of an i-tile goes to one XCD, as
+// large (up to 16) as leaves 256 units.  (Not on the scalar path, whose splits are
+// long: there the tiles of a split had better run side by side, n = 262144, 3001 rows
+// 932 us in the plain order, 942 by units.)  In the plain order the splits of a tile lie
+// on one XCD only where 8 divides the number of tiles: n = 32768, 17 tiles of 64 rows
+// MIXED order 4, 256 splits: 60 us, 47 now (16 tiles: 46 and 45).
+constexpr int kXcd = 8;
+struct Places {
+    unsigned tiles, units;
+    int shift;
+};
+
+Places places_for(int jpath, int64_t tiles, int n_split)
+{
+    Places p{unsigned(tiles), 0, 0};
+    while (jpath == 2 && n_split > kSplitFastestAbove && p.shift < 4 && tiles * n_split >= (int64_t(256) << (p.shift + 1))) ++p.shift;
+    p.units = p.tiles * ((unsigned(n_split) + (1u << p.shift) - 1u) >> p.shift);
+    return p;
+}
+unsigned place_grid(const Places &p) { return (p.units + kXcd - 1) / kXcd * kXcd << p.shift; }
+
+// False for a workgroup past the last unit or split.
+__device__ __forceinline__ bool place(const Places &p, int n_split, int64_t *tile, int *split)
+{
+    const unsigned slot = blockIdx.x / kXcd, u = (slot >> p.shift) * kXcd + blockIdx.x % kXcd;
+    const unsigned group = u / p.tiles;
+    *tile = u - group * p.tiles;
+    *split = int((group << p.shift) + (slot & ((1u << p.shift) - 1u)));
+    return u < p.units && *split < n_split;
+}
 
 template <class Pol, int P, int NI>
 __device__ __forceinline__ void store_rows(int64_t n_act, int64_t row0, int split, int n_split,
@@ -80,15 +114,17 @@ __global__ void __launch_bounds__(256)
 k_force(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
         double eps2, int64_t n_hard, int64_t j_chunk, int n_split, double *__restrict__ o_acc,
         double *__restrict__ o_jrk, double *__restrict__ o_snp, double *__restrict__ o_crk,
-        double *__restrict__ o_pot, double *__restrict__ part)
+        double *__restrict__ o_pot, double *__restrict__ part, Places places)
 {
     using Rec = typename Pol::Rec;
     using Part = typename Pol::Part;
     using ET = typename Pol::ET;
     const ET e2 = ET(eps2);
-    const int64_t row0 = int64_t(blockIdx.x) * blockDim.x * NI + threadIdx.x;
+    int64_t tile_i;
+    int split;
+    if (!place(places, n_split, &tile_i, &split)) return;
+    const int64_t row0 = tile_i * blockDim.x * NI + threadIdx.x;
     if (row0 - int64_t(threadIdx.x & 63) >= n_act) return;   // a wave of padding rows only (no barrier follows)
-    const int split = blockIdx.y;
     const int64_t j0 = int64_t(split) * j_chunk;
     const int64_t j1 = (j0 + j_chunk < n) ? j0 + j_chunk : n;
 
@@ -136,14 +172,16 @@ __global__ void __launch_bounds__(BLOCK)
 k_force_lds(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
             double eps2, int64_t n_hard, int64_t j_chunk, int n_split, double *__restrict__ o_acc,
             double *__restrict__ o_jrk, double *__restrict__ o_snp, double *__restrict__ o_crk,
-            double *__restrict__ o_pot, double *__restrict__ part)
+            double *__restrict__ o_pot, double *__restrict__ part, Places places)
 {
     using Rec = typename Pol::Rec;
     using ET = typename Pol::ET;
     __shared__ Rec tile[2][TILE];
     const ET e2 = ET(eps2);
-    const int64_t row0 = int64_t(blockIdx.x) * BLOCK * NI + threadIdx.x;
-    const int split = blockIdx.y;
+    int64_t tile_i;
+    int split;
+    if (!place(places, n_split, &tile_i, &split)) return;   // the whole workgroup
+    const int64_t row0 = tile_i * BLOCK * NI + threadIdx.x;
     const int64_t j0 = int64_t(split) * j_chunk;
     const int64_t j1 = (j0 + j_chunk < n) ? j0 + j_chunk : n;
 
@@ -388,7 +426,8 @@ hipError_t run(const ForceArgs &a, hipStream_t s, const Shape &sh)
 {
     const int64_t per_block = int64_t(sh.block) * NI;
     const int64_t tiles = (a.n_act + per_block - 1) / per_block;
-    const dim3 grid{unsigned(tiles), unsigned(sh.n_split), 1u};
+    const Places pl = places_for(sh.jpath, tiles, sh.n_split);
+    const dim3 grid{place_grid(pl), 1u, 1u};
     const auto *rec = static_cast<const typename Pol::Rec *>(a.rec);
 #define NB_FORCE_ARGS rec, a.n, a.act, a.n_act, a.eps2, a.n_hard, sh.j_chunk, sh.n_split, a.out[0], a.out[1], \
                       a.out[2], a.out[3], a.out[4], a.part
@@ -400,13 +439,13 @@ hipError_t run(const ForceArgs &a, hipStream_t s, const Shape &sh)
         else if (rw == 4) hipLaunchKernelGGL((k_force_ws<Pol, P, 4>), g3, dim3(64), 0, s, NB_FORCE_ARGS);
         else hipLaunchKernelGGL((k_force_ws<Pol, P, 16>), g3, dim3(64), 0, s, NB_FORCE_ARGS);
     } else if (sh.jpath == 1) {
-        hipLaunchKernelGGL((k_force<Pol, P, NI>), grid, dim3(sh.block), 0, s, NB_FORCE_ARGS);
+        hipLaunchKernelGGL((k_force<Pol, P, NI>), grid, dim3(sh.block), 0, s, NB_FORCE_ARGS, pl);
     } else if (sh.block == 64) {
-        hipLaunchKernelGGL((k_force_lds<Pol, P, NI, 64, 2, 64>), grid, dim3(64), 0, s, NB_FORCE_ARGS);
+        hipLaunchKernelGGL((k_force_lds<Pol, P, NI, 64, 2, 64>), grid, dim3(64), 0, s, NB_FORCE_ARGS, pl);
     } else if (sh.block == 128) {
-        hipLaunchKernelGGL((k_force_lds<Pol, P, NI, 128, 2, 128>), grid, dim3(128), 0, s, NB_FORCE_ARGS);
+        hipLaunchKernelGGL((k_force_lds<Pol, P, NI, 128, 2, 128>), grid, dim3(128), 0, s, NB_FORCE_ARGS, pl);
     } else {
-        hipLaunchKernelGGL((k_force_lds<Pol, P, NI, 256, 2, 128>), grid, dim3(256), 0, s, NB_FORCE_ARGS);
+        hipLaunchKernelGGL((k_force_lds<Pol, P, NI, 256, 2, 128>), grid, dim3(256), 0, s, NB_FORCE_ARGS, pl);
     }
 #undef NB_FORCE_ARGS
     hipError_t e = hipGetLastError();
@@ -451,9 +490,9 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
 //    three rounds, had cost 10-30% of it: n_act = n = 90000 MIXED order 6 11219
 //    us with 6 splits, 9280 with 23; n = 262144, n_act = 3001 994 with 171, 926
 //    with 683;
-//  - otherwise a MIXED row takes its FP32 chunks (128 particles) one to a wave, and
-//    two above 8192 waves (n = 262144, 400 rows order 4: 2048 partial sums a value
-//    cost 134 us for the call, 1024 127);
+//  - otherwise a MIXED row takes its FP32 chunks (128 particles) one to a wave (two
+//    cost 4 to 12% from 4096 waves on, 20 to 60% below; mean of orders 4 to 8 over n =
+//    8000 to 120000);
 //  - FP64 and DS sums have no chunks to keep, and a wave that walks 128
 //    particles alone on its SIMD is all latency (28 us at order 4, FP64, for
 //    any n): as few as 32 each, about 3072 waves, at most about 1250 splits (the
@@ -469,7 +508,7 @@ int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
         if (c < 256 && (precision != NBODY_FP64 || wt * n >= int64_t(16384) * 256)) c = 256;
         return c < 8192 ? c : 8192;
     }
-    if (precision == NBODY_MIXED) return wt * n >= int64_t(8192) * kMixedChunk ? 2 * kMixedChunk : kMixedChunk;
+    if (precision == NBODY_MIXED) return kMixedChunk;
     int64_t c = wt * n / 3072 > n / 1250 ? wt * n / 3072 : n / 1250;
     c = up(c, 32);
     return c < 32 ? 32 : (c > 128 ? 128 : c);
@@ -541,11 +580,10 @@ void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool 
 // 8 scalar 1150, LDS 970 us, order 4 with the potential 538 and 501; MIXED order 4 with it
 // 343 and 312; DS order 4 without it is the exception, 433 and 454); with few waves,
 // the LDS path, whose loads run ahead (n = 80000, 200 rows FP64 order 8: scalar
-// 107, LDS 91 us).  On the LDS path four waves share a tile where there are enough
-// rows for that (padded by an eighth at most) and three waves to a SIMD: tiles of
-// its own leave a wave's SIMD two to five waves (n = 20000, 4000 rows MIXED order 6 136
-// us with one wave to a workgroup, 118 with four, order 8 218 and 176; but n = 262144,
-// 201 rows FP64 order 8 234 and 249).
+// 107, LDS 91 us).  On the LDS path four waves share a tile where there are many
+// row tiles (padded by a sixteenth at most) and three waves to a SIMD: 2 to 5%
+// faster for 28 to 65 tiles (n = 20000, 4000 rows MIXED order 8 184 us with one wave to a
+// workgroup, 176 with four), but up to 40% slower with fewer rows or more padding.
 void default_shape(int precision, int order, bool pot, int64_t n, int64_t n_act, int *ni, int *block, int *jpath)
 {
     *ni = 1;
@@ -563,8 +601,9 @@ void default_shape(int precision, int order, bool pot, int64_t n, int64_t n_act,
         *jpath = 1;
         return;
     }
-    const int64_t c = default_chunk(precision, n, n_act, 1), waves = wt * ((n + c - 1) / c);
-    *block = wt >= 24 && waves >= 3072 ? 256 : 64;
+    const int64_t c = default_chunk(precision, n, n_act, 1);
+    const bool share = wt >= 24 && wt * ((n + c - 1) / c) >= 3072 && 16 * ((wt + 3) / 4 * 4) <= 17 * wt;
+    *block = share ? 256 : 64;
     *jpath = 2;
 }
 
@@ -581,10 +620,10 @@ hipError_t launch_force_high(const ForceArgs &a, hipStream_t s, UsedShape *used)
     sh.block = (a.block == 64 || a.block == 128) ? a.block : 256;
     split_shape(NBODY_FP64, a.n, a.n_act, a.n_split, a.fine, 1, 1, a.part_rows, &sh.n_split, &sh.j_chunk);
     if (used) *used = UsedShape{1, sh.block, sh.n_split, 1};
-    const dim3 grid{unsigned((a.n_act + sh.block - 1) / sh.block), unsigned(sh.n_split), 1u};
-    hipLaunchKernelGGL((k_force<PolF64High, 8, 1>), grid, dim3(sh.block), 0, s, static_cast<const RecF64<8> *>(a.rec),
+    const Places pl = places_for(1, (a.n_act + sh.block - 1) / sh.block, sh.n_split);
+    hipLaunchKernelGGL((k_force<PolF64High, 8, 1>), dim3(place_grid(pl)), dim3(sh.block), 0, s, static_cast<const RecF64<8> *>(a.rec),
                        a.n, a.act, a.n_act, a.eps2, a.n_hard, sh.j_chunk, sh.n_split, nullptr, nullptr, a.out[2],
-                       a.out[3], nullptr, a.part);
+                       a.out[3], nullptr, a.part, pl);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || sh.n_split == 1) return e;
     return sh.n_split > kSplitFastestAbove ? launch_reduce<8, true, PolF64High::kFirst>(a, sh.n_split, s)

@@ -327,6 +327,27 @@ def test_default_shapes(small_case, order, precision):
     sim.close()
 
 
+@pytest.mark.parametrize("order, precision", [(4, "mixed"), (8, "mixed"), (6, "ds"), (4, "fp64")])
+def test_units_of_splits(order, precision):
+    """Kernel B with its workgroups placed in units of consecutive splits (1 to
+    16 by the number of workgroups, from 33 splits on), at the edges of those
+    rules and with ragged last units: the bits of kernel A, whose order is plain."""
+    n = 128 * 520 + 11
+    model = nbody_ics.plummer(n, 1701)
+    sim = _sim(model, order, precision, 1e-8, 3, random_derivs(n, 1702, order))
+    for na in (1, 64 * 7 + 1, 64 * 8, 64 * 17 - 5):
+        act = torch.as_tensor(nbody_ics.active_subset(n, na, 1703 + na), device=sim.device)
+        for n_split in (32, 33, 61, 127, 260, 520):
+            sim.set_launch(1, 64, n_split, 1)
+            ref = {k: v.clone() for k, v in sim.force_block(act).items()}
+            for ni, block in ((1, 64), (1, 256), (2, 128)):
+                sim.set_launch(ni, block, n_split, 2)
+                out = sim.force_block(act)
+                for k in ["acc", "jrk", "snp", "crk"][: order // 2] + ["pot"]:
+                    assert torch.equal(out[k], ref[k]), (na, n_split, ni, block, k)
+    sim.close()
+
+
 def test_force_max_size_sampled():
     """The largest system the C-ABI accepts, n = 2^26 (Plummer, 4th order):
     4096 random active rows through the tiled kernels and 7 through the wave
