@@ -498,7 +498,9 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
 //    any n): as few as 32 each, about 3072 waves, at most about 1250 splits (the
 //    sum of the partials grows with them).  n = 1024, n_act = 100 FP64 order 4:
 //    20.2 us with 8 splits of 128, 9.1 with 32 of 32 (order 8: 40.9, 13.1); n =
-//    16384, n_act = 400: 26.0 with 128, 22.6 with 64.
+//    16384, n_act = 400: 26.0 with 128, 22.6 with 64.  But 128 where the 1024 SIMDs'
+//    waves then add up to fewer particles: n = 16000, 1000 rows DS order 6 59 us with
+//    three waves of 96 to a SIMD, 51 with two of 128.
 int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
 {
     const int64_t wt = (n_act + 64 * ni - 1) / (64 * ni);
@@ -511,7 +513,9 @@ int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
     if (precision == NBODY_MIXED) return kMixedChunk;
     int64_t c = wt * n / 3072 > n / 1250 ? wt * n / 3072 : n / 1250;
     c = up(c, 32);
-    return c < 32 ? 32 : (c > 128 ? 128 : c);
+    c = c < 32 ? 32 : (c > 128 ? 128 : c);
+    const auto rounds = [&](int64_t v) { return (wt * ((n + v - 1) / v) + 1023) / 1024 * v; };
+    return rounds(c) > rounds(128) ? 128 : c;
 }
 
 }  // namespace
