@@ -348,6 +348,27 @@ def test_units_of_splits(order, precision):
     sim.close()
 
 
+@pytest.mark.parametrize("n", [200000, 200001])
+def test_wave_split_limit(n):
+    """The largest system whose default is the wave j-split kernel for 33 to 64
+    rows (FP64, DS), and one more particle: both against one row per lane."""
+    model = nbody_ics.plummer(n, 1711)
+    for precision in ("fp64", "ds"):
+        sim = _sim(model, 4, precision, 1e-8, 0, random_derivs(n, 1712, 4))
+        for na in (32, 33, 64, 65):
+            act = torch.as_tensor(nbody_ics.active_subset(n, na, 1713), device=sim.device)
+            sim.set_launch(1, 64, 0, 1)
+            ref = {k: v.clone() for k, v in sim.force_block(act).items()}
+            fresh = _sim(model, 4, precision, 1e-8, 0, random_derivs(n, 1712, 4))
+            out = fresh.force_block(act)
+            assert (fresh.last_launch()[3] == 3) == (na <= (64 if n == 200000 else 32))
+            for k in ("acc", "jrk"):
+                st = err_stats(rel_err(out[k].cpu().numpy()[..., :na], ref[k].cpu().numpy()[..., :na]))
+                assert st["rms"] <= (1e-12 if precision == "fp64" else 2 * LOW_TOL[k]), (precision, na, k, st)
+            fresh.close()
+        sim.close()
+
+
 def test_force_max_size_sampled():
     """The largest system the C-ABI accepts, n = 2^26 (Plummer, 4th order):
     4096 random active rows through the tiled kernels and 7 through the wave
