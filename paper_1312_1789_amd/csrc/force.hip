@@ -34,40 +34,6 @@ namespace {
 // workgroup's stores are coalesced.
 constexpr int kSplitFastestAbove = 32;
 
-// Which i-tile and split a workgroup has.  The dispatcher places workgroup g on
-// XCD g mod 8.  Stored split-fastest, 16 consecutive splits of a row share a
-// memory line, and 8-byte stores to one line from several XCDs reach memory one by
-// one; so each unit of 2^shift consecutive splits of an i-tile goes to one XCD, as
-// large (up to 16) as leaves 256 units.  (Not on the scalar path, whose splits are
-// long: there the tiles of a split had better run side by side, n = 262144, 3001 rows
-// 932 us in the plain order, 942 by units.)  In the plain order the splits of a tile lie
-// on one XCD only where 8 divides the number of tiles: n = 32768, 17 tiles of 64 rows
-// MIXED order 4, 256 splits: 60 us, 47 now (16 tiles: 46 and 45).
-constexpr int kXcd = 8;
-struct Places {
-    unsigned tiles, units;
-    int shift;
-};
-
-Places places_for(int jpath, int64_t tiles, int n_split)
-{
-    Places p{unsigned(tiles), 0, 0};
-    while (jpath == 2 && n_split > kSplitFastestAbove && p.shift < 4 && tiles * n_split >= (int64_t(256) << (p.shift + 1))) ++p.shift;
-    p.units = p.tiles * ((unsigned(n_split) + (1u << p.shift) - 1u) >> p.shift);
-    return p;
-}
-unsigned place_grid(const Places &p) { return (p.units + kXcd - 1) / kXcd * kXcd << p.shift; }
-
-// False for a workgroup past the last unit or split.
-__device__ __forceinline__ bool place(const Places &p, int n_split, int64_t *tile, int *split)
-{
-    const unsigned slot = blockIdx.x / kXcd, u = (slot >> p.shift) * kXcd + blockIdx.x % kXcd;
-    const unsigned group = u / p.tiles;
-    *tile = u - group * p.tiles;
-    *split = int((group << p.shift) + (slot & ((1u << p.shift) - 1u)));
-    return u < p.units && *split < n_split;
-}
-
 template <class Pol, int P, int NI>
 __device__ __forceinline__ void store_rows(int64_t n_act, int64_t row0, int split, int n_split,
                                            double (*acc)[13], double *__restrict__ o_acc,
@@ -416,6 +382,12 @@ hipError_t launch_reduce_groups(const ForceArgs &a, int n_split, hipStream_t s)
     return hipGetLastError();
 }
 
+// Whether a launch places units of consecutive splits: its partial sums are
+// split-fastest.  Not on the scalar path, whose splits are long: there the tiles of
+// a split had better run side by side, n = 262144, 3001 rows 932 us in the plain
+// order, 942 by units.
+bool spread(int jpath, int n_split) { return jpath == 2 && n_split > kSplitFastestAbove; }
+
 struct Shape {
     int ni, block, n_split, jpath;
     int64_t j_chunk;
@@ -426,7 +398,7 @@ hipError_t run(const ForceArgs &a, hipStream_t s, const Shape &sh)
 {
     const int64_t per_block = int64_t(sh.block) * NI;
     const int64_t tiles = (a.n_act + per_block - 1) / per_block;
-    const Places pl = places_for(sh.jpath, tiles, sh.n_split);
+    const Places pl = places_for(tiles, sh.n_split, spread(sh.jpath, sh.n_split));
     const dim3 grid{place_grid(pl), 1u, 1u};
     const auto *rec = static_cast<const typename Pol::Rec *>(a.rec);
 #define NB_FORCE_ARGS rec, a.n, a.act, a.n_act, a.eps2, a.n_hard, sh.j_chunk, sh.n_split, a.out[0], a.out[1], \
@@ -628,7 +600,7 @@ hipError_t launch_force_high(const ForceArgs &a, hipStream_t s, UsedShape *used)
     sh.block = (a.block == 64 || a.block == 128) ? a.block : 256;
     split_shape(NBODY_FP64, a.n, a.n_act, a.n_split, a.fine, 1, 1, a.part_rows, &sh.n_split, &sh.j_chunk);
     if (used) *used = UsedShape{1, sh.block, sh.n_split, 1};
-    const Places pl = places_for(1, (a.n_act + sh.block - 1) / sh.block, sh.n_split);
+    const Places pl = places_for((a.n_act + sh.block - 1) / sh.block, sh.n_split, false);
     hipLaunchKernelGGL((k_force<PolF64High, 8, 1>), dim3(place_grid(pl)), dim3(sh.block), 0, s, static_cast<const RecF64<8> *>(a.rec),
                        a.n, a.act, a.n_act, a.eps2, a.n_hard, sh.j_chunk, sh.n_split, nullptr, nullptr, a.out[2],
                        a.out[3], nullptr, a.part, pl);

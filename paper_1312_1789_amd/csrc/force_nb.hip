@@ -12,7 +12,7 @@
 // (regular part) and over the neighbours (irregular part); the neighbour list
 // holds their indices in increasing order.
 //
-// Kernel 1, grid (i-tiles of kNbBlock rows, j-splits): each lane holds one
+// Kernel 1, a workgroup per i-tile of kNbBlock rows and j-split: each lane holds one
 // active row and walks its split in increasing j, adding the pair terms of
 // the non-neighbours (the neighbours are masked out of the same FMA sequence
 // as the full force) and appending the neighbours to its split's part of the
@@ -28,7 +28,7 @@
 // of two bytes (offsets in the split) where a split is short enough, so that the
 // scratch holds more splits.  The call at n = 131072, 1024 rows, lists of 128, MIXED
 // 167 -> 152 us (512 splits instead of 342), n = 262144, 2048 rows MIXED 510 -> 475, FP64
-// 716 -> 670, n = 8192, 64 rows MIXED 38 -> 32; n = 20000, 700 rows MIXED 46 -> 49.  One
+// 716 -> 670, n = 8192, 64 rows MIXED 38 -> 32.  One
 // scalar load of each record by the wave instead of LDS tiles: 206 us.  Kernel 2, one wave per
 // row: the regular partial sums added in split order, the split lists
 // concatenated, and the irregular part summed over the list (lanes take
@@ -123,14 +123,16 @@ __device__ __forceinline__ bool nb_pair(const typename DSIn<4>::I &i, const RecD
 template <class Pol, class SegT>
 __global__ void __launch_bounds__(kNbBlock, Pol::kChunk ? 6 : 5)
 k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *__restrict__ act, int64_t n_act,
-           const double *__restrict__ h2, double eps2, int64_t n_hard, int64_t j_chunk, int max_nb,
-           double *__restrict__ part, int32_t *__restrict__ seg_cnt, SegT *__restrict__ seg)
+           const double *__restrict__ h2, double eps2, int64_t n_hard, int64_t j_chunk, int max_nb, int n_split,
+           double *__restrict__ part, int32_t *__restrict__ seg_cnt, SegT *__restrict__ seg, Places places)
 {
     using Rec = typename Pol::Rec;
     using ET = typename Pol::ET;
     using Part = typename Pol::Part;
-    const int64_t q = int64_t(blockIdx.x) * kNbBlock + threadIdx.x;
-    const int split = blockIdx.y;
+    int64_t tile_i;
+    int split;
+    if (!place(places, n_split, &tile_i, &split)) return;   // the whole workgroup
+    const int64_t q = tile_i * kNbBlock + threadIdx.x;
     const int64_t j0 = int64_t(split) * j_chunk;
     const int64_t j1 = (j0 + j_chunk < n) ? j0 + j_chunk : n;   // j0 < n for every split
     const bool row = q < n_act;
@@ -237,7 +239,6 @@ k_force_nb(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t *
     flush<Part, 1>(&p, &acc);
     if (!row) return;
     // split-fastest: the finishing kernel's lanes read consecutive splits
-    const int n_split = int(gridDim.y);
 #pragma unroll
     for (int c = 0; c < 6; ++c) part[(int64_t(c) * n_act + q) * n_split + split] = acc[c];
     seg_cnt[q * n_split + split] = cnt;
@@ -355,13 +356,13 @@ k_nb_finish(const typename Pol::Rec *__restrict__ rec, int64_t n, const int32_t 
 template <class Pol, class SegT>
 hipError_t run_nb(const NbArgs &a, hipStream_t s, int n_split, int64_t j_chunk)
 {
-    const unsigned tiles = unsigned((a.n_act + kNbBlock - 1) / kNbBlock);
+    const Places places = places_for((a.n_act + kNbBlock - 1) / kNbBlock, n_split, true);
     double *part = a.scratch;
     int32_t *seg_cnt = reinterpret_cast<int32_t *>(part + int64_t(n_split) * 6 * a.n_act);
     SegT *seg = reinterpret_cast<SegT *>(seg_cnt + int64_t(n_split) * a.n_act);
-    hipLaunchKernelGGL((k_force_nb<Pol, SegT>), dim3(tiles, unsigned(n_split)), dim3(kNbBlock), 0, s,
+    hipLaunchKernelGGL((k_force_nb<Pol, SegT>), dim3(place_grid(places)), dim3(kNbBlock), 0, s,
                        static_cast<const typename Pol::Rec *>(a.rec), a.n, a.act, a.n_act, a.h2, a.eps2, a.n_hard,
-                       j_chunk, a.max_nb, part, seg_cnt, seg);
+                       j_chunk, a.max_nb, n_split, part, seg_cnt, seg, places);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_nb_finish<Pol, SegT>), dim3(unsigned(a.n_act)), dim3(64), 0, s,
@@ -404,9 +405,13 @@ int nb_split(int precision, int64_t n, int64_t n_act, int max_nb, int64_t scratc
     if (fit4 < 1) return 0;
     int64_t sp = (8192 + tiles - 1) / tiles;
     // (FP64: shorter than 128 particles only up to 512 splits, whose sums and lists
-    // kernel 2 adds up: n = 40000, 300 rows 56 us with 313 splits, 80 with 1250)
+    // kernel 2 adds up: n = 40000, 300 rows 56 us with 313 splits, 80 with 1250, and
+    // with three waves to a SIMD at most: n = 3000, 3000 rows 48 us with 94 splits, 35
+    // with 47)
     const int64_t by_n = (n + kNbChunk - 1) / kNbChunk, by_grain = (n + nb_grain(precision) - 1) / nb_grain(precision);
-    const int64_t fine = by_grain < 512 ? by_grain : 512;
+    const int64_t few = 3072 / tiles > 1 ? 3072 / tiles : 1;   // (three such waves to a SIMD)
+    int64_t fine = by_grain < 512 ? by_grain : 512;
+    if (fine > few) fine = few;
     if (sp > (by_n > fine ? by_n : fine)) sp = by_n > fine ? by_n : fine;
     if (sp > 65535) sp = 65535;
     const int64_t sp2 = sp < fit2 ? sp : fit2;

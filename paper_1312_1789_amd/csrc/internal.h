@@ -129,6 +129,38 @@ __device__ __forceinline__ double lane_sum(const double *__restrict__ src, int l
     return s;
 }
 
+// Which i-tile and split a workgroup of a force kernel has.  The dispatcher places
+// workgroup g on XCD g mod 8.  Stored split-fastest, 16 consecutive splits of a row
+// share a memory line, and 8-byte stores to one line from several XCDs reach memory
+// one by one; so each unit of 2^shift consecutive splits of an i-tile goes to one
+// XCD, as large (up to 16) as leaves 256 units.  In the plain order (units of one)
+// the splits of a tile lie on one XCD only where 8 divides the number of tiles: n =
+// 32768, 17 tiles of 64 rows MIXED order 4, 256 splits: 60 us, 47 by units (16 tiles:
+// 46 and 45).
+constexpr int kXcdCount = 8;
+struct Places {
+    unsigned tiles, units;
+    int shift;
+};
+inline Places places_for(int64_t tiles, int n_split, bool units)
+{
+    Places p{unsigned(tiles), 0, 0};
+    while (units && p.shift < 4 && tiles * n_split >= (int64_t(256) << (p.shift + 1))) ++p.shift;
+    p.units = p.tiles * ((unsigned(n_split) + (1u << p.shift) - 1u) >> p.shift);
+    return p;
+}
+inline unsigned place_grid(const Places &p) { return (p.units + kXcdCount - 1) / kXcdCount * kXcdCount << p.shift; }
+
+// False for a workgroup past the last unit or split.
+__device__ __forceinline__ bool place(const Places &p, int n_split, int64_t *tile, int *split)
+{
+    const unsigned slot = blockIdx.x / kXcdCount, u = (slot >> p.shift) * kXcdCount + blockIdx.x % kXcdCount;
+    const unsigned group = u / p.tiles;
+    *tile = u - group * p.tiles;
+    *split = int((group << p.shift) + (slot & ((1u << p.shift) - 1u)));
+    return u < p.units && *split < n_split;
+}
+
 // Force launch request.
 struct ForceArgs {
     const void *rec;        // predicted records

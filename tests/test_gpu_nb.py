@@ -170,6 +170,28 @@ def test_nb_long_split():
     sim.close()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("rows", [64, 65, 1100])
+def test_nb_units_of_splits(rows, precision):
+    """One, two and eighteen row tiles of a system with 200 to 500 splits: units
+    of one, two and sixteen consecutive splits, ragged last ones; checked on 40
+    rows.  (FP64 splits shorter than 128 particles only where they leave three waves
+    to a SIMD: not with 1100 rows.)"""
+    n = 30011
+    model = nbody_ics.plummer(n, 89)
+    sim = _sim(model, precision, 1e-8, 2)
+    act = np.sort(np.random.default_rng(890 + rows).choice(n, rows, replace=False)).astype(np.int32)
+    h2 = np.full(rows, 1e-4)
+    pick = np.unique(np.linspace(0, rows - 1, 40).astype(int))
+    h2r, margin = band_free_radii(model.x, act[pick], 891, k_max=30)
+    h2[pick] = h2r
+    got = _run(sim, act, h2, 512)
+    ref = oracle.force_nb(OracleConfig(order=4, eps2=1e-8, n_hard=2), model.m, model.x, model.v, act[pick], h2r, 512)
+    sub = {k: (v[:, pick] if v.ndim == 2 and k in PARTS else v[pick]) for k, v in got.items()}
+    _compare(sub, ref, pick.size, 512, precision, "%d rows" % rows)
+    sim.close()
+
+
 def test_nb_one_split_and_scratch_limit():
     """15000 rows of a 20000-particle system with room for 2048 neighbours
     each fit the scratch only as one j-split; 20000 rows with 4096 do not fit
