@@ -241,7 +241,11 @@ __host__ __device__ inline int small_group(int64_t n_act, int n_split)
 
 // The end of a block step and the schedule of the next one (step.hip).
 constexpr int kStepBlock = 256;                    // particles (and threads) per workgroup
-constexpr int64_t kStepMaxN = int64_t(1) << 20;    // systems it takes
+// Systems it takes: its last workgroup goes over the times of all blocks, which
+// costs as much as the launches saved at about n = 220000 (a step of a run, MIXED order
+// 4: n = 131072 32 us, separate kernels 44; n = 180000 57 and 59; n = 262144 49 and 45;
+// n = 2^20 111 and 77).
+constexpr int64_t kStepMaxN = 3 * (int64_t(1) << 16);
 constexpr int kStepGather = 4096;                  // active sets it lists itself
 constexpr int kStepSub = 64;                       // workgroups per arrival counter
 constexpr int kStepCounters = int(kStepMaxN / kStepBlock) / kStepSub + 1;

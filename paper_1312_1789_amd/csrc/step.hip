@@ -177,7 +177,7 @@ __device__ __forceinline__ void schedule(const StepArgs &a, int nb, int64_t *wm,
     const int64_t seq = a.mode == kStepSchedule ? a.seq : sc->seq + 1;
     int64_t bt[PER];
     int bc[PER];
-    constexpr int kAhead = PER <= 4 ? 2 : 1;   // candidates of each block loaded with its time
+    constexpr int kAhead = 2;   // candidates of each block loaded with its time
     int32_t c0[PER][kAhead];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -386,7 +386,6 @@ k_step(StepArgs a)
     __syncthreads();
     if (!s_last) return;
     if (nb <= kStepBlock) schedule<1>(a, nb, wm, wcnt, wbig, soff);
-    else if (nb <= 4 * kStepBlock) schedule<4>(a, nb, wm, wcnt, wbig, soff);
     else schedule<kStepBlocks / kStepBlock>(a, nb, wm, wcnt, wbig, soff);
 }
 

@@ -116,8 +116,8 @@ def test_active_sets_by_block(n, most):
 
 
 # the blocks of the last workgroup's four waves: 64 to a wave with one block per
-# thread (n <= 65536), 256 with four, 1024 with sixteen
-@pytest.mark.parametrize("n, per_wave", [(20000, 64), (60000, 64), (200000, 256), (600000, 1024)])
+# thread (n <= 65536), 192 with three; 196608 is the largest system of the step kernel
+@pytest.mark.parametrize("n, per_wave", [(20000, 64), (60000, 64), (130000, 192), (196608, 192), (196609, 192)])
 @pytest.mark.parametrize("where", ["last", "middle", "apart"])
 @pytest.mark.parametrize("due", [3, 9, 70])
 def test_active_sets_in_late_waves(n, per_wave, where, due):
