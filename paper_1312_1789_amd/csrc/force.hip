@@ -552,7 +552,9 @@ void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool 
 // third).  One row per lane beyond: with many waves
 // the scalar path, whose j records cost no LDS bandwidth (90000 rows MIXED order 4:
 // LDS 6261, scalar 5459 us), in workgroups of 128 (MIXED from twice as many on: n =
-// 32768, 4096 rows order 6 scalar 205, LDS 196 us, n = 120000, 2500 rows 384 and 398);
+// 32768, 4096 rows order 6 scalar 205, LDS 196 us, n = 120000, 2500 rows 384 and 398; and
+// from 16 row tiles on: n = 2^20, 500 rows order 6 716 and 674, 300 rows order 8 705
+// and 685, but 1000 rows order 6 1248 and 1275);
 // but DS, whose
 // adds keep more registers, and MIXED order 4 with the potential, whose self pairs
 // are compared in scalar registers, stay on LDS tiles (n = 120000, 2500 rows DS order
@@ -574,7 +576,7 @@ void default_shape(int precision, int order, bool pot, int64_t n, int64_t n_act,
     }
     const int64_t wt = (n_act + 63) / 64;
     const bool scalar = precision == NBODY_FP64    ? wt * n >= int64_t(16384) * 128
-                        : precision == NBODY_MIXED ? wt * n >= int64_t(32768) * 128 && !(order == 4 && pot)
+                        : precision == NBODY_MIXED ? wt >= 16 && wt * n >= int64_t(32768) * 128 && !(order == 4 && pot)
                                                    : false;
     if (scalar) {
         *block = 128;
