@@ -224,6 +224,19 @@ def test_energy_pair_tiles(n, n_hard, eps2):
     assert abs(W - Wo) <= 1e-12 * abs(Wo)
 
 
+@pytest.mark.parametrize("n", [255, 256, 257])
+def test_energy_one_row_per_lane(n):
+    """The largest systems with one row per lane, and the first with two: the
+    same bounds (and reasons) as test_energy_pair_tiles."""
+    model = nbody_ics.plummer(n, 310 + n)
+    for n_hard in (0, 3, n):
+        sim = _sim(model, 4, n_hard=n_hard, eps2=1e-4)
+        T, W = sim.energy()
+        To, Wo = oracle.energy(_ocfg(sim), model.m, model.x, model.v)
+        assert abs(T - To) <= 1e-12 * abs(To)
+        assert abs(W - Wo) <= 1e-12 * abs(Wo)
+
+
 def test_c1_integration_vs_oracle():
     """The small parity workload: Plummer n=1024, 4th order, eta=0.01,
     eps=1e-4, FP64, t = 0 -> 0.125: same block-step sequence at the start,
