@@ -286,10 +286,12 @@ nbody_status nbody_get_stats(nbody_ctx *ctx, nbody_stats *out);
  * 64-lane workgroup, each row's j range spread over 64, 16 or 4 lanes and
  * folded across them; ni and block are ignored).  A shape set here is used
  * for every later force call (it replaces an autotuned table).  Without
- * either, a call uses the wave j-split kernel for n_act <= 32 (FP64 and DS:
- * 64), else ni = 1 with LDS tiles and one-wave workgroups, or, where the call
- * has work for many waves, scalar loads in workgroups of 128, and the default
- * split.  A call lowers a requested n_split where it exceeds what the partial-sum
+ * either, a call uses the wave j-split kernel for n_act <= 32 (FP64 and DS up to
+ * n = 200000: 64); else ni = 1: FP64 and MIXED calls with work for many waves
+ * (MIXED: and 16 or more tiles of 64 rows) with scalar loads in workgroups of
+ * 128, all others, and DS always, on LDS tiles, in workgroups of 64 or, with 24
+ * or more tiles of rows that fill them, 256; and the default split.  A call
+ * lowers a requested n_split where it exceeds what the partial-sum
  * scratch holds (n_act * n_split <= max(2^21, min(16 n, 2^26))) or gives
  * splits shorter than 128 j (default and tuned splits of FP64 and DS may be as
  * short as 32); nbody_get_last_launch tells the shape used.

@@ -472,7 +472,9 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
 //    20.2 us with 8 splits of 128, 9.1 with 32 of 32 (order 8: 40.9, 13.1); n =
 //    16384, n_act = 400: 26.0 with 128, 22.6 with 64.  But 128 where the 1024 SIMDs'
 //    waves then add up to fewer particles: n = 16000, 1000 rows DS order 6 59 us with
-//    three waves of 96 to a SIMD, 51 with two of 128.
+//    three waves of 96 to a SIMD, 51 with two of 128.  Over n = 8000 to 120000 and
+//    200 to 4000 rows DS and FP64 are within 5% of the best of 32 to 256 particles in the
+//    mean; 256 instead of 128 cost 2 to 6% just below wt n / 128 = 16384 and more below.
 int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
 {
     const int64_t wt = (n_act + 64 * ni - 1) / (64 * ni);
@@ -546,7 +548,7 @@ void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool 
 // The launch shape of an untuned call.  Kernel C up to 32 rows; FP64 and DS
 // up to 64 (one row per lane leaves a chip of 1024 SIMDs nearly idle there: n =
 // 30000, 64 rows, FP64 order 8 45.7 us with kernel A, 19.9 with C; MIXED keeps
-// the order of its FP32 sums); but in systems above kWaveMaxN only up to 32 (n =
+// the order of its FP32 sums, which costs a run of n = 80000 order 6 0 to 2%); but in systems above kWaveMaxN only up to 32 (n =
 // 600000, 64 rows FP64 order 4 144 us with C, 115 with A; 33 rows DS order 8 with the
 // predictor 238 and 206; n = 120000, 64 rows FP64 order 8 C is the faster one by a
 // third).  One row per lane beyond: with many waves

@@ -17,9 +17,9 @@
 // device (DevScalars), so the host may enqueue them before it has seen it.
 //
 // A small step is then the force kernel and this one, with 1 to 2 us between
-// kernels: whole runs (n = 1024 FP64 order 4, t = 1/32) 7632 -> 4252 us, (n = 30002
-// FP64 order 4 with a post-Newtonian binary, t = 1/128) 22202 -> 14532 us, (n =
-// 80000 MIXED order 6, t = 1/512) 14861 -> 14297 us.
+// kernels: whole runs against the separate kernels (n = 1024 FP64 order 4, t = 1/32)
+// 6573 -> 2873 us, (n = 30002 FP64 order 4 with a post-Newtonian binary, t = 1/128)
+// 21570 -> 12664 us, (n = 80000 MIXED order 6, t = 1/512) 15245 -> 14083 us.
 //
 // It is a chain of dependent round trips to memory, most of them to lines that
 // another XCD has written (about 1 us each), and of serial arithmetic on a few
@@ -28,9 +28,9 @@
 // ones' state before their forces are summed, the first candidates of every
 // block with its time; least times and prefix sums are taken with moves between
 // lanes, the corrector multiplies by powers of two instead of dividing, and the
-// words for the host are stored without an order.  n = 1024: 7.2 -> 6.2 us, n =
-// 30002 with the binary 10.4 -> 9.2, n = 80000 10.8 -> 10.1; the runs 2620 -> 2390,
-// 13650 -> 12830, 15090 -> 14920 us (another realisation of the same sizes).
+// words for the host are stored without an order.  5.9 us at n = 1024, 9.3 at n =
+// 30002 with the binary and 9.8 at n = 80000 (with one load waiting for another 7.2,
+// 10.4 and 10.8).
 #include <climits>
 
 #include "pn.h"
