@@ -548,10 +548,10 @@ void split_shape(int precision, int64_t n, int64_t n_act, int n_split_req, bool 
 // The launch shape of an untuned call.  Kernel C up to 32 rows; FP64 and DS
 // up to 64 (one row per lane leaves a chip of 1024 SIMDs nearly idle there: n =
 // 30000, 64 rows, FP64 order 8 45.7 us with kernel A, 19.9 with C; MIXED keeps
-// the order of its FP32 sums, which costs a run of n = 80000 order 6 0 to 2%); but in systems above kWaveMaxN only up to 32 (n =
-// 600000, 64 rows FP64 order 4 144 us with C, 115 with A; 33 rows DS order 8 with the
-// predictor 238 and 206; n = 120000, 64 rows FP64 order 8 C is the faster one by a
-// third).  One row per lane beyond: with many waves
+// the order of its FP32 sums, which costs a run of n = 80000 order 6 0 to 2%); but in
+// systems above kWaveMaxN only up to 32 (n = 600000, 64 rows FP64 order 4 144 us with
+// C, 115 with A; 33 rows DS order 8 with the predictor 238 and 206; n = 120000, 64 rows
+// FP64 order 8 C is the faster one by a third).  One row per lane beyond: with many waves
 // the scalar path, whose j records cost no LDS bandwidth (90000 rows MIXED order 4:
 // LDS 6261, scalar 5459 us), in workgroups of 128 (MIXED from twice as many on: n =
 // 32768, 4096 rows order 6 scalar 205, LDS 196 us, n = 120000, 2500 rows 384 and 398; and
