@@ -463,8 +463,11 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
 //    us with 6 splits, 9280 with 23; n = 262144, n_act = 3001 994 with 171, 926
 //    with 683;
 //  - otherwise a MIXED row takes its FP32 chunks (128 particles) one to a wave (two
-//    cost 4 to 12% from 4096 waves on, 20 to 60% below; mean of orders 4 to 8 over n =
-//    8000 to 120000);
+//    cost 12% between 4096 and 8192 waves, 20 to 60% below; mean of orders 4 to 8 over
+//    n = 8000 to 120000), and two above 8192 waves: there two cost 4% as long as the
+//    partial sums stay in cache, but less memory (n = 32768, 2048 rows order 8 with the
+//    potential, other inputs on every call: 169 us with one, 162 with two; n = 600000,
+//    65 rows order 8 185 and 171);
 //  - FP64 and DS sums have no chunks to keep, and a wave that walks 128
 //    particles alone on its SIMD is all latency (28 us at order 4, FP64, for
 //    any n): as few as 32 each, about 3072 waves, at most about 1250 splits (the
@@ -484,7 +487,7 @@ int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
         if (c < 256 && (precision != NBODY_FP64 || wt * n >= int64_t(16384) * 256)) c = 256;
         return c < 8192 ? c : 8192;
     }
-    if (precision == NBODY_MIXED) return kMixedChunk;
+    if (precision == NBODY_MIXED) return wt * n >= int64_t(8192) * kMixedChunk ? 2 * kMixedChunk : kMixedChunk;
     int64_t c = wt * n / 3072 > n / 1250 ? wt * n / 3072 : n / 1250;
     c = up(c, 32);
     c = c < 32 ? 32 : (c > 128 ? 128 : c);
