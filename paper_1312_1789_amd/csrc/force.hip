@@ -454,11 +454,13 @@ hipError_t run_prec(int precision, const ForceArgs &a, hipStream_t s, const Shap
 // The default j-split of kernels A and B, sized in waves of 64 NI rows (wt row
 // tiles) that walk c particles each:
 //  - many (wt n / 128 >= 16384, several rounds of waves on the chip): about
-//    32768 waves of at least 128 particles (256 in MIXED and DS, or if that still
-//    gives 16384), so that the last round is a small part of the call, and at
-//    most 8192 (a wave is then some microseconds of work to a 100-byte partial
-//    row; n = 32768, n_act = 4096 MIXED order 8 with the potential 334 us with 256
-//    splits, 297 with 128).  About 8192 waves, two or
+//    32768 waves of at least 256 particles (128 in FP64 with fewer than 32 row tiles
+//    unless 256 still give 16384 waves), so that the last round is a small part
+//    of the call, and at most 8192 (a wave is then some microseconds of work to a
+//    100-byte partial row; n = 32768, n_act = 4096 MIXED order 8 with the potential
+//    334 us with 256 splits, 297 with 128; n = n_act = 16000 FP64 order 8 908 with
+//    125 splits, 861 with 63; but n = 600000, 200 rows FP64 order 4 220 with 128
+//    particles to a wave, 241 with 256).  About 8192 waves, two or
 //    three rounds, had cost 10-30% of it: n_act = n = 90000 MIXED order 6 11219
 //    us with 6 splits, 9280 with 23; n = 262144, n_act = 3001 994 with 171, 926
 //    with 683;
@@ -484,7 +486,7 @@ int64_t default_chunk(int precision, int64_t n, int64_t n_act, int ni)
     const auto up = [](int64_t v, int64_t g) { return (v + g - 1) / g * g; };
     if (wt * n >= int64_t(16384) * 128) {
         int64_t c = up(wt * n / 32768, 128);
-        if (c < 256 && (precision != NBODY_FP64 || wt * n >= int64_t(16384) * 256)) c = 256;
+        if (c < 256 && (precision != NBODY_FP64 || wt >= 32 || wt * n >= int64_t(16384) * 256)) c = 256;
         return c < 8192 ? c : 8192;
     }
     if (precision == NBODY_MIXED) return wt * n >= int64_t(8192) * kMixedChunk ? 2 * kMixedChunk : kMixedChunk;
